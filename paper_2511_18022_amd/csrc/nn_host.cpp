@@ -34,23 +34,6 @@ uint64_t splitmix64(uint64_t &s)
 
 double uniform01(uint64_t &s) { return (double)(splitmix64(s) >> 11) * (1.0 / 9007199254740992.0); }
 
-// Scratch of one top-k selection.
-struct TopkScratch {
-    NnSelect *sel = nullptr;
-    unsigned long long *hist = nullptr, *base = nullptr;
-    unsigned int *cnt = nullptr;
-    int64_t cap_blocks = 0;
-};
-
-void free_topk(TopkScratch &k)
-{
-    if (k.sel) (void)hipFree(k.sel);
-    if (k.hist) (void)hipFree(k.hist);
-    if (k.base) (void)hipFree(k.base);
-    if (k.cnt) (void)hipFree(k.cnt);
-    k = TopkScratch();
-}
-
 }  // namespace
 
 struct split_nn {
@@ -84,7 +67,7 @@ struct split_nn {
     int64_t cap_btours = 0, cap_perm = 0, cap_losshist = 0;
     int32_t cap_blab = 0;
     // screening
-    TopkScratch tk;
+    NnTopk *tk = nullptr;
     float *pred = nullptr;
     int64_t cap_pred = 0;
     int32_t *sidx = nullptr, *stours = nullptr;
@@ -341,30 +324,30 @@ split_status check_ids(split_nn *nn, const char *who, hipStream_t st)
     return SPLIT_OK;
 }
 
-split_status topk_run(split_ctx *ctx, TopkScratch &k, const float *scores, int64_t C, int64_t K,
+// The K smallest of C scores with scratch *k (allocated and cleared by its first call; a
+// selection leaves it ready for the next). Waits for the stream: one scratch serves any stream.
+split_status topk_run(split_ctx *ctx, NnTopk **k, const float *scores, int64_t C, int64_t K,
                       int32_t *idx, hipStream_t st)
 {
-    const int64_t nb = (C + 255) / 256;
-    if (!k.sel || nb > k.cap_blocks) {
-        if (hipDeviceSynchronize() != hipSuccess)
-            return ctx_fail(ctx, SPLIT_E_HIP, "top-k: hipDeviceSynchronize failed");
-        free_topk(k);
-        if (hipMalloc(&k.sel, sizeof(NnSelect)) != hipSuccess ||
-            hipMalloc(&k.hist, sizeof(unsigned long long) * 256) != hipSuccess ||
-            hipMalloc(&k.cnt, sizeof(unsigned int) * 2 * (size_t)nb) != hipSuccess ||
-            hipMalloc(&k.base, sizeof(unsigned long long) * 2 * (size_t)nb) != hipSuccess)
+    if (!*k) {
+        if (hipMalloc(k, sizeof(NnTopk)) != hipSuccess) {
+            *k = nullptr;
             return ctx_fail(ctx, SPLIT_E_NOMEM, "top-k: scratch allocation failed");
-        k.cap_blocks = nb;
+        }
+        if (hipMemsetAsync(*k, 0, sizeof(NnTopk), st) != hipSuccess) {
+            (void)hipFree(*k);
+            *k = nullptr;
+            return ctx_fail(ctx, SPLIT_E_HIP, "top-k: clearing the scratch failed");
+        }
     }
-    NnSelect init = {0u, 0u, (unsigned long long)K};
-    if (hipMemcpyAsync(k.sel, &init, sizeof init, hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipMemsetAsync(k.hist, 0, sizeof(unsigned long long) * 256, st) != hipSuccess)
-        return ctx_fail(ctx, SPLIT_E_HIP, "top-k: setup copies failed");
-    const hipError_t e = nn_launch_topk(scores, C, K, k.sel, k.hist, k.cnt, k.base, idx, st);
-    if (e != hipSuccess) return ctx_fail(ctx, SPLIT_E_HIP, "top-k: %s", hipGetErrorString(e));
-    // the init struct lives on this stack frame: finish before returning
-    if (hipStreamSynchronize(st) != hipSuccess)
-        return ctx_fail(ctx, SPLIT_E_HIP, "top-k: hipStreamSynchronize failed");
+    hipError_t e = nn_launch_topk(scores, C, K, *k, idx, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) {
+        // a selection that did not run to its end may leave counts behind
+        (void)hipFree(*k);
+        *k = nullptr;
+        return ctx_fail(ctx, SPLIT_E_HIP, "top-k: %s", hipGetErrorString(e));
+    }
     return SPLIT_OK;
 }
 
@@ -386,7 +369,7 @@ void free_nn(split_nn *nn)
         if (p) (void)hipFree(p);
     if (nn->musd) (void)hipFree(nn->musd);
     if (nn->h_err) (void)hipHostFree(nn->h_err);
-    free_topk(nn->tk);
+    if (nn->tk) (void)hipFree(nn->tk);
     for (auto &pr : nn->tpairs) {
         (void)hipEventDestroy(pr.first);
         (void)hipEventDestroy(pr.second);
@@ -783,10 +766,8 @@ split_status split_topk_smallest(split_ctx *ctx, const float *scores, int64_t C,
         return ctx_fail(ctx, SPLIT_E_INVAL, "split_topk_smallest: need scores, idx and "
                         "1 <= K <= C < 2^31");
     Guard g(ctx_device(ctx));
-    TopkScratch k;
-    const split_status s = topk_run(ctx, k, scores, C, K, idx, (hipStream_t)hip_stream);
-    free_topk(k);
-    return s;
+    NnTopk **k = reinterpret_cast<NnTopk **>(ctx_topk_scratch(ctx));
+    return topk_run(ctx, k, scores, C, K, idx, (hipStream_t)hip_stream);
 }
 
 split_status split_nn_shortlist(split_nn *nn, const int32_t *tours, int32_t T, int32_t n,
@@ -818,7 +799,7 @@ split_status split_nn_shortlist(split_nn *nn, const int32_t *tours, int32_t T, i
     }
     s = check_ids(nn, "split_nn_shortlist", st);
     if (s != SPLIT_OK) return s;
-    return topk_run(nn->ctx, nn->tk, pr, T, K, idx, st);
+    return topk_run(nn->ctx, &nn->tk, pr, T, K, idx, st);
 }
 
 split_status split_nn_screen(split_nn *nn, const int32_t *cands, int64_t C, int32_t n, int64_t K,
@@ -861,7 +842,7 @@ split_status split_nn_screen(split_nn *nn, const int32_t *cands, int64_t C, int3
         nn->cap_sidx = K;
         nn->cap_stours = K * n;
     }
-    s = topk_run(nn->ctx, nn->tk, pr, C, K, nn->sidx, st);
+    s = topk_run(nn->ctx, &nn->tk, pr, C, K, nn->sidx, st);
     if (s != SPLIT_OK) return s;
     NN_TRY(nn, nn_launch_gather(cands, nullptr, nn->sidx, (int32_t)K, n, nn->stours, nullptr, st));
     std::vector<int32_t> hidx((size_t)K), htours((size_t)K * n);

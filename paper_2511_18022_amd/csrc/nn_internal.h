@@ -46,11 +46,20 @@ struct NnWeights {
     uint16_t *g[4];  // layer l in MFMA fragment order (the fused prediction kernel's reads)
 };
 
-// Radix-select state: the key prefix found so far, its mask, and the rank still to reach.
-struct NnSelect {
-    uint32_t prefix;
-    uint32_t mask;
-    unsigned long long rank;
+// Device scratch of one top-k selection (all zero before the first). After `pass` + 1 digit passes,
+// state[pass] holds the key prefix found, its mask and the rank still to reach; hist the digit
+// counts of each pass, which a selection leaves zeroed; cnt, per chunk of scores, the keys below
+// and equal to the threshold.
+constexpr int kTopkBins = 2048;
+constexpr int kTopkChunks = 1024;
+constexpr int kTopkSmall = 16384;  // scores that one workgroup selects from by itself
+struct NnTopkState {
+    uint32_t prefix, mask, rank;
+};
+struct NnTopk {
+    NnTopkState state[3];
+    uint32_t hist[3][kTopkBins];
+    uint32_t cnt[2 * kTopkChunks];
 };
 
 hipError_t nn_launch_dstats(const int16_t *demand, int64_t ld, int64_t S, int32_t N, double *musd,
@@ -94,8 +103,7 @@ hipError_t nn_launch_moves(const int32_t *cur, const int32_t *moves, int32_t cou
                            int32_t *out, hipStream_t st);
 hipError_t nn_launch_check_ids(const int32_t *ids, long long count, int32_t N, int32_t *err,
                                hipStream_t st);
-hipError_t nn_launch_topk(const float *s, long long C, long long K, NnSelect *sel,
-                          unsigned long long *hist, unsigned int *cnt, unsigned long long *base,
-                          int32_t *idx, hipStream_t st);
+hipError_t nn_launch_topk(const float *s, long long C, long long K, NnTopk *g, int32_t *idx,
+                          hipStream_t st);
 
 }  // namespace splitgpu

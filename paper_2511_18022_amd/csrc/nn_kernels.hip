@@ -991,118 +991,297 @@ __global__ __launch_bounds__(256) void nn_pack_kernel(const float *P, NnWeights 
 
 // ------------------------------------------------------------------------- top-k
 
+// Three digits of a 32-bit key, from the top: 11, 11 and 10 bits.
+__device__ constexpr int kTopkShift[3] = {21, 10, 0};
+__device__ constexpr uint32_t kTopkMask[3] = {2047u, 2047u, 1023u};
+
 __device__ __forceinline__ uint32_t nn_key(float f)
 {
     const uint32_t u = __float_as_uint(f);
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);  // increasing with f
 }
 
-// Histogram of the 8-bit digit `shift` of the keys whose higher digits equal sel->prefix.
-__global__ __launch_bounds__(256) void nn_topk_hist_kernel(const float *s, long long C,
-                                                           const NnSelect *sel, int shift,
-                                                           unsigned long long *hist)
+// Adds one to h[d] for every lane with `in`. The lanes that share the first such lane's digit add
+// theirs at once: costs of one population share sign, exponent and leading fraction bits, and 64
+// single additions to one LDS word would run one after the other.
+__device__ __forceinline__ void count_digit(uint32_t *h, bool in, uint32_t d)
 {
-    __shared__ unsigned int h[256];
-    h[threadIdx.x] = 0;
-    __syncthreads();
-    const uint32_t prefix = sel->prefix, pmask = sel->mask;
-    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < C;
-         i += (long long)gridDim.x * 256) {
-        const uint32_t k = nn_key(s[i]);
-        if ((k & pmask) == prefix) atomicAdd(&h[(k >> shift) & 255u], 1u);
-    }
-    __syncthreads();
-    if (h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], (unsigned long long)h[threadIdx.x]);
+    const unsigned long long m = __ballot(in);
+    if (m == 0) return;
+    const int leader = __builtin_ctzll(m);
+    const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, leader);
+    const unsigned long long same = __ballot(in && d == d0);
+    if ((int)(threadIdx.x & 63) == leader) atomicAdd(&h[d0], (uint32_t)__popcll(same));
+    if (in && d != d0) atomicAdd(&h[d], 1u);
 }
 
-// One thread: pick the digit where the running count reaches the remaining rank; clear hist.
-__global__ void nn_topk_pick_kernel(NnSelect *sel, int shift, unsigned long long *hist)
+// The digit of the kTopkBins counts h (LDS or memory) where the running count reaches `rank`
+// (1 <= rank <= their total), and the count below it: every thread of a workgroup of TH threads
+// gets both. part: TH / 64 + 2 words of LDS, free again after the caller's next barrier.
+template <int TH>
+__device__ __forceinline__ void pick_digit(const uint32_t *h, uint32_t *part, uint32_t rank,
+                                           uint32_t &digit, uint32_t &below)
 {
-    unsigned long long below = 0;
-    int d = 0;
-    for (; d < 256; ++d) {
-        if (below + hist[d] >= sel->rank) break;
-        below += hist[d];
+    constexpr int PER = kTopkBins / TH;
+    const int tid = threadIdx.x, lane = tid & 63;
+    uint32_t bin[PER], mine = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        bin[k] = h[tid * PER + k];
+        mine += bin[k];
     }
-    if (d > 255) d = 255;  // unreachable when rank <= the candidates left
-    sel->rank -= below;
-    sel->prefix |= (uint32_t)d << shift;
-    sel->mask |= 255u << shift;
-    for (int k = 0; k < 256; ++k) hist[k] = 0;
-}
-
-// Per block of 256 candidates: how many keys are below the threshold and how many equal it.
-__global__ __launch_bounds__(256) void nn_topk_count_kernel(const float *s, long long C,
-                                                            const NnSelect *sel,
-                                                            unsigned int *cnt)
-{
-    __shared__ unsigned int lt, eq;
-    if (threadIdx.x == 0) {
-        lt = 0;
-        eq = 0;
+    uint32_t end = mine;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t add = __shfl_up(end, off, 64);
+        end += lane >= off ? add : 0u;
+    }
+    if (lane == 63) part[tid >> 6] = end;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < TH / 64; ++w) end += w < (tid >> 6) ? part[w] : 0u;
+    uint32_t at = end - mine;
+    if (at < rank && rank <= end) {  // one thread
+        int k = 0;
+#pragma unroll
+        for (int j = 0; j + 1 < PER; ++j) {
+            if (k == j && at + bin[j] < rank) {
+                at += bin[j];
+                k = j + 1;
+            }
+        }
+        part[TH / 64] = (uint32_t)(tid * PER + k);
+        part[TH / 64 + 1] = at;
     }
     __syncthreads();
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i < C) {
-        const uint32_t k = nn_key(s[i]);
-        if (k < sel->prefix) atomicAdd(&lt, 1u);
-        else if (k == sel->prefix) atomicAdd(&eq, 1u);
+    digit = part[TH / 64];
+    below = part[TH / 64 + 1];
+}
+
+// Up to kTopkSmall scores in one workgroup: the keys stay in registers over the three digit
+// passes, and the same workgroup writes the selected indices. Key j of thread tid is score
+// j * 1024 + tid. One launch instead of five: a search's pool of a few thousand candidates is
+// launch-bound.
+__global__ __launch_bounds__(1024) void nn_topk_small_kernel(const float *s, int32_t C, uint32_t K,
+                                                             int32_t *idx)
+{
+    constexpr int J = kTopkSmall / 1024;
+    __shared__ uint32_t h[kTopkBins];
+    __shared__ uint32_t part[1024];
+    __shared__ uint32_t wcnt[J][16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t key[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int i = j * 1024 + tid;
+        key[j] = i < C ? nn_key(s[i]) : 0u;
+    }
+    uint32_t prefix = 0, mask = 0, rank = K;
+    for (int pass = 0; pass < 3; ++pass) {
+        for (int k = tid; k < kTopkBins; k += 1024) h[k] = 0;
+        __syncthreads();
+        const int shift = kTopkShift[pass];
+        const uint32_t dmask = kTopkMask[pass];
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+            if (j * 1024 < C)
+                count_digit(h, j * 1024 + tid < C && (key[j] & mask) == prefix,
+                            (key[j] >> shift) & dmask);
+        __syncthreads();
+        uint32_t digit, below;
+        pick_digit<1024>(h, part, rank, digit, below);
+        rank -= below;
+        prefix |= digit << shift;
+        mask |= dmask << shift;
+        __syncthreads();
+    }
+    // keys below the threshold `prefix`, and the first `rank` equal ones in index order
+    const unsigned long long before = (1ull << lane) - 1;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const bool in = j * 1024 + tid < C;
+        const unsigned long long lt = __ballot(in && key[j] < prefix);
+        const unsigned long long eq = __ballot(in && key[j] == prefix);
+        if (lane == 0) wcnt[j][wave] = (uint32_t)__popcll(lt) | ((uint32_t)__popcll(eq) << 16);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        cnt[2 * blockIdx.x] = lt;
-        cnt[2 * blockIdx.x + 1] = eq;
+    // counts of both kinds stay below 2^15: one packed running sum
+    if (tid < J * 16) part[tid] = wcnt[tid >> 4][tid & 15];
+    __syncthreads();
+    for (int off = 1; off < J * 16; off <<= 1) {
+        const uint32_t add = tid >= off && tid < J * 16 ? part[tid - off] : 0u;
+        __syncthreads();
+        if (tid < J * 16) part[tid] += add;
+        __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const bool in = j * 1024 + tid < C;
+        const bool is_lt = in && key[j] < prefix, is_eq = in && key[j] == prefix;
+        const unsigned long long lt = __ballot(is_lt), eq = __ballot(is_eq);
+        const uint32_t base = part[j * 16 + wave] - wcnt[j][wave];
+        const uint32_t nlt = (base & 0xFFFFu) + (uint32_t)__popcll(lt & before);
+        const uint32_t neq = (base >> 16) + (uint32_t)__popcll(eq & before);
+        if (is_lt || (is_eq && neq < rank)) idx[nlt + min(neq, rank)] = j * 1024 + tid;
     }
 }
 
-// One workgroup: exclusive prefix of the per-block counts, in block order. Ties at the threshold
-// go to the lowest indices: a block takes min(eq, remaining ties) of them.
-__global__ __launch_bounds__(256) void nn_topk_scan_kernel(unsigned int *cnt, long long nblocks,
-                                                           const NnSelect *sel,
-                                                           unsigned long long *base)
+// What the passes so far found: the key prefix, its mask and the rank still to reach among the
+// keys that share it. Every workgroup of the next launch picks the digit of the pass before it
+// from that pass's histogram, so no workgroup has to wait for the others and no launch of its own
+// is needed for the pick.
+template <int TH>
+__device__ __forceinline__ NnTopkState topk_state(const NnTopk *g, int passes, uint32_t K,
+                                                  uint32_t *part)
 {
-    if (threadIdx.x != 0) return;
-    unsigned long long pos = 0, ties = sel->rank;  // equal keys still to take
-    for (long long b = 0; b < nblocks; ++b) {
-        const unsigned long long lt = cnt[2 * b], eq = cnt[2 * b + 1];
-        const unsigned long long take_eq = eq < ties ? eq : ties;
-        ties -= take_eq;
-        base[2 * b] = pos;
-        base[2 * b + 1] = take_eq;
-        pos += lt + take_eq;
-    }
+    NnTopkState st = {0u, 0u, K};
+    if (passes == 0) return st;
+    if (passes > 1) st = g->state[passes - 2];
+    uint32_t digit, below;
+    pick_digit<TH>(g->hist[passes - 1], part, st.rank, digit, below);
+    st.prefix |= digit << kTopkShift[passes - 1];
+    st.mask |= kTopkMask[passes - 1] << kTopkShift[passes - 1];
+    st.rank -= below;
+    return st;
 }
 
-// Write the selected indices in increasing index order.
+// Histogram of digit `pass` of the keys whose higher digits equal the prefix found so far.
+// Bound by launches and by the latency of a workgroup's 4096 scores (read 8 at a time per thread):
+// three passes of 11, 11 and 10 bits, 9.5 us each over 10^6 scores. A pass of 8 bits took 12.1 us
+// with one LDS addition per score, its pick 7.3 us as a one-thread launch, and a pick by the last
+// workgroup to finish (a ticket behind device-scope fences) 22 us a pass.
+__global__ __launch_bounds__(256) void nn_topk_hist_kernel(const float *s, long long C, uint32_t K,
+                                                           int pass, NnTopk *g)
+{
+    __shared__ uint32_t h[kTopkBins];
+    __shared__ uint32_t part[8];
+    const int tid = threadIdx.x;
+    for (int k = tid; k < kTopkBins; k += 256) h[k] = 0;
+    const NnTopkState st = topk_state<256>(g, pass, K, part);
+    if (pass > 0 && blockIdx.x == 0 && tid == 0) g->state[pass - 1] = st;
+    const int shift = kTopkShift[pass];
+    const uint32_t dmask = kTopkMask[pass];
+    __syncthreads();
+    const long long step = (long long)gridDim.x * 2048;
+    for (long long i0 = (long long)blockIdx.x * 2048; i0 < C; i0 += step) {
+        uint32_t key[8];
+        bool in[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const long long i = i0 + u * 256 + tid;
+            in[u] = i < C;
+            key[u] = in[u] ? nn_key(s[i]) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            count_digit(h, in[u] && (key[u] & st.mask) == st.prefix, (key[u] >> shift) & dmask);
+    }
+    __syncthreads();
+    for (int k = tid; k < kTopkBins; k += 256)
+        if (h[k]) atomicAdd(&g->hist[pass][k], h[k]);
+}
+
+// Per workgroup's chunk of scores: how many keys are below the threshold and how many equal it.
+// Clears the first two histograms for the next selection (the third is still being read).
+__global__ __launch_bounds__(256) void nn_topk_count_kernel(const float *s, long long C, uint32_t K,
+                                                            long long chunk, NnTopk *g)
+{
+    __shared__ uint32_t red[2][4];
+    __shared__ uint32_t part[8];
+    const int tid = threadIdx.x;
+    const NnTopkState st = topk_state<256>(g, 3, K, part);
+    if (blockIdx.x == 0 && tid == 0) g->state[2] = st;
+    for (int k = blockIdx.x * 256 + tid; k < 2 * kTopkBins; k += gridDim.x * 256)
+        g->hist[k / kTopkBins][k % kTopkBins] = 0;
+    const uint32_t T = st.prefix;
+    const long long lo = (long long)blockIdx.x * chunk, hi = lo + chunk < C ? lo + chunk : C;
+    uint32_t lt = 0, eq = 0;
+    for (long long i0 = lo; i0 < hi; i0 += 1024) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const long long i = i0 + u * 256 + tid;
+            const bool in = i < hi;
+            const uint32_t k = in ? nn_key(s[i]) : 0u;
+            lt += (uint32_t)__popcll(__ballot(in && k < T));
+            eq += (uint32_t)__popcll(__ballot(in && k == T));
+        }
+    }
+    if ((tid & 63) == 0) {
+        red[0][tid >> 6] = lt;
+        red[1][tid >> 6] = eq;
+    }
+    __syncthreads();
+    if (tid < 2) g->cnt[2 * blockIdx.x + tid] = red[tid][0] + red[tid][1] + red[tid][2] + red[tid][3];
+}
+
+// Writes the selected indices in increasing index order: every key below the threshold and the
+// first `rank` keys that equal it. A workgroup adds up the counts of the chunks before its own
+// (at most kTopkChunks of them), so no launch scans them: one thread walking 3,907 blocks of 256
+// took 396 us of a 567 us call over 10^6 scores, and ranking each index by a walk over its block's
+// flags another 38 us. This kernel takes 5.3 us there, the call 52 us.
 __global__ __launch_bounds__(256) void nn_topk_write_kernel(const float *s, long long C,
-                                                            const NnSelect *sel,
-                                                            const unsigned long long *base,
+                                                            long long chunk, NnTopk *g,
                                                             int32_t *idx)
 {
-    __shared__ unsigned int flags[256];
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    uint32_t f = 0;
-    if (i < C) {
-        const uint32_t k = nn_key(s[i]);
-        f = k < sel->prefix ? 1u : (k == sel->prefix ? 2u : 0u);
+    __shared__ uint32_t sum[2][4];
+    __shared__ uint32_t cnt[2][4][4];  // [below, equal][group u][wavefront]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t T = g->state[2].prefix, rank = g->state[2].rank;
+    for (int k = blockIdx.x * 256 + tid; k < kTopkBins; k += gridDim.x * 256) g->hist[2][k] = 0;
+    uint32_t nlt = 0, neq = 0;
+    for (unsigned k = tid; k < blockIdx.x; k += 256) {
+        nlt += g->cnt[2 * k];
+        neq += g->cnt[2 * k + 1];
     }
-    flags[threadIdx.x] = f;
+    for (int off = 32; off > 0; off >>= 1) {
+        nlt += __shfl_xor(nlt, off, 64);
+        neq += __shfl_xor(neq, off, 64);
+    }
+    if (lane == 0) {
+        sum[0][wave] = nlt;
+        sum[1][wave] = neq;
+    }
     __syncthreads();
-    if (f == 0) return;
-    // rank among this block's selected entries (below first, ties by index within the quota)
-    unsigned int before = 0, eq_before = 0;
-    for (int u = 0; u < (int)threadIdx.x; ++u) {
-        if (flags[u] == 2u) ++eq_before;
+    nlt = sum[0][0] + sum[0][1] + sum[0][2] + sum[0][3];
+    neq = sum[1][0] + sum[1][1] + sum[1][2] + sum[1][3];
+    const unsigned long long before = (1ull << lane) - 1;
+    const long long lo = (long long)blockIdx.x * chunk, hi = lo + chunk < C ? lo + chunk : C;
+    for (long long i0 = lo; i0 < hi; i0 += 1024) {
+        unsigned long long lt[4], eq[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const long long i = i0 + u * 256 + tid;
+            const bool in = i < hi;
+            const uint32_t k = in ? nn_key(s[i]) : 0u;
+            lt[u] = __ballot(in && k < T);
+            eq[u] = __ballot(in && k == T);
+        }
+        if (lane == 0) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                cnt[0][u][wave] = (uint32_t)__popcll(lt[u]);
+                cnt[1][u][wave] = (uint32_t)__popcll(eq[u]);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            uint32_t a = nlt, b = neq;  // counts before this wavefront's 64 scores of group u
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                a += w < wave ? cnt[0][u][w] : 0u;
+                b += w < wave ? cnt[1][u][w] : 0u;
+                nlt += cnt[0][u][w];
+                neq += cnt[1][u][w];
+            }
+            a += (uint32_t)__popcll(lt[u] & before);
+            b += (uint32_t)__popcll(eq[u] & before);
+            const bool is_lt = (lt[u] >> lane) & 1, is_eq = (eq[u] >> lane) & 1;
+            if (is_lt || (is_eq && b < rank))
+                idx[a + min(b, rank)] = (int32_t)(i0 + u * 256 + tid);
+        }
+        __syncthreads();  // cnt is free for the next tile
     }
-    const unsigned long long quota = base[2 * blockIdx.x + 1];
-    if (f == 2u && eq_before >= quota) return;
-    for (int u = 0; u < (int)threadIdx.x; ++u) {
-        if (flags[u] == 1u) ++before;
-        else if (flags[u] == 2u) before += 1;
-    }
-    // equal keys beyond the quota that precede this entry are not taken
-    const unsigned int skipped = eq_before > quota ? (unsigned int)(eq_before - quota) : 0u;
-    idx[base[2 * blockIdx.x] + before - skipped] = (int32_t)i;
 }
 
 // ------------------------------------------------------------------------- batches and loss
@@ -1323,30 +1502,31 @@ hipError_t nn_launch_pack(const float *P, const NnWeights &w, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t nn_launch_topk(const float *s, long long C, long long K, NnSelect *sel,
-                          unsigned long long *hist, unsigned int *cnt, unsigned long long *base,
-                          int32_t *idx, hipStream_t st)
+hipError_t nn_launch_topk(const float *s, long long C, long long K, NnTopk *g, int32_t *idx,
+                          hipStream_t st)
 {
-    const unsigned hg = (unsigned)(C < 256LL * 1024 ? grid_of(C, 256) : 1024);
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        hipLaunchKernelGGL(nn_topk_hist_kernel, dim3(hg), dim3(256), 0, st, s, C, sel, shift,
-                           hist);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(nn_topk_pick_kernel, dim3(1), dim3(1), 0, st, sel, shift, hist);
-        e = hipGetLastError();
+    if (C <= kTopkSmall) {
+        hipLaunchKernelGGL(nn_topk_small_kernel, dim3(1), dim3(1024), 0, st, s, (int32_t)C,
+                           (uint32_t)K, idx);
+        return hipGetLastError();
+    }
+    // 4096 scores per workgroup, up to 512 workgroups: each adds its nonzero bins to one histogram
+    // in memory
+    const unsigned hg = (unsigned)(C < 512LL * 4096 ? grid_of(C, 4096) : 512);
+    for (int pass = 0; pass < 3; ++pass) {
+        hipLaunchKernelGGL(nn_topk_hist_kernel, dim3(hg), dim3(256), 0, st, s, C, (uint32_t)K, pass,
+                           g);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    const unsigned nb = grid_of(C, 256);
-    hipLaunchKernelGGL(nn_topk_count_kernel, dim3(nb), dim3(256), 0, st, s, C, sel, cnt);
-    hipError_t e = hipGetLastError();
+    long long chunk = (C + kTopkChunks - 1) / kTopkChunks;
+    chunk = (chunk + 1023) / 1024 * 1024;
+    const unsigned nb = (unsigned)((C + chunk - 1) / chunk);
+    hipLaunchKernelGGL(nn_topk_count_kernel, dim3(nb), dim3(256), 0, st, s, C, (uint32_t)K,
+                       chunk, g);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(nn_topk_scan_kernel, dim3(1), dim3(256), 0, st, cnt, (long long)nb, sel,
-                       base);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(nn_topk_write_kernel, dim3(nb), dim3(256), 0, st, s, C, sel, base, idx);
-    (void)K;
+    hipLaunchKernelGGL(nn_topk_write_kernel, dim3(nb), dim3(256), 0, st, s, C, chunk, g, idx);
     return hipGetLastError();
 }
 

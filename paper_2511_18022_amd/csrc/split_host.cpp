@@ -156,6 +156,7 @@ struct split_ctx {
 
     // device address of this GPU's fixed scratch (split_eval_noalloc), looked up at creation
     unsigned char *scratch = nullptr;
+    void *topk = nullptr;  // device scratch of split_topk_smallest, kept between calls
 };
 
 struct split_graph {
@@ -655,6 +656,8 @@ bool ctx_instance(const split_ctx *ctx, int32_t *N, int *kind, const int32_t **x
     return true;
 }
 
+void **ctx_topk_scratch(split_ctx *ctx) { return &ctx->topk; }
+
 split_status ctx_fail(split_ctx *ctx, split_status st, const char *fmt, ...)
 {
     if (ctx) {
@@ -714,6 +717,7 @@ void split_ctx_destroy(split_ctx *ctx)
         (void)hipDeviceSynchronize();
         free_instance(ctx->inst);
         free_buffers(ctx->buf);
+        if (ctx->topk) (void)hipFree(ctx->topk);
         for (int k = 0; k < kStages; ++k) {
             if (ctx->h_stage[k]) (void)hipHostFree(ctx->h_stage[k]);
             if (ctx->stage_ev[k]) (void)hipEventDestroy(ctx->stage_ev[k]);

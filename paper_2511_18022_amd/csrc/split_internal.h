@@ -22,6 +22,9 @@ int ctx_device(const split_ctx *ctx);
 // false when no instance is set
 bool ctx_instance(const split_ctx *ctx, int32_t *N, int *kind, const int32_t **xy,
                   const int32_t **dist, int64_t *max_arc);
+// the context's device scratch of split_topk_smallest (NULL until its first call; freed with the
+// context)
+void **ctx_topk_scratch(split_ctx *ctx);
 // records the message as the context's last error and returns st
 split_status ctx_fail(split_ctx *ctx, split_status st, const char *fmt, ...);
 
