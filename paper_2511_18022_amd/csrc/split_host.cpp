@@ -40,6 +40,8 @@ constexpr int kGraphSlots = 2;          // a graph's launches alternate between 
 constexpr int32_t kMaxLanePerCu = 8;    // the lane kernel's LDS allows 8 workgroups per CU
 constexpr int32_t kLaneStaticPerCu = kMaxLanePerCu;  // fixed-stride grid: all resident at once
 constexpr int64_t kLaneStaticMaxRounds = 16;         // and at most this many items each
+constexpr int32_t kLongPerCu = 2;       // the long kernel's LDS allows 2 workgroups per CU
+constexpr int64_t kClassMaxArc = 2047;  // 16 states times 2 max_arc: below 2^16
 
 // Device buffers of one evaluation sequence. The context's grow with its calls; a graph owns
 // a fixed set.
@@ -99,6 +101,7 @@ struct BatchInfo {
 struct Plan {
     int form = SPLIT_FORM_LANE;
     int32_t lane_grid = 0, wave_grid = 0, maxn = 0, lane_block = 16;
+    int32_t long_grid = 0;
     bool lane_static = false, lane_uniform = false;
     uint32_t lane_bytes = 0;
 };
@@ -453,7 +456,7 @@ void stage_write(char *h, const StageLayout &L, const int32_t *tours, const int6
 // Launch configuration from the tuning. T_grid bounds T; maxn and max_id bound the tours;
 // `uniform`: every tour of the launch has the same length (so has every work item).
 Plan make_plan(const split_ctx *ctx, const split_tuning &tu, int64_t S, int64_t ld, int32_t Q,
-               int32_t T_grid, int32_t maxn, int32_t max_id, bool uniform)
+               int32_t T_grid, int32_t maxn, int32_t max_id, bool uniform, int64_t max_arc)
 {
     Plan p;
     p.form = tu.form;
@@ -478,7 +481,12 @@ Plan make_plan(const split_ctx *ctx, const split_tuning &tu, int64_t S, int64_t 
     p.lane_grid = (int32_t)(lg < items ? lg : items);
     p.lane_static = fixed;
     p.lane_uniform = uniform;
-    p.lane_block = tu.lane_block == 8 ? 8 : 16;
+    // Left to the library, the block length follows the windows of each item's first positions,
+    // where arcs this short keep every suffix offset of either length within 16 bits (at most 2 max_arc a state):
+    // n_fallback then does not depend on the length chosen.
+    const bool by_class = tu.lane_block == 0 && max_arc <= kClassMaxArc;
+    p.lane_block = by_class ? 0 : tu.lane_block == 8 ? 8 : 16;
+    p.long_grid = ctx->cus * kLongPerCu;
     p.wave_grid = tu.wave_grid > 0 ? tu.wave_grid : 65536;
     p.maxn = maxn;
     return p;
@@ -528,6 +536,8 @@ split_status enqueue_kernels(split_ctx *ctx, const Instance &in, const EvalBuffe
     ea.lane_static = p.lane_static ? 1 : 0;
     ea.lane_uniform = p.lane_uniform ? 1 : 0;
     ea.lane_block = p.lane_block;
+    ea.recount = p.form == SPLIT_FORM_LANE && p.lane_block != 8 ? 1 : 0;
+    ea.long_grid = p.long_grid;
     ea.wave_grid = p.wave_grid;
     ea.maxn = p.maxn;
 
@@ -545,12 +555,12 @@ split_status enqueue_kernels(split_ctx *ctx, const Instance &in, const EvalBuffe
         HIP_TRY(ctx, launch_mask(ea, b.d_mask, S, stream));
         HIP_TRY(ctx, launch_masked_dp(ea, b.d_mask, S, stream));
         if (stop) HIP_TRY(ctx, hipEventRecord(stop, stream));
-        HIP_TRY(ctx, launch_wave_fallback(ea, stream));
+        HIP_TRY(ctx, launch_long(ea, stream));
     } else {
         ctx->tname = lane_kernel_name();
         HIP_TRY(ctx, launch_lane(ea, stream));
         if (stop) HIP_TRY(ctx, hipEventRecord(stop, stream));
-        HIP_TRY(ctx, launch_wave_fallback(ea, stream));
+        HIP_TRY(ctx, launch_long(ea, stream));
     }
 
     MomentArgs ma;
@@ -599,7 +609,7 @@ split_status eval_batch(split_ctx *ctx, const char *who, const int32_t *tours,
     ctx->stage_ev_used[slot] = true;
 
     const Plan p = make_plan(ctx, ctx->tuning, S, ld, Q, T, bi.maxn, bi.max_id,
-                             bi.minn == bi.maxn);
+                             bi.minn == bi.maxn, ctx->inst.max_arc);
     if (p.form == SPLIT_FORM_MASK && (__int128)ctx->buf.cap_pos * S > ctx->buf.cap_mask) {
         // one int16 window start per (position row, scenario)
         HIP_TRY(ctx, hipDeviceSynchronize());
@@ -872,7 +882,8 @@ split_status split_eval_noalloc(split_ctx *ctx, const int32_t *tour, int32_t n,
                                 hipMemcpyHostToDevice, stream));
     HIP_TRY(ctx, hipMemcpyAsync(b.d_stage + L.off_tours, tour, sizeof(int32_t) * (size_t)n,
                                 hipMemcpyHostToDevice, stream));
-    const Plan p = make_plan(ctx, tu, S, ld, Q, 1, bi.maxn, bi.max_id, true);
+    const Plan p = make_plan(ctx, tu, S, ld, Q, 1, bi.maxn, bi.max_id, true,
+                             ctx->inst.max_arc);
     // the prep kernel zeroes the result block and the counters of every call
     st = enqueue_kernels(ctx, ctx->inst, b, L, p, demand, S, ld, Q, cost, S, stream, false);
     if (st != SPLIT_OK) return st;
@@ -1027,7 +1038,7 @@ split_status split_autotune(split_ctx *ctx, const int32_t *tours, const int64_t 
     split_tuning win = saved;
     double win_ms = 1e300;
     const Plan lane_probe = make_plan(ctx, split_tuning{SPLIT_FORM_LANE, 0, 0, 0, 0}, S, ld, Q,
-                                      T, bi.maxn, bi.max_id, bi.minn == bi.maxn);
+                                      T, bi.maxn, bi.max_id, bi.minn == bi.maxn, ctx->inst.max_arc);
     if (lane_probe.form == SPLIT_FORM_LANE) {
         // the block length first (it follows the window lengths, so the demand law), then the
         // grid and the order with that block length. 8-state blocks hand windows longer than
@@ -1232,7 +1243,8 @@ split_status split_graph_create(split_ctx *ctx, int32_t max_T, int64_t max_total
     if (st != SPLIT_OK) return bail(st);
     // any tour of the instance: lengths up to N, ids up to N
     // the tours of a replay are known only then: a fixed item stride only for one tour
-    gr->plan = make_plan(ctx, ctx->tuning, S, ld, Q, max_T, N, N, max_T == 1);
+    gr->plan = make_plan(ctx, ctx->tuning, S, ld, Q, max_T, N, N, max_T == 1,
+                         gr->inst.max_arc);
     if (gr->plan.form == SPLIT_FORM_MASK)
         return bail(fail(ctx, SPLIT_E_INVAL, "split_graph_create: the two-kernel form is an "
                          "ablation and is not captured"));

@@ -40,13 +40,13 @@ struct DevStats {
     unsigned long long sq_lo;  // sum of squared costs, low 64 bits
     unsigned long long sq_hi;  // sum of squared costs, high 64 bits
     int32_t err_demand;        // nonzero: some scenario has q > Q (or q < 0) on the tour
-    int32_t ovf_count;         // scenarios of this tour finished by the general kernel
+    int32_t ovf_count;         // scenarios of this tour past the lane kernel's history
 };
 
 // Batch-wide counters (reset by the prep kernel of each call).
 struct BatchCtl {
     uint32_t head;       // next work item of the lane kernel's queue
-    uint32_t ovf_total;  // scenarios marked kCostOvf, over all tours
+    uint32_t ovf_total;  // nonzero: some scenario is marked kCostOvf
 };
 
 // Per-tour arrays built on the device by the prep kernel from the tours and the instance.
@@ -110,7 +110,9 @@ struct EvalArgs {
     int32_t lane_static;     // lane kernel, fewer workgroups than items: 1 = each takes items
                              // at a fixed stride of lane_grid, 0 = from the queue
     int32_t lane_uniform;    // lane kernel: 1 = every tour of the launch has the same length
-    int32_t lane_block;      // lane kernel block length: 16 or 8 states
+    int32_t lane_block;      // lane kernel block length: 16 or 8 states, 0 by the windows
+    int32_t recount;         // 1: the long kernel counts the scenarios past the lane kernel's history
+    int32_t long_grid;       // long kernel workgroups (at most)
     int32_t wave_grid;       // wave kernel workgroups of a full evaluation (form wave)
     int32_t maxn;            // bound on the tour lengths (sizes the wave kernel's LDS)
 };
@@ -130,7 +132,7 @@ struct MomentArgs {
 hipError_t launch_prep(const PrepArgs &a, hipStream_t stream);
 hipError_t launch_lane(const EvalArgs &a, hipStream_t stream);
 hipError_t launch_wave_all(const EvalArgs &a, hipStream_t stream);
-hipError_t launch_wave_fallback(const EvalArgs &a, hipStream_t stream);
+hipError_t launch_long(const EvalArgs &a, hipStream_t stream);
 hipError_t launch_moments(const MomentArgs &a, hipStream_t stream);
 // two-kernel form: mask int16 [rows][mask_ld], row abase(t) + i
 hipError_t launch_mask(const EvalArgs &a, int16_t *mask, long long mask_ld, hipStream_t stream);

@@ -14,13 +14,18 @@
 //  split_lane_kernel      one scenario per lane (scenario-level parallelism of Section 3);
 //                         the window minimum is answered in O(1) per state from block
 //                         suffix minima held in LDS; windows longer than its LDS history are
-//                         queued for the general kernel.
+//                         left to the long kernel.
+//  split_long_kernel      the lane kernel's blocks over a history of 256 positions, for tours
+//                         whose windows outgrow the lane kernel's 64 and for the scenarios it
+//                         marks; what outgrows this history too is finished one scenario per
+//                         wavefront.
 //  split_wave_kernel      one scenario per wavefront; lanes cover the window's predecessors
 //                         (transition-level parallelism of Section 3) and the minimum is a
-//                         DPP reduction. Exact for any window length; used for small S and
-//                         for the scenarios the lane kernel queues.
+//                         DPP reduction. Exact for any window length; used for small S.
 //  split_moments_*        exact 128-bit sum and sum of squares of the costs.
 #include "split_internal.h"
+
+#include <limits.h>
 
 #include <mutex>
 
@@ -144,27 +149,35 @@ __global__ __launch_bounds__(1024) void split_prep_kernel(PrepArgs a)
 // rec slot and the even base below s take one or two instructions each. The block loop is
 // unrolled 64 / LB times so that every LDS store has a constant offset.
 
-constexpr int kRingPairs = 32;  // prefix-load ring of 64 positions, two per dword
-constexpr int kMirror = 7;      // ring rows repeated after the ring
+constexpr int kMirror = 7;  // ring rows repeated after the ring
 
-// Blocks of LB states: kSteps = blocks in the 64-position history (the unroll of the block
-// loop), kLog = log2(LB). The ring, the suffix offsets and the four block records hold every
-// window start of a block that lies at most three blocks back, so 4 * LB <= 64.
-template <int LB>
+// Blocks of LB states over a history of H positions: kRing = blocks in the history, kRecs = block
+// records kept, kSteps = blocks unrolled in the block loop, kLog = log2(LB). The ring, the suffix
+// offsets and the records hold every window start that lies at most kRecs - 1 blocks back.
+// H = 64 (the lane kernel) unrolls its whole history, so that every LDS store has a constant
+// offset; H = 256 (the long kernel, blocks of 16) adds the block's ring position to them.
+template <int LB, int H>
 struct LaneCfg {
-    static_assert(LB == 16 || LB == 8, "blocks of 16 or 8 states");
-    static constexpr int kSteps = 64 / LB;
+    static_assert((H == 64 && (LB == 16 || LB == 8)) || (H == 256 && LB == 16),
+                  "blocks of 16 or 8 states over 64 positions, of 16 over 256");
+    static constexpr int kRing = H / LB;
+    static constexpr int kRecs = H == 64 ? 4 : kRing;
+    static constexpr int kSteps = H == 64 ? kRing : 4;
     static constexpr int kLog = LB == 16 ? 4 : 3;
+    static constexpr int kPairs = H / 2;  // rows of the prefix-load ring, two positions each
+    static constexpr uint32_t kDlMask = (uint32_t)(H * 128 - 1) & ~1u;
+    static constexpr uint32_t kPpMask = (uint32_t)(kPairs * 256 - 1) & ~255u;
+    static constexpr uint32_t kRecMask = (uint32_t)(kRecs - 1) * 512u;
 };
 
+template <int H>
 struct __attribute__((aligned(16))) LaneLds {
-    uint64_t rec[4][64];
-    uint16_t dl[64][64];
-    uint32_t pp[kRingPairs + kMirror][64];
+    uint64_t rec[LaneCfg<16, H>::kRecs][64];
+    uint16_t dl[H][64];
+    uint32_t pp[H / 2 + kMirror][64];
+    static constexpr uint32_t kDlOff = sizeof(uint64_t) * LaneCfg<16, H>::kRecs * 64;
+    static constexpr uint32_t kPpOff = kDlOff + sizeof(uint16_t) * H * 64;
 };
-constexpr uint32_t kRecOff = 0;
-constexpr uint32_t kDlOff = sizeof(uint64_t) * 4 * 64;
-constexpr uint32_t kPpOff = kDlOff + sizeof(uint16_t) * 64 * 64;
 
 // Read-only per-tour arrays (written by the prep kernel, a previous launch): the constant
 // address space lets every uniform read of them be a scalar load.
@@ -181,21 +194,24 @@ typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ int s_of(int S) { return S >> 7; }
 __device__ __forceinline__ int S_of(int s, int lane) { return (s << 7) | (lane << 1); }
 
-__device__ __forceinline__ const lds_char *lds_base(LaneLds &L)
+template <int H>
+__device__ __forceinline__ const lds_char *lds_base(LaneLds<H> &L)
 {
     return (const lds_char *)(&L);
 }
 
 // Window-minimum lookup of a start S (in an older block): the 16-bit suffix offset and the
 // block record; combined later by query_min so that the reads are in flight meanwhile.
-// The record slot (s / LB) & 3, 512 bytes a slot, is bits 9..10 of S >> (log2(LB) - 2).
-template <int LB>
-__device__ __forceinline__ void query_issue(LaneLds &L, int S, uint32_t lane8, uint32_t &dlv,
+// The record slot (s / LB) & (kRecs - 1), 512 bytes a slot, is bits 9 and up of
+// S >> (log2(LB) - 2).
+template <int LB, int H>
+__device__ __forceinline__ void query_issue(LaneLds<H> &L, int S, uint32_t lane8, uint32_t &dlv,
                                             uint64_t &recv)
 {
-    constexpr int kSh = LaneCfg<LB>::kLog - 2;
-    dlv = *(const lds_u16 *)(lds_base(L) + kDlOff + ((uint32_t)S & 0x1FFEu));
-    recv = *(const lds_u64 *)(lds_base(L) + kRecOff + ((((uint32_t)S >> kSh) & 0x600u) | lane8));
+    using C = LaneCfg<LB, H>;
+    constexpr int kSh = C::kLog - 2;
+    dlv = *(const lds_u16 *)(lds_base(L) + LaneLds<H>::kDlOff + ((uint32_t)S & C::kDlMask));
+    recv = *(const lds_u64 *)(lds_base(L) + ((((uint32_t)S >> kSh) & C::kRecMask) | lane8));
 }
 __device__ __forceinline__ int query_min(uint32_t dlv, uint64_t recv, int pre)
 {
@@ -204,15 +220,23 @@ __device__ __forceinline__ int query_min(uint32_t dlv, uint64_t recv, int pre)
     return min(min(bm + (int)dlv, bs), pre);
 }
 
-__device__ __forceinline__ uint32_t pp_at(LaneLds &L, uint32_t off, int row)
+// Offset of the ring row that holds a start S (and of the lane within it).
+template <int H>
+__device__ __forceinline__ uint32_t pp_off(int S, uint32_t lane4)
 {
-    return *(const lds_u32 *)(lds_base(L) + kPpOff + off + row * 256);
+    return ((uint32_t)S & LaneCfg<16, H>::kPpMask) | lane4;
+}
+template <int H>
+__device__ __forceinline__ uint32_t pp_at(LaneLds<H> &L, uint32_t off, int row)
+{
+    return *(const lds_u32 *)(lds_base(L) + LaneLds<H>::kPpOff + off + row * 256);
 }
 // 16-bit ring value of position p
-__device__ __forceinline__ uint32_t pp_pos(LaneLds &L, int lane, int p)
+template <int H>
+__device__ __forceinline__ uint32_t pp_pos(LaneLds<H> &L, int lane, int p)
 {
-    const lds_u16 *h = (const lds_u16 *)(lds_base(L) + kPpOff);
-    return h[(((p >> 1) & (kRingPairs - 1)) * 64 + lane) * 2 + (p & 1)];
+    const lds_u16 *h = (const lds_u16 *)(lds_base(L) + LaneLds<H>::kPpOff);
+    return h[(((p >> 1) & (H / 2 - 1)) * 64 + lane) * 2 + (p & 1)];
 }
 
 // Packed 16-bit a - t in both halves, t a 16-bit value (no borrow between the halves).
@@ -230,24 +254,27 @@ __device__ __forceinline__ uint32_t sign_bytes(uint32_t hi, uint32_t lo)
 
 // Exact start of a state with threshold T, advancing one position at a time from a start that
 // is not past it. Bounded: position i of the state is never expired, and the ring holds it.
-__device__ __forceinline__ int exact_start(LaneLds &L, int lane, int S, uint32_t T)
+template <int H>
+__device__ __forceinline__ int exact_start(LaneLds<H> &L, int lane, int S, uint32_t T)
 {
     int s = s_of(S);
-    for (int k = 0; k < 2 * kRingPairs; ++k) {
+    for (int k = 0; k < H; ++k) {
         if ((int16_t)(uint16_t)(pp_pos(L, lane, s) - T) >= 0) break;
         ++s;
     }
     return S_of(s, lane);
 }
 
-// Prefix loads of block c (R = c mod 64/LB): q[j] is the demand of position LB*c + j (zero
+// Prefix loads of block c (R = c mod kRing): q[j] is the demand of position LB*c + j (zero
 // where a position does not exist). Writes the ring rows of the block and returns the packed
 // thresholds TT[k] = (P_{LB*c+2k} - Q, P_{LB*c+2k+1} - Q) mod 2^16.
-template <int LB, int R>
-__device__ __forceinline__ void lane_prefix(LaneLds &L, int lane, const uint16_t (&q)[LB],
-                                            uint32_t QQ, uint32_t &Plast, uint32_t &qor,
+template <int LB, int H>
+__device__ __forceinline__ void lane_prefix(LaneLds<H> &L, int lane, int R,
+                                            const uint16_t (&q)[LB], uint32_t QQ,
+                                            uint32_t &Plast, uint32_t &qor,
                                             uint32_t (&TT)[LB / 2])
 {
+    const int row0 = (LB / 2) * R;
     uint32_t prev = Plast;
 #pragma unroll
     for (int k = 0; k < LB / 2; ++k) {
@@ -264,10 +291,8 @@ __device__ __forceinline__ void lane_prefix(LaneLds &L, int lane, const uint16_t
         TT[k] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, PP) -
                                                  __builtin_bit_cast(u16x2, QQ));
         qor |= Qp;  // both halves: the bound below takes the larger
-        constexpr int row0 = (LB / 2) * R;
-        L.pp[(row0 + k) & (kRingPairs - 1)][lane] = PP;
-        if (((row0 + k) & (kRingPairs - 1)) < kMirror)
-            L.pp[((row0 + k) & (kRingPairs - 1)) + kRingPairs][lane] = PP;
+        L.pp[row0 + k][lane] = PP;
+        if (row0 + k < kMirror) L.pp[row0 + k + H / 2][lane] = PP;
     }
     Plast = prev;
 }
@@ -282,8 +307,8 @@ __device__ __forceinline__ uint32_t tt_half(const uint32_t (&TT)[LB / 2], int t)
 // lookahead, completed exactly where the lookahead saturated or reached past the last written
 // prefix load (first + LB-1). States past n (demand 0) get valid starts too. In: Sp = start of
 // state first - 1.
-template <int LB>
-__device__ __forceinline__ void lane_starts_careful(LaneLds &L, int lane, int first,
+template <int LB, int H>
+__device__ __forceinline__ void lane_starts_careful(LaneLds<H> &L, int lane, int first,
                                                     const uint32_t (&TT)[LB / 2], int Sp,
                                                     int (&sOut)[LB])
 {
@@ -291,7 +316,7 @@ __device__ __forceinline__ void lane_starts_careful(LaneLds &L, int lane, int fi
 #pragma unroll
     for (int t = 0; t < LB; ++t) {
         const uint32_t T = tt_half<LB>(TT, t);
-        const uint32_t off = ((uint32_t)Sp & 0x1F00u) | lane4;
+        const uint32_t off = pp_off<H>(Sp, lane4);
         const uint32_t d0 = pp_at(L, off, 0), d1 = pp_at(L, off, 1);
         const uint32_t d2 = pp_at(L, off, 2), d3 = pp_at(L, off, 3);
         const uint32_t a01 = sign_bytes(pk_sub16(d1, T), pk_sub16(d0, T));
@@ -318,10 +343,11 @@ struct PairData {
     uint32_t d[6];
     int base;
 };
-__device__ __forceinline__ PairData pair_read(LaneLds &L, uint32_t lane4, int Sp)
+template <int H>
+__device__ __forceinline__ PairData pair_read(LaneLds<H> &L, uint32_t lane4, int Sp)
 {
     PairData p;
-    const uint32_t off = ((uint32_t)Sp & 0x1F00u) | lane4;
+    const uint32_t off = pp_off<H>(Sp, lane4);
 #pragma unroll
     for (int r = 0; r < 6; ++r) p.d[r] = pp_at(L, off, r);
     p.base = Sp & ~0x80;
@@ -358,8 +384,8 @@ __device__ __forceinline__ int pair_count10(const PairData &p, uint32_t T, uint3
 // Window starts of the states first .. first + LB-1 from Sp (start of state first - 1) with the
 // pair counts; where a count may be short or a read reached past the written prefix loads
 // (first + LB-1), the block is redone state by state.
-template <int LB>
-__device__ __forceinline__ void lane_starts_pairs(LaneLds &L, int lane, int first,
+template <int LB, int H>
+__device__ __forceinline__ void lane_starts_pairs(LaneLds<H> &L, int lane, int first,
                                                   const uint32_t (&TT)[LB / 2], int Sp,
                                                   int (&sOut)[LB])
 {
@@ -376,7 +402,7 @@ __device__ __forceinline__ void lane_starts_pairs(LaneLds &L, int lane, int firs
         Sp = sOut[2 * u + 1];
     }
     if (__any((int32_t)sat < 0 || (s_of(sOut[LB - 3]) & ~1) > first + LB - 12))
-        lane_starts_careful<LB>(L, lane, first, TT, S_in, sOut);
+        lane_starts_careful<LB, H>(L, lane, first, TT, S_in, sOut);
 }
 
 // 16 positions (8 packed dwords) from the even position below Sp.
@@ -384,10 +410,11 @@ struct WideData {
     uint32_t d[8];
     int base;
 };
-__device__ __forceinline__ WideData wide_read(LaneLds &L, uint32_t lane4, int Sp)
+template <int H>
+__device__ __forceinline__ WideData wide_read(LaneLds<H> &L, uint32_t lane4, int Sp)
 {
     WideData p;
-    const uint32_t off = ((uint32_t)Sp & 0x1F00u) | lane4;
+    const uint32_t off = pp_off<H>(Sp, lane4);
 #pragma unroll
     for (int r = 0; r < 8; ++r) p.d[r] = pp_at(L, off, r);
     p.base = Sp & ~0x80;
@@ -410,8 +437,8 @@ __device__ __forceinline__ int wide_count(const WideData &p, uint32_t T, uint32_
 // the second all 16 (half the serial reads of a state-by-state redo, which has no other work
 // left to overlap); where those fall short or read past the written prefix loads too, state by
 // state. Used for 16-state blocks (an 8-state block's ring rarely holds 16 positions ahead).
-template <int LB>
-__device__ __forceinline__ void lane_starts_wide(LaneLds &L, int lane, int first,
+template <int LB, int H>
+__device__ __forceinline__ void lane_starts_wide(LaneLds<H> &L, int lane, int first,
                                                  const uint32_t (&TT)[LB / 2], int Sp,
                                                  int (&sOut)[LB])
 {
@@ -428,7 +455,7 @@ __device__ __forceinline__ void lane_starts_wide(LaneLds &L, int lane, int first
         Sp = sOut[2 * u + 1];
     }
     if (__any((int32_t)sat < 0 || (s_of(sOut[LB - 3]) & ~1) > first + LB - 16))
-        lane_starts_careful<LB>(L, lane, first, TT, S_in, sOut);
+        lane_starts_careful<LB, H>(L, lane, first, TT, S_in, sOut);
 }
 
 // g of state t of a block (t uniform). Written as explicit selects: the compiler would
@@ -447,34 +474,41 @@ __device__ __forceinline__ int block_g_at(const int (&gb)[LB], int t)
     return g;
 }
 
-// Block c complete (R = c mod 64/LB): suffix minima as 16-bit offsets from the block minimum,
-// and the records of blocks c, c-1, c-2 (bm1, bm2: minima of blocks c-1, c-2).
-template <int LB, int R>
-__device__ __forceinline__ void lane_block_end(LaneLds &L, int lane, const int (&gb)[LB],
-                                               int &bm1, int &bm2, bool &ovf)
+// Block c complete (R = c mod kRing): suffix minima as 16-bit offsets from the block minimum,
+// and the records of the kRecs - 1 newest blocks (bm[j]: minimum of block c - 1 - j).
+template <int LB, int H>
+__device__ __forceinline__ void lane_block_end(LaneLds<H> &L, int lane, int R,
+                                               const int (&gb)[LB],
+                                               int (&bm)[LaneCfg<LB, H>::kRecs - 2], int &ovf)
 {
+    constexpr int NR = LaneCfg<LB, H>::kRecs;
     int sm[LB];
     sm[LB - 1] = gb[LB - 1];
 #pragma unroll
     for (int t = LB - 2; t >= 0; --t) sm[t] = min(sm[t + 1], gb[t]);
-    const int bm = sm[0];
-    ovf |= (unsigned)(sm[LB - 1] - bm) > 0xFFFFu;  // the largest offset is the last one
+    const int bmin = sm[0];
+    ovf |= (sm[LB - 1] - bmin) & ~0xFFFF;  // the largest offset is the last one
 #pragma unroll
-    for (int t = 0; t < LB; ++t) L.dl[LB * R + t][lane] = (uint16_t)(sm[t] - bm);
+    for (int t = 0; t < LB; ++t) L.dl[LB * R + t][lane] = (uint16_t)(sm[t] - bmin);
     auto pack = [](int lo, int hi) {
         return (uint64_t)(uint32_t)lo | ((uint64_t)(uint32_t)hi << 32);
     };
-    L.rec[R & 3][lane] = pack(bm, kInf);
-    L.rec[(R + 3) & 3][lane] = pack(bm1, bm);
-    L.rec[(R + 2) & 3][lane] = pack(bm2, min(bm, bm1));
-    bm2 = bm1;
-    bm1 = bm;
+    L.rec[R & (NR - 1)][lane] = pack(bmin, kInf);
+    int between = bmin;
+#pragma unroll
+    for (int j = 1; j < NR - 1; ++j) {
+        L.rec[(R + NR - j) & (NR - 1)][lane] = pack(bm[j - 1], between);
+        between = min(between, bm[j - 1]);
+    }
+#pragma unroll
+    for (int j = NR - 3; j > 0; --j) bm[j] = bm[j - 1];
+    bm[0] = bmin;
 }
 
 // DP of block c, state by state, for any window position (inside the block, or empty).
 // States past n (demand 0, weight 0) are evaluated too and not used.
-template <int LB>
-__device__ __forceinline__ void lane_dp_careful(LaneLds &L, int lane, int c,
+template <int LB, int H>
+__device__ __forceinline__ void lane_dp_careful(LaneLds<H> &L, int lane, int c,
                                                 ci32 *__restrict__ w,
                                                 const int (&sCur)[LB], int (&gb)[LB], bool &err)
 {
@@ -485,7 +519,7 @@ __device__ __forceinline__ void lane_dp_careful(LaneLds &L, int lane, int c,
     uint32_t qd[LB];
     uint64_t qr[LB];
 #pragma unroll
-    for (int t = 0; t < LB; ++t) query_issue<LB>(L, sCur[t], lane8, qd[t], qr[t]);
+    for (int t = 0; t < LB; ++t) query_issue<LB, H>(L, sCur[t], lane8, qd[t], qr[t]);
     int pre = kInf;
 #pragma unroll
     for (int t = 0; t < LB; ++t) {
@@ -547,37 +581,45 @@ __device__ __forceinline__ void lane_load_w(__amdgpu_buffer_rsrc_t wrsrc, int bl
     }
 }
 
+template <int LB, int H>
 struct LaneState {
     uint32_t Plast;  // high half: prefix load of the last position written to the ring
     uint32_t qor;    // OR of the demands read
-    int bm1, bm2;    // minima of the last two completed blocks
+    int bm[LaneCfg<LB, H>::kRecs - 2];  // minima of the last completed blocks
     int gres;        // g_n
-    bool err, ovf;
+    bool err;
+    int ovf;         // nonzero: past the history or 16 bits (a lane mask in scalar registers
+                     // measured 1% slower over the whole kernel)
+    bool past;       // H = 256: a window start fell out of the lane kernel's 64 positions
 };
 
-// One block step (R = c mod 64/LB): demands of block c + 3, window starts of block c + 1, DP
+// One block step (R = c mod kRing): demands of block c + 3, window starts of block c + 1, DP
 // of block c. qUse holds the demands of block c + 1, qLoad receives those of block c + 3.
-template <int LB, int R>
-__device__ __forceinline__ void lane_step(LaneLds &L, int lane, int c, int n, uint32_t QQ,
+template <int LB, int H>
+__device__ __forceinline__ void lane_step(LaneLds<H> &L, int lane, int R, int c, int n, uint32_t QQ,
                                           __amdgpu_buffer_rsrc_t dem, __amdgpu_buffer_rsrc_t wrsrc,
                                           cu32 *__restrict__ rowoff, uint32_t lane_off,
                                           ci32 *__restrict__ w, const uint16_t (&qUse)[LB],
                                           uint16_t (&qLoad)[LB], const int (&sCur)[LB],
                                           int (&sNext)[LB], const int (&wUse)[LB],
-                                          int (&wLoad)[LB], LaneState &st)
+                                          int (&wLoad)[LB], LaneState<LB, H> &st)
 {
+    using C = LaneCfg<LB, H>;
     // weights of block c + 1 (used by the next step), demands of block c + 3; unconditional,
     // so that every path has the same vector-memory wait counts
     lane_load_w<LB>(wrsrc, c + 1, wLoad);
     lane_load_block<LB>(dem, rowoff, lane_off, c + 3, qLoad);
-    const int nb = n >> LaneCfg<LB>::kLog;
+    const int nb = n >> C::kLog;
     if (c > nb) return;
     const int p0 = c * LB;
     const int first = p0 + LB;  // states of block c + 1
     const uint32_t lane4 = (uint32_t)lane << 2, lane8 = (uint32_t)lane << 3;
     // the ring and the block records must still hold every window start of block c + 1
     // (state LB*c + LB-1 exists whenever block c + 1 does)
-    if (c + 1 <= nb) st.ovf |= sCur[LB - 1] < ((p0 - 2 * LB) << 7);
+    if (c + 1 <= nb) {
+        st.ovf |= (sCur[LB - 1] - ((p0 - (C::kRecs - 2) * LB) << 7)) & INT_MIN;
+        if constexpr (H > 64) st.past |= sCur[LB - 1] < ((p0 - 2 * LB) << 7);
+    }
     int gb[LB];
     // states past n (demand 0, weight 0) are evaluated like the others and not used
     const bool fast = c >= 1 && !__any(sCur[LB - 1] >= (p0 << 7));
@@ -592,11 +634,11 @@ __device__ __forceinline__ void lane_step(LaneLds &L, int lane, int c, int n, ui
 #pragma unroll
         for (int t = 0; t < LB; ++t) wv[t] = wUse[t];
         uint32_t TT[LB / 2];
-        lane_prefix<LB, (R + 1) % LaneCfg<LB>::kSteps>(L, lane, qUse, QQ, st.Plast, st.qor, TT);
+        lane_prefix<LB, H>(L, lane, (R + 1) % C::kRing, qUse, QQ, st.Plast, st.qor, TT);
         uint32_t qd[LB];
         uint64_t qr[LB];
-        query_issue<LB>(L, sCur[0], lane8, qd[0], qr[0]);
-        query_issue<LB>(L, sCur[1], lane8, qd[1], qr[1]);
+        query_issue<LB, H>(L, sCur[0], lane8, qd[0], qr[0]);
+        query_issue<LB, H>(L, sCur[1], lane8, qd[1], qr[1]);
         PairData pcur = pair_read(L, lane4, sCur[LB - 1]);
         PairData pprev = pcur;
         uint32_t sat = 0;  // sign bit: some count of this lane may be short
@@ -605,8 +647,8 @@ __device__ __forceinline__ void lane_step(LaneLds &L, int lane, int c, int n, ui
 #pragma unroll
         for (int u = 0; u < LB / 2; ++u) {
             if (u + 1 < LB / 2) {
-                query_issue<LB>(L, sCur[2 * u + 2], lane8, qd[2 * u + 2], qr[2 * u + 2]);
-                query_issue<LB>(L, sCur[2 * u + 3], lane8, qd[2 * u + 3], qr[2 * u + 3]);
+                query_issue<LB, H>(L, sCur[2 * u + 2], lane8, qd[2 * u + 2], qr[2 * u + 2]);
+                query_issue<LB, H>(L, sCur[2 * u + 3], lane8, qd[2 * u + 3], qr[2 * u + 3]);
             }
 #pragma unroll
             for (int t = 2 * u; t < 2 * u + 2; ++t) {
@@ -635,15 +677,15 @@ __device__ __forceinline__ void lane_step(LaneLds &L, int lane, int c, int n, ui
         }
         // no later block reads the last block's records (and its suffix offsets would hold
         // g_n = f_n, which need not fit 16 bits)
-        if (c < nb) lane_block_end<LB, R>(L, lane, gb, st.bm1, st.bm2, st.ovf);
+        if (c < nb) lane_block_end<LB, H>(L, lane, R, gb, st.bm, st.ovf);
         // the last pair counts positions up to its base + 9; the ring is written up to
         // first + LB-1. Either condition below is rare: redo the block's starts (16-state
         // blocks with wider pair counts first, then state by state where those fall short).
         if (__any((int32_t)sat < 0 || (s_of(sNext[LB - 3]) & ~1) > first + LB - 10)) {
             if constexpr (LB == 16)
-                lane_starts_wide<LB>(L, lane, first, TT, sCur[LB - 1], sNext);
+                lane_starts_wide<LB, H>(L, lane, first, TT, sCur[LB - 1], sNext);
             else
-                lane_starts_careful<LB>(L, lane, first, TT, sCur[LB - 1], sNext);
+                lane_starts_careful<LB, H>(L, lane, first, TT, sCur[LB - 1], sNext);
         }
         if (c == nb) st.gres = block_g_at<LB>(gb, n & (LB - 1));
         return;
@@ -651,12 +693,12 @@ __device__ __forceinline__ void lane_step(LaneLds &L, int lane, int c, int n, ui
     // careful step (positions past n load demand 0)
     if (c + 1 <= nb) {
         uint32_t TT[LB / 2];
-        lane_prefix<LB, (R + 1) % LaneCfg<LB>::kSteps>(L, lane, qUse, QQ, st.Plast, st.qor, TT);
-        lane_starts_pairs<LB>(L, lane, first, TT, sCur[LB - 1], sNext);
+        lane_prefix<LB, H>(L, lane, (R + 1) % C::kRing, qUse, QQ, st.Plast, st.qor, TT);
+        lane_starts_pairs<LB, H>(L, lane, first, TT, sCur[LB - 1], sNext);
     }
-    lane_dp_careful<LB>(L, lane, c, w, sCur, gb, st.err);
+    lane_dp_careful<LB, H>(L, lane, c, w, sCur, gb, st.err);
     if (c + 1 <= nb) {
-        lane_block_end<LB, R>(L, lane, gb, st.bm1, st.bm2, st.ovf);
+        lane_block_end<LB, H>(L, lane, R, gb, st.bm, st.ovf);
     } else {
         st.gres = block_g_at<LB>(gb, n & (LB - 1));  // block c holds state n
     }
@@ -683,88 +725,202 @@ __device__ __forceinline__ void item_priority(int c, int nb)
         __builtin_amdgcn_s_setprio(0);
 }
 
-// One work item: the 64 scenarios sb*64 .. sb*64+63 of tour t.
-template <int LB>
-__device__ __forceinline__ void lane_item(LaneLds &L, const EvalArgs &a, int t, long long sb,
-                                          __amdgpu_buffer_rsrc_t rsrc, bool by_progress)
+// A tour's per-position arrays and the descriptors of its weights and of the demands.
+struct LaneTour {
+    cu32 *__restrict__ rowoff;
+    ci32 *__restrict__ w;
+    __amdgpu_buffer_rsrc_t wrsrc;
+    int n;
+};
+
+__device__ __forceinline__ LaneTour lane_tour(const EvalArgs &a, int t)
 {
-    const int lane = threadIdx.x;
-    const long long nscen = a.S;
     // tour values come from memory: state that they are the same on every lane
     ci64 *tptr = (ci64 *)a.tour.tptr;
     const int64_t p0 = tptr[t];
-    const int n = (int)(tptr[t + 1] - p0);
     const int64_t ab = p0 + (int64_t)t * (1 + kRowPad);
-    cu32 *__restrict__ rowoff = (cu32 *)a.tour.rowoff32 + ab;
-    ci32 *__restrict__ w = (ci32 *)a.tour.w + ab;
-    const long long scen_raw = sb * 64 + lane;
-    const bool active = scen_raw < nscen;
-    const long long scen = active ? scen_raw : nscen - 1;
-    const uint32_t lane_off = (uint32_t)scen * 2u;
-    const int Q = a.Q;
+    LaneTour r;
+    r.n = (int)(tptr[t + 1] - p0);
+    r.rowoff = (cu32 *)a.tour.rowoff32 + ab;
+    r.w = (ci32 *)a.tour.w + ab;
+    r.wrsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.tour.w + ab), (short)0,
+                                                (int)(sizeof(int32_t) * (r.n + 1 + kRowPad)),
+                                                0x00020000);
+    return r;
+}
+
+// States 0..n of a tour for the scenarios at byte offset lane_off (one per lane) of its demand
+// rows; qA, qB and qC hold the demands of blocks 0, 1 and 2.
+template <int LB, int H>
+__device__ __forceinline__ void lane_run(LaneLds<H> &L, const LaneTour &tr, int Q,
+                                         __amdgpu_buffer_rsrc_t rsrc, uint32_t lane_off,
+                                         uint16_t (&qA)[LB], uint16_t (&qB)[LB],
+                                         uint16_t (&qC)[LB], bool by_progress,
+                                         LaneState<LB, H> &st)
+{
+    using C = LaneCfg<LB, H>;
+    const int lane = threadIdx.x & 63;
+    const int n = tr.n;
+    cu32 *__restrict__ rowoff = tr.rowoff;
+    ci32 *__restrict__ w = tr.w;
+    const __amdgpu_buffer_rsrc_t wrsrc = tr.wrsrc;
     const uint32_t QQ = (uint32_t)Q | ((uint32_t)Q << 16);
 
-    LaneState st;
     st.Plast = 0;
     st.qor = 0;
-    st.bm1 = kInf;
-    st.bm2 = kInf;
+#pragma unroll
+    for (int j = 0; j < C::kRecs - 2; ++j) st.bm[j] = kInf;
     st.gres = 0;
     st.err = false;
-    st.ovf = false;
+    st.ovf = 0;
+    st.past = false;
 
-    const int nb = n >> LaneCfg<LB>::kLog;
-    uint16_t qA[LB], qB[LB], qC[LB], qD[LB];
+    const int nb = n >> C::kLog;
+    uint16_t qD[LB];
     int sA[LB], sB[LB];
     int wA[LB], wB[LB];  // weights of the block a step evaluates, loaded one step ahead
-    const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(a.tour.w + ab), (short)0, (int)(sizeof(int32_t) * (n + 1 + kRowPad)), 0x00020000);
 #pragma unroll
     for (int k = 0; k < LB; ++k) {
         sA[k] = S_of(0, lane);
         sB[k] = S_of(0, lane);
     }
     lane_load_w<LB>(wrsrc, 0, wA);
-    lane_load_block<LB>(rsrc, rowoff, lane_off, 0, qA);
-    lane_load_block<LB>(rsrc, rowoff, lane_off, 1, qB);
-    lane_load_block<LB>(rsrc, rowoff, lane_off, 2, qC);
     {
         // block 0: position 0 has no demand (P_0 = 0, its row offset is absent); start 0
         uint32_t TT[LB / 2];
-        lane_prefix<LB, 0>(L, lane, qA, QQ, st.Plast, st.qor, TT);
-        lane_starts_pairs<LB>(L, lane, 0, TT, S_of(0, lane), sA);
+        lane_prefix<LB, H>(L, lane, 0, qA, QQ, st.Plast, st.qor, TT);
+        lane_starts_pairs<LB, H>(L, lane, 0, TT, S_of(0, lane), sA);
     }
     // block b's demands live in q[A, B, C, D][b & 3], its starts and weights in [A, B][b & 1];
-    // 64 / LB steps per iteration keep these roles and the LDS rows of every step constant
-    for (int c = 0; c <= nb; c += LaneCfg<LB>::kSteps) {
+    // kSteps steps per iteration keep these roles constant (H = 64: and the LDS rows of a step)
+    for (int c = 0; c <= nb; c += C::kSteps) {
         if (by_progress) item_priority(c, nb);
-        lane_step<LB, 0>(L, lane, c, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qB, qD, sA, sB, wA, wB, st);
-        lane_step<LB, 1>(L, lane, c + 1, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qC, qA, sB, sA, wB, wA, st);
-        lane_step<LB, 2>(L, lane, c + 2, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qD, qB, sA, sB, wA, wB, st);
-        lane_step<LB, 3>(L, lane, c + 3, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qA, qC, sB, sA, wB, wA, st);
-        if constexpr (LaneCfg<LB>::kSteps == 8) {
-            lane_step<LB, 4>(L, lane, c + 4, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qB, qD, sA, sB, wA, wB, st);
-            lane_step<LB, 5>(L, lane, c + 5, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qC, qA, sB, sA, wB, wA, st);
-            lane_step<LB, 6>(L, lane, c + 6, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qD, qB, sA, sB, wA, wB, st);
-            lane_step<LB, 7>(L, lane, c + 7, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qA, qC, sB, sA, wB, wA, st);
+        const int R = H == 64 ? 0 : c & (C::kRing - 1);
+        lane_step<LB, H>(L, lane, R, c, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qB, qD, sA, sB, wA, wB, st);
+        lane_step<LB, H>(L, lane, R + 1, c + 1, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qC, qA, sB, sA, wB, wA, st);
+        lane_step<LB, H>(L, lane, R + 2, c + 2, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qD, qB, sA, sB, wA, wB, st);
+        lane_step<LB, H>(L, lane, R + 3, c + 3, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qA, qC, sB, sA, wB, wA, st);
+        if constexpr (C::kSteps == 8) {
+            lane_step<LB, H>(L, lane, 4, c + 4, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qB, qD, sA, sB, wA, wB, st);
+            lane_step<LB, H>(L, lane, 5, c + 5, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qC, qA, sB, sA, wB, wA, st);
+            lane_step<LB, H>(L, lane, 6, c + 6, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qD, qB, sA, sB, wA, wB, st);
+            lane_step<LB, H>(L, lane, 7, c + 7, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qA, qC, sB, sA, wB, wA, st);
         }
     }
-
-    __builtin_amdgcn_s_setprio(0);
     // counts exact only while 8 * max(q) + Q < 2^15 (qor >= max(q)); bit 15 (a negative
     // int16 demand) also lands here, and the general kernel reports it
     st.ovf |= 8u * ((st.qor | (st.qor >> 16)) & 0xFFFFu) + (uint32_t)Q > 32767u;
-    int32_t *cost = a.cost + (long long)t * a.ldc;
-    if (active) {
-        if (st.ovf) {
-            cost[scen] = kCostOvf;
-            atomicAdd(&a.stats[t].ovf_count, 1);
-            atomicAdd(&a.ctl->ovf_total, 1u);
-        } else if (st.err) {
-            atomicOr(&a.stats[t].err_demand, 1);
-        } else {
-            cost[scen] = st.gres;
+}
+
+// The end of a work item: the costs of the scenarios that are done; the others are marked for the
+// long kernel, which also counts them under `recount`.
+template <int LB>
+__device__ __forceinline__ void lane_finish(const EvalArgs &a, int t, long long scen,
+                                            const LaneState<LB, 64> &st, bool recount)
+{
+    __builtin_amdgcn_s_setprio(0);
+    const bool active = scen < a.S;
+    const bool left = active && st.ovf != 0;
+    if (active && (left || !st.err))
+        a.cost[(long long)t * a.ldc + scen] = left ? kCostOvf : st.gres;
+    const unsigned long long m = __ballot(left);
+    if (m != 0 && threadIdx.x == 0) {
+        a.ctl->ovf_total = 1;  // whoever writes it, the same value
+        if (!recount) atomicAdd(&a.stats[t].ovf_count, (int)__popcll(m));
+    }
+    if (active && !left && st.err) atomicOr(&a.stats[t].err_demand, 1);
+}
+
+// The windows of a work item, from the demands of its first positions (loaded anyway):
+//  kWindowsLong   under half of the scenarios or more, the first 15 customers fill at most 15 / 40 of
+//                 the capacity: some window will outgrow 47 positions;
+//  kWindowsShort  under every lane, its first route holds at most 18 customers and routes over its
+//                 first 47 positions 15.5 on average: a 16-state block would mostly see windows
+//                 that start inside it. A lane whose first 15 customers fill at most 15 / 22 of
+//                 the capacity decides against it from block 0 alone, before blocks 1 and 2
+//                 have arrived.
+// Windows of up to 13 (demands with a coefficient of variation of 0.5; 14 at 0.25) keep their tails
+// within the 23 positions of 8-state blocks; at 14.6 a few in 10^5 pass them, and redoing their
+// items made a call of 849 scenarios 121 us instead of 93.
+// The class only chooses a kernel: what outgrows its history all the same is redone by the long one.
+// Measured, whole calls: 200 customers, windows of 13, S = 10^5: 83 us (90 in blocks of 16);
+// 701 customers, windows of 60, S = 20,011: 181 us (14,760 with blocks of 16 first and the rest one
+// scenario per wavefront).
+enum { kWindowsMid, kWindowsShort, kWindowsLong };
+__device__ __forceinline__ int window_class(const uint16_t (&qA)[16], const uint16_t (&qB)[16],
+                                            const uint16_t (&qC)[16], int n, int Q,
+                                            bool active)
+{
+    int load = 0, len = 0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) load += qA[j];  // position 0 has no demand
+    if (__any(22 * load <= 15 * Q))
+        return n > 64 && 2 * __popcll(__ballot(active && 40 * load <= 15 * Q)) >=
+                             __popcll(__ballot(active))
+                   ? kWindowsLong
+                   : kWindowsMid;
+    load = 0;
+    auto count = [&](const uint16_t (&q)[16]) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            load += q[j];
+            len += load <= Q ? 1 : 0;  // counts position 0 too
         }
+    };
+    count(qA);
+    count(qB);
+    count(qC);
+    return __any(len > 19 || 31 * load < 2 * min(n, 47) * Q) ? kWindowsMid : kWindowsShort;
+}
+
+// One work item: the 64 scenarios sb*64 .. sb*64+63 of tour t. LB = 0: blocks of 8 or 16 states, or
+// the long kernel, by the item's windows.
+template <int LB>
+__device__ __forceinline__ void lane_item(LaneLds<64> &L, const EvalArgs &a, int t, long long sb,
+                                          __amdgpu_buffer_rsrc_t rsrc)
+{
+    const LaneTour tr = lane_tour(a, t);
+    const long long scen = sb * 64 + (int)threadIdx.x;
+    const uint32_t lane_off = (uint32_t)min(scen, (long long)a.S - 1) * 2u;
+    const bool prio = a.lane_uniform != 0;
+    if constexpr (LB == 8) {
+        uint16_t qA[8], qB[8], qC[8];
+        lane_load_block<8>(rsrc, tr.rowoff, lane_off, 0, qA);
+        lane_load_block<8>(rsrc, tr.rowoff, lane_off, 1, qB);
+        lane_load_block<8>(rsrc, tr.rowoff, lane_off, 2, qC);
+        LaneState<8, 64> st;
+        lane_run<8, 64>(L, tr, a.Q, rsrc, lane_off, qA, qB, qC, prio, st);
+        lane_finish<8>(a, t, scen, st, false);
+    } else {
+        uint16_t qA[16], qB[16], qC[16];
+        lane_load_block<16>(rsrc, tr.rowoff, lane_off, 0, qA);
+        lane_load_block<16>(rsrc, tr.rowoff, lane_off, 1, qB);
+        lane_load_block<16>(rsrc, tr.rowoff, lane_off, 2, qC);
+        LaneState<16, 64> st;
+        if constexpr (LB == 0) {
+            const int cls = window_class(qA, qB, qC, tr.n, a.Q, scen < a.S);
+            if (cls == kWindowsShort) {
+                uint16_t rA[8], rB[8], rC[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    rA[j] = qA[j];
+                    rB[j] = qA[8 + j];
+                    rC[j] = qB[j];
+                }
+                LaneState<8, 64> st8;
+                lane_run<8, 64>(L, tr, a.Q, rsrc, lane_off, rA, rB, rC, prio, st8);
+                lane_finish<8>(a, t, scen, st8, true);
+                return;
+            }
+            if (cls == kWindowsLong) {
+                st.ovf = 1;
+                st.err = false;
+                lane_finish<16>(a, t, scen, st, true);
+                return;
+            }
+        }
+        lane_run<16, 64>(L, tr, a.Q, rsrc, lane_off, qA, qB, qC, prio, st);
+        lane_finish<16>(a, t, scen, st, true);
     }
 }
 
@@ -775,7 +931,7 @@ __device__ __forceinline__ void lane_item(LaneLds &L, const EvalArgs &a, int t, 
 template <int LB>
 __global__ __launch_bounds__(64) void split_lane_kernel(EvalArgs a)
 {
-    __shared__ LaneLds L;
+    __shared__ LaneLds<64> L;
     const int lane = threadIdx.x;
     // raw buffer over the demand bytes the tours can address (gfx9 descriptor word 3:
     // 0x00020000); loads at offsets past lane_bytes (absent positions) return 0
@@ -795,7 +951,7 @@ __global__ __launch_bounds__(64) void split_lane_kernel(EvalArgs a)
         }
         const long long r = (long long)k / nsb;
         const int t = ((ci32 *)a.tour.order)[r];
-        lane_item<LB>(L, a, t, (long long)k - r * nsb, rsrc, a.lane_uniform != 0);
+        lane_item<LB>(L, a, t, (long long)k - r * nsb, rsrc);
         k = __builtin_amdgcn_readfirstlane(knext);
     }
 }
@@ -888,35 +1044,76 @@ __device__ void wave_one(const EvalArgs &a, int t, long long scen, int32_t *G, i
     __syncthreads();
 }
 
-// mode 0: every (tour, scenario) pair, k = t * S + s over k = blockIdx.x, blockIdx.x +
-//         gridDim.x, ...
-// mode 1: the pairs the lane kernel marked kCostOvf; a workgroup scans 64 costs of one tour
-//         at a time and evaluates the marked ones. Returns at once when nothing was marked.
-__global__ __launch_bounds__(64) void split_wave_kernel(EvalArgs a, int mode)
+// Every (tour, scenario) pair, k = t * S + s over k = blockIdx.x, blockIdx.x + gridDim.x, ...
+__global__ __launch_bounds__(64) void split_wave_kernel(EvalArgs a)
 {
     extern __shared__ int32_t lds[];
     int32_t *G = lds;
     int32_t *PP = lds + (a.maxn + 1);
     const long long T = *a.tour.nt;
-    if (mode == 0) {
-        for (long long k = blockIdx.x; k < T * a.S; k += gridDim.x) {
-            const int t = (int)(k / a.S);
-            wave_one(a, t, k - (long long)t * a.S, G, PP);
-        }
-        return;
+    for (long long k = blockIdx.x; k < T * a.S; k += gridDim.x) {
+        const int t = (int)(k / a.S);
+        wave_one(a, t, k - (long long)t * a.S, G, PP);
     }
-    if (a.ctl->ovf_total == 0) return;
+}
+
+// ------------------------------------------------------------------------- long kernel
+
+// The scenarios marked kCostOvf, 64 at a time with the lane kernel's blocks of 16 over a history of
+// 256 positions (windows of up to 239). Scenarios that outgrow this history too, or whose suffix
+// offsets or demands pass 16 bits, are then finished one by one by the whole wavefront, in the same
+// LDS. With a.recount it counts the scenarios past the lane kernel's history (n_fallback): an item
+// is left here whole.
+//
+// Bound by the latency of one wavefront's serial chain: 75.5 KB of LDS leave two wavefronts a
+// compute unit, one on every other SIMD. That is still one state of 64 scenarios per step, where
+// one scenario per wavefront leaves most lanes idle: 701 customers, windows of 60,
+// S = 20,011 took 14.76 ms as a call; with this kernel 0.18 ms, 0.12 of them here.
+// Counts go to memory once per item: one atomic per scenario took 240 us of this launch there.
+// When nothing is marked it only reads the flag.
+__global__ __launch_bounds__(64) void split_long_kernel(EvalArgs a)
+{
+    __shared__ LaneLds<256> L;
+    static_assert(sizeof(L) >= 2 * sizeof(int32_t) * (SPLIT_MAX_N + 1),
+                  "the wavefront's prefix loads and g values of a maximal tour fit");
+    if (*(cu32 *)&a.ctl->ovf_total == 0) return;
+    const int lane = threadIdx.x;
+    const long long T = *(ci64 *)a.tour.nt;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)a.demand, (short)0, (int)a.lane_bytes, 0x00020000);
     const long long nsb = (a.S + 63) / 64;
     for (long long k = blockIdx.x; k < T * nsb; k += gridDim.x) {
         const int t = (int)(k / nsb);
         const long long s0 = (k - (long long)t * nsb) * 64;
-        const long long scen = s0 + threadIdx.x;
-        const bool marked = scen < a.S && a.cost[(long long)t * a.ldc + scen] == kCostOvf;
-        unsigned long long m = __ballot(marked);
+        const bool active = s0 + lane < a.S;
+        const long long scen = active ? s0 + lane : a.S - 1;
+        int32_t *cost = a.cost + (long long)t * a.ldc;
+        const bool todo = active && cost[scen] == kCostOvf;
+        if (!__any(todo)) continue;
+        const LaneTour tr = lane_tour(a, t);
+        const uint32_t lane_off = (uint32_t)scen * 2u;
+        uint16_t qA[16], qB[16], qC[16];
+        lane_load_block<16>(rsrc, tr.rowoff, lane_off, 0, qA);
+        lane_load_block<16>(rsrc, tr.rowoff, lane_off, 1, qB);
+        lane_load_block<16>(rsrc, tr.rowoff, lane_off, 2, qC);
+        LaneState<16, 256> st;
+        lane_run<16, 256>(L, tr, a.Q, rsrc, lane_off, qA, qB, qC, false, st);
+        if (a.recount) {
+            const int past = (int)__popcll(__ballot(todo && (st.past || st.ovf)));
+            if (lane == 0 && past) atomicAdd(&a.stats[t].ovf_count, past);
+        }
+        if (todo && st.ovf == 0) {
+            if (st.err)
+                atomicOr(&a.stats[t].err_demand, 1);
+            else
+                cost[scen] = st.gres;
+        }
+        unsigned long long m = __ballot(todo && st.ovf);
+        int32_t *G = reinterpret_cast<int32_t *>(&L);
         while (m) {
             const int j = __builtin_ctzll(m);
             m &= m - 1;
-            wave_one(a, t, s0 + j, G, PP);
+            wave_one(a, t, s0 + j, G, G + SPLIT_MAX_N + 1);
         }
     }
 }
@@ -1121,7 +1318,10 @@ hipError_t launch_prep(const PrepArgs &a, hipStream_t stream)
 
 hipError_t launch_lane(const EvalArgs &a, hipStream_t stream)
 {
-    if (a.lane_block == 8)
+    if (a.lane_block == 0)
+        hipLaunchKernelGGL(split_lane_kernel<0>, dim3((unsigned)a.lane_grid), dim3(64), 0, stream,
+                           a);
+    else if (a.lane_block == 8)
         hipLaunchKernelGGL(split_lane_kernel<8>, dim3((unsigned)a.lane_grid), dim3(64), 0, stream,
                            a);
     else
@@ -1147,18 +1347,15 @@ hipError_t launch_wave_all(const EvalArgs &a, hipStream_t stream)
     const long long work = a.S * a.tour.T_grid;
     const long long nb = work < a.wave_grid ? work : a.wave_grid;
     hipLaunchKernelGGL(split_wave_kernel, dim3((unsigned)nb), dim3(64), wave_lds_bytes(a.maxn), stream,
-                       a, 0);
+                       a);
     return hipGetLastError();
 }
 
-hipError_t launch_wave_fallback(const EvalArgs &a, hipStream_t stream)
+hipError_t launch_long(const EvalArgs &a, hipStream_t stream)
 {
-    hipError_t e = wave_lds_allow(wave_lds_bytes(a.maxn));
-    if (e != hipSuccess) return e;
     const long long work = (a.S + 63) / 64 * a.tour.T_grid;
-    const long long nb = work < 2048 ? work : 2048;
-    hipLaunchKernelGGL(split_wave_kernel, dim3((unsigned)nb), dim3(64), wave_lds_bytes(a.maxn), stream,
-                       a, 1);
+    const long long nb = work < a.long_grid ? work : a.long_grid;
+    hipLaunchKernelGGL(split_long_kernel, dim3((unsigned)nb), dim3(64), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -1,0 +1,100 @@
+"""Window lengths around the edges of the kernels' histories: blocks of 8 states keep windows of up
+to 23 positions, blocks of 16 up to 47, the long kernel up to 239. Costs and moments against the
+oracle, bit for bit, and n_fallback against its definition: the scenarios whose window of some last
+state of a full 16-state block (but the last block) holds more than 47 predecessors."""
+import numpy as np
+import pytest
+
+import gen
+import oracle
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+N, S = 700, 130
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import paper_2511_18022_amd as sg
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    c = sg.SplitContext(0)
+    c.set_coords(gen.coords(21, N))
+    yield c
+    c.close()
+
+
+def past_history(tour, dem, Q):
+    n = len(tour)
+    P = np.zeros((n + 1, dem.shape[1]), dtype=np.int64)
+    P[1:] = np.cumsum(dem[tour - 1], axis=0)
+    hit = np.zeros(dem.shape[1], dtype=bool)
+    for i in range(63, 16 * (n // 16), 16):
+        hit |= P[i] - P[i - 48] <= Q
+    return int(hit.sum())
+
+
+def demands(window, spread, seed):
+    """Windows of about `window` customers: demands of 8 each, or 8 plus or minus `spread`."""
+    g = np.random.default_rng(seed)
+    dem = np.full((N, S), 8, dtype=np.int16)
+    if spread:
+        dem += g.integers(-spread, spread + 1, size=dem.shape, dtype=np.int16)
+    return dem, 8 * window
+
+
+@pytest.mark.parametrize("n", [700, 641, 96, 16])
+@pytest.mark.parametrize("window", [6, 17, 18, 19, 23, 24, 30, 44, 45, 46, 47, 48, 49, 90, 111, 224,
+                                    238, 239, 240, 256, 690])
+def test_windows_at_the_edges_of_the_histories(ctx, window, n):
+    d = oracle.dist_matrix(gen.coords(21, N))
+    tour = gen.tour(21, N, n, variant=3)
+    for spread in (0, 7):
+        dem, Q = demands(window, spread, window)
+        want = oracle.split(tour, d, dem, Q)
+        cost, st = ctx.eval(tour, torch.from_numpy(dem).cuda(), Q)
+        assert np.array_equal(cost.cpu().numpy(), want), (window, n, spread)
+        mom = oracle.moments(want)
+        assert (st.sum, st.sumsq, st.mean, st.var) == (mom["sum"], mom["sumsq"], mom["mean"],
+                                                      mom["var"])
+        assert st.n_fallback == past_history(tour, dem, Q), (window, n, spread)
+
+
+def test_tours_of_short_middling_and_long_windows_in_one_batch(ctx):
+    # the classes are taken tour by tour: one demand matrix, tours over customers of small, middling
+    # and large demands, and some scenarios whose windows outgrow what their tour's sample shows
+    d = oracle.dist_matrix(gen.coords(21, N))
+    g = np.random.default_rng(5)
+    dem = np.empty((N, S), dtype=np.int16)
+    dem[:200] = g.integers(1, 4, size=(200, S))     # Q / 2: windows of about 100
+    dem[200:450] = g.integers(3, 12, size=(250, S))  # about 27
+    dem[450:] = g.integers(14, 20, size=(250, S))    # about 12
+    dem[200:, 127] = 1
+    Q = 200
+    ids = [np.arange(1, 201), np.arange(201, 451), np.arange(451, 701), np.arange(1, 701)]
+    tours = [g.permutation(i).astype(np.int32) for i in ids]
+    dt = torch.from_numpy(dem).cuda()
+    graph = ctx.graph(4, 4 * N, dt, Q)
+    cost, stats, status = ctx.eval_batch(tours, dt, Q)
+    for t, tour in enumerate(tours):
+        want = oracle.split(tour, d, dem, Q)
+        assert np.array_equal(cost[t].cpu().numpy(), want), t
+        assert stats[t].sum == oracle.moments(want)["sum"]
+        assert stats[t].n_fallback == past_history(tour, dem, Q), t
+    for _ in range(3):
+        got = graph.launch(tours)
+        gstats, gstatus = graph.stats()
+        assert torch.equal(got, cost) and gstatus == [0] * 4
+        assert [s.n_fallback for s in gstats] == [s.n_fallback for s in stats]
+    graph.close()
+
+
+def test_infeasible_demand_under_long_windows(ctx):
+    import paper_2511_18022_amd as sg
+    tour = gen.tour(21, N, 300, variant=4)
+    dem, Q = demands(100, 3, 9)
+    dem[int(tour[150]) - 1, 77] = Q + 1
+    with pytest.raises(sg.SplitError) as ei:
+        ctx.eval(tour, torch.from_numpy(dem).cuda(), Q)
+    assert ei.value.status == sg.SPLIT_E_DEMAND
