@@ -129,7 +129,7 @@ split_status split_eval(split_ctx *ctx, const int32_t *tour, int32_t n, const in
  * split_eval for callers that cannot allocate device memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): the same evaluation and results as
  * split_eval, with every per-call device buffer (the staged tour, the per-position arrays, the
- * result block, the counters and the moment partials) carved from a fixed scratch array of
+ * result block, the counters and the cost sums) carved from a fixed scratch array of
  * 192 KiB that each GPU holds for the life of the process. The call makes no device or pinned
  * host allocation; the context, its instance and the caller's demand and cost buffers must
  * exist beforehand. Arguments as in split_eval; `tour` is copied from pageable host memory.
@@ -238,7 +238,7 @@ split_status split_autotune(split_ctx *ctx, const int32_t *tours, const int64_t 
 
 /*
  * Captured evaluation: the whole split_eval_batch sequence (tour upload from pinned host
- * memory, prep, Split DP, moments, statistics copy) recorded once as a HIP graph for a fixed
+ * memory, prep, Split DP, tail) recorded once as a HIP graph for a fixed
  * demand matrix, cost matrix, S, Q and instance, then replayed with new tours by
  * split_graph_launch: one graph launch per batch, for search loops that evaluate many batches.
  * Results are exactly those of split_eval_batch (Section 3, Eqs. (1)-(3)).

@@ -40,7 +40,7 @@ constexpr int kGraphSlots = 2;          // a graph's launches alternate between 
 constexpr int32_t kMaxLanePerCu = 8;    // the lane kernel's LDS allows 8 workgroups per CU
 constexpr int32_t kLaneStaticPerCu = kMaxLanePerCu;  // fixed-stride grid: all resident at once
 constexpr int64_t kLaneStaticMaxRounds = 16;         // and at most this many items each
-constexpr int32_t kLongPerCu = 2;       // the long kernel's LDS allows 2 workgroups per CU
+constexpr int32_t kTailPerCu = 2;       // the tail kernel's LDS allows 2 workgroups per CU
 constexpr int64_t kClassMaxArc = 2047;  // 16 states times 2 max_arc: below 2^16
 
 // Device buffers of one evaluation sequence. The context's grow with its calls; a graph owns
@@ -54,8 +54,8 @@ struct EvalBuffers {
     int64_t cap_pos = 0;      // entries of the per-tour arrays
     DevStats *d_stats = nullptr;
     int32_t cap_T = 0;
-    unsigned long long *d_partials = nullptr;
-    int64_t cap_partials = 0;
+    char *d_sums = nullptr;
+    int64_t cap_sums = 0;  // bytes
     BatchCtl *d_ctl = nullptr;
     int16_t *d_mask = nullptr;  // two-kernel form only: window starts [positions][S]
     int64_t cap_mask = 0;       // elements
@@ -68,7 +68,7 @@ void free_buffers(EvalBuffers &b)
     if (b.d_rowoff32) (void)hipFree(b.d_rowoff32);
     if (b.d_w) (void)hipFree(b.d_w);
     if (b.d_stats) (void)hipFree(b.d_stats);
-    if (b.d_partials) (void)hipFree(b.d_partials);
+    if (b.d_sums) (void)hipFree(b.d_sums);
     if (b.d_ctl) (void)hipFree(b.d_ctl);
     if (b.d_mask) (void)hipFree(b.d_mask);
     b = EvalBuffers();
@@ -101,7 +101,7 @@ struct BatchInfo {
 struct Plan {
     int form = SPLIT_FORM_LANE;
     int32_t lane_grid = 0, wave_grid = 0, maxn = 0, lane_block = 16;
-    int32_t long_grid = 0;
+    int32_t tail_grid = 0;
     bool lane_static = false, lane_uniform = false;
     uint32_t lane_bytes = 0;
 };
@@ -141,9 +141,9 @@ struct split_ctx {
     hipEvent_t stage_ev[kStages] = {};
     bool stage_ev_used[kStages] = {};
     int stage = 0;
-    DevStats *h_stats = nullptr;
+    TourResult *h_stats = nullptr;
     int32_t cap_h_stats = 0;
-    hipEvent_t stats_ev = nullptr;
+    hipEvent_t last_ev = nullptr;  // end of the latest call (one of stage_ev)
     bool have_call = false;
     int64_t last_S = 0;
     int32_t last_T = 0;
@@ -176,7 +176,7 @@ struct split_graph {
     Plan plan;
     hipStream_t cap_stream = nullptr;
     char *h_stage[kGraphSlots] = {};
-    DevStats *h_stats[kGraphSlots] = {};
+    TourResult *h_stats[kGraphSlots] = {};
     hipGraph_t graph[kGraphSlots] = {};
     hipGraphExec_t exec[kGraphSlots] = {};
     hipEvent_t done[kGraphSlots] = {};
@@ -235,17 +235,17 @@ bool grow(P **ptr, size_t bytes)
     return hipMalloc(ptr, bytes) == hipSuccess;
 }
 
-// Device buffers for T tours with total_n positions in all, staging of stage_bytes and moment
-// partials of partial_blocks blocks (exact sizes, or with room to grow). Growing waits for
+// Device buffers for T tours with total_n positions in all, a header of stage_bytes and sum_bytes
+// of cost sums (exact sizes, or with room to grow). Growing waits for
 // enqueued work before replacing a buffer.
 split_status ensure_buffers(split_ctx *ctx, EvalBuffers &b, int32_t T, int64_t total_n,
-                            int64_t stage_bytes, int64_t partial_blocks, bool exact)
+                            int64_t stage_bytes, int64_t sum_bytes, bool exact)
 {
     const int64_t pos = total_n + (int64_t)T * (1 + kRowPad);
     const bool g_pos = pos > b.cap_pos, g_stage = stage_bytes > b.cap_stage;
-    const bool g_T = T > b.cap_T, g_part = partial_blocks > b.cap_partials;
+    const bool g_T = T > b.cap_T, g_sums = sum_bytes > b.cap_sums;
     const bool g_ctl = b.d_ctl == nullptr;
-    if (!g_pos && !g_stage && !g_T && !g_part && !g_ctl) return SPLIT_OK;
+    if (!g_pos && !g_stage && !g_T && !g_sums && !g_ctl) return SPLIT_OK;
     HIP_TRY(ctx, hipDeviceSynchronize());
     auto room = [exact](int64_t need, int64_t floor) {
         return exact ? need : (need < floor ? floor : need + need / 4);
@@ -273,15 +273,23 @@ split_status ensure_buffers(split_ctx *ctx, EvalBuffers &b, int32_t T, int64_t t
             return fail(ctx, SPLIT_E_NOMEM, "allocation of %d result blocks failed", nt);
         b.cap_T = nt;
     }
-    if (g_part) {
-        b.cap_partials = 0;
-        if (!grow(&b.d_partials, sizeof(unsigned long long) * 3 * partial_blocks))
-            return fail(ctx, SPLIT_E_NOMEM, "allocation of moment partials failed");
-        b.cap_partials = partial_blocks;
+    if (g_sums) {
+        b.cap_sums = 0;
+        if (!grow(&b.d_sums, (size_t)sum_bytes))
+            return fail(ctx, SPLIT_E_NOMEM, "allocation of the cost sums failed");
+        b.cap_sums = sum_bytes;
     }
     if (g_ctl && hipMalloc(&b.d_ctl, sizeof(BatchCtl)) != hipSuccess)
         return fail(ctx, SPLIT_E_NOMEM, "allocation of the batch counters failed");
     return SPLIT_OK;
+}
+
+// Pinned host memory that kernels read and write themselves: coherent, so that neither side sees
+// what a cache kept from an earlier call.
+template <class P>
+bool pinned(P **ptr, size_t bytes)
+{
+    return hipHostMalloc((void **)ptr, bytes, hipHostMallocCoherent) == hipSuccess;
 }
 
 // Pinned host staging of the context: kStages slots of stage_bytes and T result blocks.
@@ -295,7 +303,7 @@ split_status ensure_host(split_ctx *ctx, int64_t stage_bytes, int32_t T)
             if (ctx->h_stage[k]) (void)hipHostFree(ctx->h_stage[k]);
             ctx->h_stage[k] = nullptr;
             ctx->stage_ev_used[k] = false;
-            if (hipHostMalloc((void **)&ctx->h_stage[k], (size_t)nb, 0) != hipSuccess)
+            if (!pinned(&ctx->h_stage[k], (size_t)nb))
                 return fail(ctx, SPLIT_E_NOMEM, "pinned staging of %lld bytes failed",
                             (long long)nb);
         }
@@ -307,9 +315,9 @@ split_status ensure_host(split_ctx *ctx, int64_t stage_bytes, int32_t T)
         if (ctx->h_stats) (void)hipHostFree(ctx->h_stats);
         ctx->h_stats = nullptr;
         ctx->cap_h_stats = 0;
-        if (hipHostMalloc((void **)&ctx->h_stats, sizeof(DevStats) * nt, 0) != hipSuccess)
+        if (!pinned(&ctx->h_stats, sizeof(TourResult) * nt))
             return fail(ctx, SPLIT_E_NOMEM, "pinned allocation of %d result blocks failed", nt);
-        memset(ctx->h_stats, 0, sizeof(DevStats) * nt);
+        memset(ctx->h_stats, 0, sizeof(TourResult) * nt);
         ctx->cap_h_stats = nt;
     }
     return SPLIT_OK;
@@ -349,16 +357,16 @@ split_status timing_begin(split_ctx *ctx, hipStream_t stream, hipEvent_t *stop_o
     return SPLIT_OK;
 }
 
-void fill_stats(const DevStats &d, int64_t S, split_stats *out)
+void fill_stats(const TourResult &d, int64_t S, split_stats *out)
 {
+    const unsigned __int128 sq = ((unsigned __int128)d.sq_h32 << 32) + d.sq_l32;
     out->sum = (int64_t)d.sum;
-    out->sumsq_lo = d.sq_lo;
-    out->sumsq_hi = d.sq_hi;
+    out->sumsq_lo = (uint64_t)sq;
+    out->sumsq_hi = (uint64_t)(sq >> 64);
     out->mean = (double)(int64_t)d.sum / (double)S;
     if (S == 1) {
         out->var = 0.0;
     } else {
-        const unsigned __int128 sq = ((unsigned __int128)d.sq_hi << 64) | d.sq_lo;
         const unsigned __int128 sm = d.sum;
         const unsigned __int128 num = (unsigned __int128)(uint64_t)S * sq - sm * sm;
         out->var = ((double)num / (double)S) / (double)(S - 1);
@@ -367,7 +375,7 @@ void fill_stats(const DevStats &d, int64_t S, split_stats *out)
 }
 
 // Per-tour statistics and status of T result blocks; SPLIT_E_DEMAND names the first bad tour.
-split_status report(split_ctx *ctx, const DevStats *h, int32_t T, int64_t S, split_stats *stats,
+split_status report(split_ctx *ctx, const TourResult *h, int32_t T, int64_t S, split_stats *stats,
                     int32_t *tour_status)
 {
     int bad = -1;
@@ -453,6 +461,17 @@ void stage_write(char *h, const StageLayout &L, const int32_t *tours, const int6
     memcpy(h + L.off_tours, tours, sizeof(int32_t) * (size_t)tour_ptr[T]);
 }
 
+// The cost sums of a launch of up to T_grid tours over S scenarios (their buffer left open).
+SumSlots sum_slots(int form, int32_t T_grid, int64_t S)
+{
+    SumSlots s;
+    s.base = nullptr;
+    s.by_item = form == SPLIT_FORM_LANE && T_grid > 1 ? 1 : 0;
+    s.slots = s.by_item ? (S + 63) / 64 : kMaxSlots;
+    s.stride = s.by_item ? (int32_t)sizeof(CostSums) : kSlotStride;
+    return s;
+}
+
 // Launch configuration from the tuning. T_grid bounds T; maxn and max_id bound the tours;
 // `uniform`: every tour of the launch has the same length (so has every work item).
 Plan make_plan(const split_ctx *ctx, const split_tuning &tu, int64_t S, int64_t ld, int32_t Q,
@@ -486,25 +505,25 @@ Plan make_plan(const split_ctx *ctx, const split_tuning &tu, int64_t S, int64_t 
     // n_fallback then does not depend on the length chosen.
     const bool by_class = tu.lane_block == 0 && max_arc <= kClassMaxArc;
     p.lane_block = by_class ? 0 : tu.lane_block == 8 ? 8 : 16;
-    p.long_grid = ctx->cus * kLongPerCu;
+    p.tail_grid = ctx->cus * kTailPerCu;
     p.wave_grid = tu.wave_grid > 0 ? tu.wave_grid : 65536;
     p.maxn = maxn;
     return p;
 }
 
-// The kernels of one evaluation on `stream`, reading the header already staged in b.d_stage
-// (laid out by L): prep, the Split DP (lane kernel and its fallback, or the wave kernel),
-// moments. The dominant kernel is timed when ctx->timing and `timed` are set.
+// The kernels of one evaluation on `stream`, reading the header `src` (host or device memory, laid
+// out by L) and reporting the tours' results to `out`: prep, the Split DP (lane kernel or wave
+// kernel), tail. The dominant kernel is timed when ctx->timing and `timed` are set.
 split_status enqueue_kernels(split_ctx *ctx, const Instance &in, const EvalBuffers &b,
-                             const StageLayout &L, const Plan &p, const int16_t *demand,
+                             const StageLayout &L, const char *src, TourResult *out,
+                             const Plan &p, const int16_t *demand,
                              int64_t S, int64_t ld, int32_t Q, int32_t *cost, int64_t ldc,
                              hipStream_t stream, bool timed)
 {
     TourDev td;
-    td.nt = reinterpret_cast<const int64_t *>(b.d_stage);
+    td.nt = reinterpret_cast<int64_t *>(b.d_stage);
     td.tptr = td.nt + 1;
-    td.order = reinterpret_cast<const int32_t *>(b.d_stage + L.off_order);
-    td.tours = reinterpret_cast<const int32_t *>(b.d_stage + L.off_tours);
+    td.order = reinterpret_cast<int32_t *>(b.d_stage + L.off_order);
     td.T_grid = L.capT;
     td.rowoff = b.d_rowoff;
     td.rowoff32 = b.d_rowoff32;
@@ -512,6 +531,12 @@ split_status enqueue_kernels(split_ctx *ctx, const Instance &in, const EvalBuffe
 
     PrepArgs pa;
     pa.tour = td;
+    pa.src_nt = reinterpret_cast<const int64_t *>(src);
+    pa.src_tptr = pa.src_nt + 1;
+    pa.src_order = reinterpret_cast<const int32_t *>(src + L.off_order);
+    pa.src_tours = reinterpret_cast<const int32_t *>(src + L.off_tours);
+    pa.sums = sum_slots(p.form, L.capT, S);
+    pa.sums.base = b.d_sums;
     pa.N = in.N;
     pa.kind = in.kind;
     pa.xy = in.d_xy;
@@ -530,6 +555,8 @@ split_status enqueue_kernels(split_ctx *ctx, const Instance &in, const EvalBuffe
     ea.cost = cost;
     ea.ldc = ldc;
     ea.stats = b.d_stats;
+    ea.sums = pa.sums;
+    ea.out = out;
     ea.ctl = b.d_ctl;
     ea.lane_bytes = p.lane_bytes;
     ea.lane_grid = p.lane_grid;
@@ -537,7 +564,7 @@ split_status enqueue_kernels(split_ctx *ctx, const Instance &in, const EvalBuffe
     ea.lane_uniform = p.lane_uniform ? 1 : 0;
     ea.lane_block = p.lane_block;
     ea.recount = p.form == SPLIT_FORM_LANE && p.lane_block != 8 ? 1 : 0;
-    ea.long_grid = p.long_grid;
+    ea.tail_grid = p.tail_grid;
     ea.wave_grid = p.wave_grid;
     ea.maxn = p.maxn;
 
@@ -555,24 +582,12 @@ split_status enqueue_kernels(split_ctx *ctx, const Instance &in, const EvalBuffe
         HIP_TRY(ctx, launch_mask(ea, b.d_mask, S, stream));
         HIP_TRY(ctx, launch_masked_dp(ea, b.d_mask, S, stream));
         if (stop) HIP_TRY(ctx, hipEventRecord(stop, stream));
-        HIP_TRY(ctx, launch_long(ea, stream));
     } else {
         ctx->tname = lane_kernel_name();
         HIP_TRY(ctx, launch_lane(ea, stream));
         if (stop) HIP_TRY(ctx, hipEventRecord(stop, stream));
-        HIP_TRY(ctx, launch_long(ea, stream));
     }
-
-    MomentArgs ma;
-    ma.cost = cost;
-    ma.ldc = ldc;
-    ma.S = S;
-    ma.nt = td.nt;
-    ma.T_grid = L.capT;
-    ma.partials = b.d_partials;
-    ma.nblocks = moment_blocks(S);
-    ma.stats = b.d_stats;
-    HIP_TRY(ctx, launch_moments(ma, stream));
+    HIP_TRY(ctx, launch_tail(ea, stream));
     return SPLIT_OK;
 }
 
@@ -592,24 +607,22 @@ split_status eval_batch(split_ctx *ctx, const char *who, const int32_t *tours,
     DeviceGuard g(ctx->device);
     if (!g.ok) return fail(ctx, SPLIT_E_HIP, "hipSetDevice failed");
     const StageLayout L = stage_layout(T, bi.total_n);
-    const int32_t nblk = moment_blocks(S);
-    st = ensure_buffers(ctx, ctx->buf, T, bi.total_n, (int64_t)L.bytes, (int64_t)nblk * T, false);
+    const Plan p = make_plan(ctx, ctx->tuning, S, ld, Q, T, bi.maxn, bi.max_id,
+                             bi.minn == bi.maxn, ctx->inst.max_arc);
+    // on the device the header ends before the tours
+    const SumSlots ss = sum_slots(p.form, T, S);
+    st = ensure_buffers(ctx, ctx->buf, T, bi.total_n, (int64_t)L.off_tours,
+                        ss.slots * ss.stride * T, false);
     if (st != SPLIT_OK) return st;
     st = ensure_host(ctx, (int64_t)L.bytes, T);
     if (st != SPLIT_OK) return st;
 
-    // Upload through a pinned slot, reused only after its previous copy completed.
+    // The header in a pinned slot, reused only after the call that read it completed.
     const int slot = ctx->stage;
     ctx->stage = (ctx->stage + 1) % kStages;
     if (ctx->stage_ev_used[slot]) HIP_TRY(ctx, hipEventSynchronize(ctx->stage_ev[slot]));
     stage_write(ctx->h_stage[slot], L, tours, tour_ptr, T, ctx->tuning.order);
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->buf.d_stage, ctx->h_stage[slot], L.bytes,
-                                hipMemcpyHostToDevice, stream));
-    HIP_TRY(ctx, hipEventRecord(ctx->stage_ev[slot], stream));
-    ctx->stage_ev_used[slot] = true;
 
-    const Plan p = make_plan(ctx, ctx->tuning, S, ld, Q, T, bi.maxn, bi.max_id,
-                             bi.minn == bi.maxn, ctx->inst.max_arc);
     if (p.form == SPLIT_FORM_MASK && (__int128)ctx->buf.cap_pos * S > ctx->buf.cap_mask) {
         // one int16 window start per (position row, scenario)
         HIP_TRY(ctx, hipDeviceSynchronize());
@@ -622,11 +635,14 @@ split_status eval_batch(split_ctx *ctx, const char *who, const int32_t *tours,
                         "could not be allocated", who, (long long)(2 * elems));
         ctx->buf.cap_mask = elems;
     }
-    st = enqueue_kernels(ctx, ctx->inst, ctx->buf, L, p, demand, S, ld, Q, cost, ldc, stream, true);
+    st = enqueue_kernels(ctx, ctx->inst, ctx->buf, L, ctx->h_stage[slot], ctx->h_stats, p, demand,
+                         S, ld, Q, cost, ldc, stream, true);
+    // recorded after a failed launch too: what was enqueued reads the slot
+    const hipError_t ev = hipEventRecord(ctx->stage_ev[slot], stream);
+    ctx->stage_ev_used[slot] = true;
     if (st != SPLIT_OK) return st;
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->h_stats, ctx->buf.d_stats, sizeof(DevStats) * (size_t)T,
-                                hipMemcpyDeviceToHost, stream));
-    HIP_TRY(ctx, hipEventRecord(ctx->stats_ev, stream));
+    HIP_TRY(ctx, ev);
+    ctx->last_ev = ctx->stage_ev[slot];
     ctx->have_call = true;
     ctx->last_S = S;
     ctx->last_T = T;
@@ -697,8 +713,7 @@ split_status split_ctx_create(int hip_device, split_ctx **out)
     ctx->device = hip_device;
     DeviceGuard g(hip_device);
     hipDeviceProp_t prop;
-    if (!g.ok || hipGetDeviceProperties(&prop, hip_device) != hipSuccess ||
-        hipEventCreateWithFlags(&ctx->stats_ev, hipEventDisableTiming) != hipSuccess) {
+    if (!g.ok || hipGetDeviceProperties(&prop, hip_device) != hipSuccess) {
         split_ctx_destroy(ctx);
         return SPLIT_E_NOMEM;
     }
@@ -733,7 +748,6 @@ void split_ctx_destroy(split_ctx *ctx)
             if (ctx->stage_ev[k]) (void)hipEventDestroy(ctx->stage_ev[k]);
         }
         if (ctx->h_stats) (void)hipHostFree(ctx->h_stats);
-        if (ctx->stats_ev) (void)hipEventDestroy(ctx->stats_ev);
         for (auto &pr : ctx->tpairs) {
             (void)hipEventDestroy(pr.first);
             (void)hipEventDestroy(pr.second);
@@ -814,11 +828,11 @@ split_status split_eval(split_ctx *ctx, const int32_t *tour, int32_t n, const in
     return SPLIT_OK;
 }
 
-// The largest call (a tour of SPLIT_MAX_N positions, 1024 moment blocks) fits the scratch.
+// The largest call (a tour of SPLIT_MAX_N positions) fits the scratch.
 static_assert(((32 + 4 * (size_t)SPLIT_MAX_N + 255) & ~(size_t)255) +
                   ((8 * ((size_t)SPLIT_MAX_N + 1 + kRowPad) + 255) & ~(size_t)255) +
                   2 * ((4 * ((size_t)SPLIT_MAX_N + 1 + kRowPad) + 255) & ~(size_t)255) +
-                  2 * 256 + 24 * 1024 <= kScratchBytes,
+                  3 * 256 + kSlotStride * kMaxSlots <= kScratchBytes,
               "split_eval_noalloc: the scratch does not hold a maximal tour");
 
 split_status split_eval_noalloc(split_ctx *ctx, const int32_t *tour, int32_t n,
@@ -843,7 +857,6 @@ split_status split_eval_noalloc(split_ctx *ctx, const int32_t *tour, int32_t n,
     // Carve the call's device buffers from the scratch, each 256-byte aligned.
     const StageLayout L = stage_layout(1, n);
     const int64_t pos = (int64_t)n + 1 + kRowPad;
-    const int32_t nblk = moment_blocks(S);
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t o_stage = 0;
     const size_t o_rowoff = o_stage + up(L.bytes);
@@ -851,8 +864,9 @@ split_status split_eval_noalloc(split_ctx *ctx, const int32_t *tour, int32_t n,
     const size_t o_w = o_rowoff32 + up(sizeof(uint32_t) * (size_t)pos);
     const size_t o_stats = o_w + up(sizeof(int32_t) * (size_t)pos);
     const size_t o_ctl = o_stats + up(sizeof(DevStats));
-    const size_t o_part = o_ctl + up(sizeof(BatchCtl));
-    const size_t need = o_part + up(sizeof(unsigned long long) * 3 * (size_t)nblk);
+    const size_t o_out = o_ctl + up(sizeof(BatchCtl));
+    const size_t o_sums = o_out + up(sizeof(TourResult));
+    const size_t need = o_sums + (size_t)kSlotStride * kMaxSlots;
     if (need > kScratchBytes)
         return fail(ctx, SPLIT_E_INVAL, "%s: a tour of %d positions needs %zu bytes of device "
                     "scratch, above the fixed %zu", who, n, need, kScratchBytes);
@@ -869,8 +883,9 @@ split_status split_eval_noalloc(split_ctx *ctx, const int32_t *tour, int32_t n,
     b.d_stats = reinterpret_cast<DevStats *>(ctx->scratch + o_stats);
     b.cap_T = 1;
     b.d_ctl = reinterpret_cast<BatchCtl *>(ctx->scratch + o_ctl);
-    b.d_partials = reinterpret_cast<unsigned long long *>(ctx->scratch + o_part);
-    b.cap_partials = nblk;
+    b.d_sums = reinterpret_cast<char *>(ctx->scratch + o_sums);
+    b.cap_sums = (int64_t)kSlotStride * kMaxSlots;
+    TourResult *d_out = reinterpret_cast<TourResult *>(ctx->scratch + o_out);
 
     // The staged header of a batch of one: T, tptr, order, then the tour itself, copied from
     // pageable host memory (the runtime stages it before the call returns).
@@ -884,12 +899,13 @@ split_status split_eval_noalloc(split_ctx *ctx, const int32_t *tour, int32_t n,
                                 hipMemcpyHostToDevice, stream));
     const Plan p = make_plan(ctx, tu, S, ld, Q, 1, bi.maxn, bi.max_id, true,
                              ctx->inst.max_arc);
-    // the prep kernel zeroes the result block and the counters of every call
-    st = enqueue_kernels(ctx, ctx->inst, b, L, p, demand, S, ld, Q, cost, S, stream, false);
+    // the prep kernel zeroes the sums and the counters of every call
+    st = enqueue_kernels(ctx, ctx->inst, b, L, b.d_stage, d_out, p, demand, S, ld, Q, cost, S,
+                         stream, false);
     if (st != SPLIT_OK) return st;
     if (!stats) return SPLIT_OK;
-    DevStats d;
-    HIP_TRY(ctx, hipMemcpyAsync(&d, b.d_stats, sizeof d, hipMemcpyDeviceToHost, stream));
+    TourResult d;
+    HIP_TRY(ctx, hipMemcpyAsync(&d, d_out, sizeof d, hipMemcpyDeviceToHost, stream));
     HIP_TRY(ctx, hipStreamSynchronize(stream));
     fill_stats(d, S, stats);
     if (d.err_demand)
@@ -916,7 +932,7 @@ split_status split_batch_stats_get(split_ctx *ctx, split_stats *stats, int32_t *
     if (!ctx) return SPLIT_E_INVAL;
     if (!ctx->have_call) return fail(ctx, SPLIT_E_INVAL, "split_batch_stats_get: no evaluation yet");
     DeviceGuard g(ctx->device);
-    HIP_TRY(ctx, hipEventSynchronize(ctx->stats_ev));
+    HIP_TRY(ctx, hipEventSynchronize(ctx->last_ev));
     return report(ctx, ctx->h_stats, ctx->last_T, ctx->last_S, stats, tour_status);
 }
 
@@ -926,8 +942,8 @@ split_status split_stats_get(split_ctx *ctx, split_stats *stats)
     if (!stats) return fail(ctx, SPLIT_E_INVAL, "split_stats_get: NULL stats");
     if (!ctx->have_call) return fail(ctx, SPLIT_E_INVAL, "split_stats_get: no evaluation yet");
     DeviceGuard g(ctx->device);
-    HIP_TRY(ctx, hipEventSynchronize(ctx->stats_ev));
-    const DevStats d = ctx->h_stats[0];
+    HIP_TRY(ctx, hipEventSynchronize(ctx->last_ev));
+    const TourResult d = ctx->h_stats[0];
     fill_stats(d, ctx->last_S, stats);
     if (d.err_demand)
         return fail(ctx, SPLIT_E_DEMAND,
@@ -1237,14 +1253,14 @@ split_status split_graph_create(split_ctx *ctx, int32_t max_T, int64_t max_total
     gr->Q = Q;
     gr->order = ctx->tuning.order;
     gr->layout = stage_layout(max_T, max_total_n);
-    const int32_t nblk = moment_blocks(S);
-    st = ensure_buffers(ctx, gr->buf, max_T, max_total_n, (int64_t)gr->layout.bytes,
-                        (int64_t)nblk * max_T, true);
-    if (st != SPLIT_OK) return bail(st);
     // any tour of the instance: lengths up to N, ids up to N
     // the tours of a replay are known only then: a fixed item stride only for one tour
     gr->plan = make_plan(ctx, ctx->tuning, S, ld, Q, max_T, N, N, max_T == 1,
                          gr->inst.max_arc);
+    const SumSlots ss = sum_slots(gr->plan.form, max_T, S);
+    st = ensure_buffers(ctx, gr->buf, max_T, max_total_n, (int64_t)gr->layout.off_tours,
+                        ss.slots * ss.stride * max_T, true);
+    if (st != SPLIT_OK) return bail(st);
     if (gr->plan.form == SPLIT_FORM_MASK)
         return bail(fail(ctx, SPLIT_E_INVAL, "split_graph_create: the two-kernel form is an "
                          "ablation and is not captured"));
@@ -1253,28 +1269,21 @@ split_status split_graph_create(split_ctx *ctx, int32_t max_T, int64_t max_total
         return bail(fail(ctx, SPLIT_E_HIP, "split_graph_create: hipStreamCreate failed"));
     }
     for (int k = 0; k < kGraphSlots; ++k) {
-        if (hipHostMalloc((void **)&gr->h_stage[k], gr->layout.bytes, 0) != hipSuccess ||
-            hipHostMalloc((void **)&gr->h_stats[k], sizeof(DevStats) * (size_t)max_T, 0) !=
-                hipSuccess)
+        if (!pinned(&gr->h_stage[k], gr->layout.bytes) ||
+            !pinned(&gr->h_stats[k], sizeof(TourResult) * (size_t)max_T))
             return bail(fail(ctx, SPLIT_E_NOMEM, "split_graph_create: pinned allocation failed"));
         memset(gr->h_stage[k], 0, gr->layout.bytes);
         if (hipEventCreateWithFlags(&gr->done[k], hipEventDisableTiming) != hipSuccess)
             return bail(fail(ctx, SPLIT_E_HIP, "split_graph_create: hipEventCreate failed"));
     }
-    // one graph per host slot: upload of the slot's header, the kernels, the statistics copy
+    // one graph per host slot: the kernels read the slot's header and report to its results
     for (int k = 0; k < kGraphSlots; ++k) {
         if (hipStreamBeginCapture(gr->cap_stream, hipStreamCaptureModeThreadLocal) != hipSuccess)
             return bail(fail(ctx, SPLIT_E_HIP, "split_graph_create: hipStreamBeginCapture failed"));
         capturing = true;
-        if (hipMemcpyAsync(gr->buf.d_stage, gr->h_stage[k], gr->layout.bytes,
-                           hipMemcpyHostToDevice, gr->cap_stream) != hipSuccess)
-            return bail(fail(ctx, SPLIT_E_HIP, "split_graph_create: capture of the upload failed"));
-        st = enqueue_kernels(ctx, gr->inst, gr->buf, gr->layout, gr->plan, demand, S, ld, Q, cost,
-                             ldc, gr->cap_stream, false);
+        st = enqueue_kernels(ctx, gr->inst, gr->buf, gr->layout, gr->h_stage[k], gr->h_stats[k],
+                             gr->plan, demand, S, ld, Q, cost, ldc, gr->cap_stream, false);
         if (st != SPLIT_OK) return bail(st);
-        if (hipMemcpyAsync(gr->h_stats[k], gr->buf.d_stats, sizeof(DevStats) * (size_t)max_T,
-                           hipMemcpyDeviceToHost, gr->cap_stream) != hipSuccess)
-            return bail(fail(ctx, SPLIT_E_HIP, "split_graph_create: capture of the copy failed"));
         hipGraph_t graph = nullptr;
         const hipError_t e = hipStreamEndCapture(gr->cap_stream, &graph);
         capturing = false;

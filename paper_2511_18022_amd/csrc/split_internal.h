@@ -34,19 +34,51 @@ constexpr int32_t kInf = 0x3fffffff;
 // Cost mark of a scenario the lane kernel leaves to the general kernel (costs are >= 0).
 constexpr int32_t kCostOvf = INT32_MIN;
 
-// Device-side result block of one tour (zeroed by the prep kernel of each call).
+// Device-side flags of one tour (zeroed by the prep kernel of each call).
 struct DevStats {
-    unsigned long long sum;    // sum of costs
-    unsigned long long sq_lo;  // sum of squared costs, low 64 bits
-    unsigned long long sq_hi;  // sum of squared costs, high 64 bits
-    int32_t err_demand;        // nonzero: some scenario has q > Q (or q < 0) on the tour
-    int32_t ovf_count;         // scenarios of this tour past the lane kernel's history
+    int32_t err_demand;  // nonzero: some scenario has q > Q (or q < 0) on the tour
+    int32_t ovf_count;   // scenarios of this tour past the lane kernel's history
+};
+
+// Sums of some of a tour's costs: of the costs, and of their squares' low and high 32 bits (each
+// below 2^63: a cost is below 2^30 and S below 2^31).
+struct __attribute__((aligned(32))) CostSums {
+    unsigned long long sum, sq_l32, sq_h32;
+};
+
+// Where the DP kernels leave them: slots entries per tour, `stride` bytes apart.
+//  by item   one entry per work item, stored by it. For several tours: a workgroup that ends on
+//            atomic additions holds its place until they are done, which made 256 tours over 65,536
+//            scenarios 1.7% slower (8,710 us against 8,560).
+//  added     kMaxSlots entries, zeroed by the prep kernel and added to by the scenario's block (or
+//            the scenario), each on a memory channel of its own: additions to one line, or to lines
+//            of one channel, follow each other at about 11 ns. For one tour, whose workgroups go
+//            on to their next item meanwhile, and for the other forms.
+struct SumSlots {
+    char *base;
+    int64_t slots;
+    int32_t stride;
+    int32_t by_item;
+};
+constexpr int32_t kMaxSlots = 64;
+constexpr int32_t kSlotStride = 256;
+__host__ __device__ inline CostSums *sums_at(const SumSlots &s, int64_t t, int64_t k)
+{
+    return reinterpret_cast<CostSums *>(s.base + (t * s.slots + k) * s.stride);
+}
+
+// What the tail kernel reports of one tour (pinned host memory, or device memory where the caller
+// copies it): sumsq = sq_l32 + 2^32 sq_h32.
+struct TourResult {
+    unsigned long long sum, sq_l32, sq_h32;
+    int32_t err_demand, ovf_count;
 };
 
 // Batch-wide counters (reset by the prep kernel of each call).
 struct BatchCtl {
     uint32_t head;       // next work item of the lane kernel's queue
     uint32_t ovf_total;  // nonzero: some scenario is marked kCostOvf
+    uint32_t done;       // tail kernel workgroups that have finished their items
 };
 
 // Per-tour arrays built on the device by the prep kernel from the tours and the instance.
@@ -70,14 +102,14 @@ __host__ __device__ inline int64_t tour_abase(const int64_t *tptr, int t)
     return tptr[t] + (int64_t)t * (1 + kRowPad);
 }
 
-// Staged header, uploaded before every evaluation: int64 T, int64 tptr[T + 1], int32 order[T]
-// (the lane kernel's work order), int32 tours[tptr[T]], each part at an offset fixed by the
-// capacity the buffers were laid out for.
+// Header of an evaluation: int64 T, int64 tptr[T + 1], int32 order[T] (the lane kernel's work
+// order), int32 tours[tptr[T]], each part at an offset fixed by the capacity the buffers were laid
+// out for. The prep kernel reads it where the host wrote it (pinned host memory, or device memory
+// that it was copied to) and leaves all but the tours in device memory for the other kernels.
 struct TourDev {
-    const int64_t *nt;     // [1] number of tours T of this evaluation
-    const int32_t *tours;  // [tptr[T]] concatenated tours
-    const int64_t *tptr;   // [T + 1]
-    const int32_t *order;  // [T] work order of the lane kernel
+    int64_t *nt;           // [1] number of tours T of this evaluation
+    int64_t *tptr;         // [T + 1]
+    int32_t *order;        // [T] work order of the lane kernel
     int32_t T_grid;        // upper bound of T that the launch grids are sized for
     int64_t *rowoff;       // concatenated, see above
     uint32_t *rowoff32;    // rowoff mod 2^32 (exact where it is used), kRowAbsent where absent
@@ -86,6 +118,11 @@ struct TourDev {
 
 struct PrepArgs {
     TourDev tour;
+    const int64_t *src_nt;     // the header as the host wrote it
+    const int64_t *src_tptr;
+    const int32_t *src_order;
+    const int32_t *src_tours;
+    SumSlots sums;
     int32_t N;
     int32_t kind;          // 0: coordinates, 1: distance matrix
     const int32_t *xy;     // device [(N+1)*2]
@@ -104,6 +141,8 @@ struct EvalArgs {
     int32_t *cost;           // device [T][ldc]
     int64_t ldc;
     DevStats *stats;         // [T]
+    SumSlots sums;
+    TourResult *out;         // [T] the tail kernel's report
     BatchCtl *ctl;
     uint32_t lane_bytes;     // lane kernel: bytes of demand it may address, <= kRowAbsent
     int32_t lane_grid;       // lane kernel workgroups (>= the work items: one item each)
@@ -111,35 +150,22 @@ struct EvalArgs {
                              // at a fixed stride of lane_grid, 0 = from the queue
     int32_t lane_uniform;    // lane kernel: 1 = every tour of the launch has the same length
     int32_t lane_block;      // lane kernel block length: 16 or 8 states, 0 by the windows
-    int32_t recount;         // 1: the long kernel counts the scenarios past the lane kernel's history
-    int32_t long_grid;       // long kernel workgroups (at most)
+    int32_t recount;         // 1: the tail kernel counts the scenarios past the lane kernel's history
+    int32_t tail_grid;       // tail kernel workgroups (at most)
     int32_t wave_grid;       // wave kernel workgroups of a full evaluation (form wave)
     int32_t maxn;            // bound on the tour lengths (sizes the wave kernel's LDS)
-};
-
-struct MomentArgs {
-    const int32_t *cost;           // [T][ldc]
-    int64_t ldc;
-    int64_t S;
-    const int64_t *nt;             // [1] T
-    int32_t T_grid;
-    unsigned long long *partials;  // [T][nblocks][3]
-    int32_t nblocks;               // per tour
-    DevStats *stats;               // [T]
 };
 
 // Kernel launchers (split_kernels.hip). All are asynchronous on `stream`.
 hipError_t launch_prep(const PrepArgs &a, hipStream_t stream);
 hipError_t launch_lane(const EvalArgs &a, hipStream_t stream);
 hipError_t launch_wave_all(const EvalArgs &a, hipStream_t stream);
-hipError_t launch_long(const EvalArgs &a, hipStream_t stream);
-hipError_t launch_moments(const MomentArgs &a, hipStream_t stream);
+hipError_t launch_tail(const EvalArgs &a, hipStream_t stream);
 // two-kernel form: mask int16 [rows][mask_ld], row abase(t) + i
 hipError_t launch_mask(const EvalArgs &a, int16_t *mask, long long mask_ld, hipStream_t stream);
 hipError_t launch_masked_dp(const EvalArgs &a, const int16_t *mask, long long mask_ld,
                             hipStream_t stream);
 const char *mask_kernel_name();
-int32_t moment_blocks(int64_t S);
 const char *lane_kernel_name();
 const char *wave_kernel_name();
 

@@ -15,14 +15,14 @@
 //                         the window minimum is answered in O(1) per state from block
 //                         suffix minima held in LDS; windows longer than its LDS history are
 //                         left to the long kernel.
-//  split_long_kernel      the lane kernel's blocks over a history of 256 positions, for tours
+//  split_tail_kernel      reports the sums; first the lane kernel's blocks over a history of 256 positions, for tours
 //                         whose windows outgrow the lane kernel's 64 and for the scenarios it
 //                         marks; what outgrows this history too is finished one scenario per
 //                         wavefront.
 //  split_wave_kernel      one scenario per wavefront; lanes cover the window's predecessors
 //                         (transition-level parallelism of Section 3) and the minimum is a
 //                         DPP reduction. Exact for any window length; used for small S.
-//  split_moments_*        exact 128-bit sum and sum of squares of the costs.
+// The DP kernels also add up the costs and their squares, exactly; the tail kernel reports them.
 #include "split_internal.h"
 
 #include <limits.h>
@@ -62,10 +62,14 @@ __global__ __launch_bounds__(1024) void split_prep_kernel(PrepArgs a)
     __shared__ int32_t ends[2];  // c(0, first customer), c(last customer, 0)
     const int tid = threadIdx.x;
     const int t = blockIdx.x;
-    if (t >= *a.tour.nt) return;
-    const int32_t *tour = a.tour.tours + a.tour.tptr[t];
-    const int n = (int)(a.tour.tptr[t + 1] - a.tour.tptr[t]);
-    const int64_t ab = tour_abase(a.tour.tptr, t);
+    // the header may lie in host memory: one round trip for these four, one for the tour
+    const int64_t T = *a.src_nt, p0 = a.src_tptr[t], p1 = a.src_tptr[t + 1];
+    const int32_t ord = a.src_order[t];
+    if (t >= T) return;
+    const int32_t *tour = a.src_tours + p0;
+    const int n = (int)(p1 - p0);
+    const int64_t ab = p0 + (int64_t)t * (1 + kRowPad);
+    if (!a.sums.by_item && tid < kMaxSlots) *sums_at(a.sums, t, tid) = CostSums{0, 0, 0};
     int64_t *rowoff = a.tour.rowoff + ab;
     uint32_t *rowoff32 = a.tour.rowoff32 + ab;
     int32_t *w = a.tour.w + ab;
@@ -104,16 +108,62 @@ __global__ __launch_bounds__(1024) void split_prep_kernel(PrepArgs a)
         rowoff32[0] = kRowAbsent;
         w[0] = ends[0];
         w[n] = (int32_t)(red[0] + ends[1]);
-        DevStats *st = a.stats + t;
-        st->sum = 0;
-        st->sq_lo = 0;
-        st->sq_hi = 0;
-        st->err_demand = 0;
-        st->ovf_count = 0;
+        a.stats[t] = DevStats{0, 0};
+        a.tour.tptr[t] = p0;
+        a.tour.order[t] = ord;
+        if (t == T - 1) a.tour.tptr[T] = p1;
         if (t == 0) {
-            a.ctl->head = 0;
-            a.ctl->ovf_total = 0;
+            *a.tour.nt = T;
+            *a.ctl = BatchCtl{0, 0, 0};
         }
+    }
+}
+
+// ------------------------------------------------------------------------- sums of the costs
+
+// Sum over the 64 lanes of a wavefront, in lane 63 (DPP row shifts and row broadcasts).
+__device__ __forceinline__ uint32_t wave_sum_last(uint32_t v)
+{
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);  // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);  // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);  // row_shr:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return v;
+}
+
+// The sums of the 64 lanes' costs (each below 2^30; 0 where a lane has none) and their squares,
+// in lane 63: 16-bit parts, whose sums over the lanes fit 32 bits.
+__device__ __forceinline__ CostSums wave_costs(uint32_t c)
+{
+    const unsigned long long q = (unsigned long long)c * c;
+    const uint32_t c0 = wave_sum_last(c & 0xFFFFu), c1 = wave_sum_last(c >> 16);
+    const uint32_t q0 = wave_sum_last((uint32_t)q & 0xFFFFu);
+    const uint32_t q1 = wave_sum_last((uint32_t)q >> 16);
+    const uint32_t q2 = wave_sum_last((uint32_t)(q >> 32) & 0xFFFFu);
+    const uint32_t q3 = wave_sum_last((uint32_t)(q >> 48));
+    return CostSums{c0 + ((unsigned long long)c1 << 16), q0 + ((unsigned long long)q1 << 16),
+                    q2 + ((unsigned long long)q3 << 16)};
+}
+
+__device__ __forceinline__ void add_sums(CostSums *to, const CostSums &v)
+{
+    atomicAdd(&to->sum, v.sum);
+    atomicAdd(&to->sq_l32, v.sq_l32);
+    atomicAdd(&to->sq_h32, v.sq_h32);
+}
+
+// Leaves the costs of work item (t, sb) in its slot. Two launches over the cost matrix did this
+// before: 10 us of a call at 10^5 scenarios, 24 us of 256 tours over 65,536.
+__device__ __forceinline__ void item_costs(const SumSlots &s, int t, long long sb, uint32_t c)
+{
+    const CostSums v = wave_costs(c);
+    if ((threadIdx.x & 63) == 63) {
+        if (s.by_item)
+            *sums_at(s, t, sb) = v;
+        else
+            add_sums(sums_at(s, t, sb & (kMaxSlots - 1)), v);
     }
 }
 
@@ -814,34 +864,34 @@ __device__ __forceinline__ void lane_run(LaneLds<H> &L, const LaneTour &tr, int 
 
 // The end of a work item: the costs of the scenarios that are done; the others are marked for the
 // long kernel, which also counts them under `recount`.
-template <int LB>
-__device__ __forceinline__ void lane_finish(const EvalArgs &a, int t, long long scen,
-                                            const LaneState<LB, 64> &st, bool recount)
+__device__ __forceinline__ void lane_finish(const EvalArgs &a, int t, long long scen, bool ovf,
+                                            bool err, int gres, bool recount)
 {
     __builtin_amdgcn_s_setprio(0);
     const bool active = scen < a.S;
-    const bool left = active && st.ovf != 0;
-    if (active && (left || !st.err))
-        a.cost[(long long)t * a.ldc + scen] = left ? kCostOvf : st.gres;
+    const bool left = active && ovf;
+    if (active && (left || !err))
+        a.cost[(long long)t * a.ldc + scen] = left ? kCostOvf : gres;
+    item_costs(a.sums, t, scen >> 6, active && !left && !err ? (uint32_t)gres : 0u);
     const unsigned long long m = __ballot(left);
     if (m != 0 && threadIdx.x == 0) {
         a.ctl->ovf_total = 1;  // whoever writes it, the same value
         if (!recount) atomicAdd(&a.stats[t].ovf_count, (int)__popcll(m));
     }
-    if (active && !left && st.err) atomicOr(&a.stats[t].err_demand, 1);
+    if (active && !left && err) atomicOr(&a.stats[t].err_demand, 1);
 }
 
 // The windows of a work item, from the demands of its first positions (loaded anyway):
 //  kWindowsLong   under half of the scenarios or more, the first 15 customers fill at most 15 / 40 of
 //                 the capacity: some window will outgrow 47 positions;
-//  kWindowsShort  under every lane, its first route holds at most 18 customers and routes over its
-//                 first 47 positions 15.5 on average: a 16-state block would mostly see windows
-//                 that start inside it. A lane whose first 15 customers fill at most 15 / 22 of
-//                 the capacity decides against it from block 0 alone, before blocks 1 and 2
-//                 have arrived.
-// Windows of up to 13 (demands with a coefficient of variation of 0.5; 14 at 0.25) keep their tails
-// within the 23 positions of 8-state blocks; at 14.6 a few in 10^5 pass them, and redoing their
-// items made a call of 849 scenarios 121 us instead of 93.
+//  kWindowsShort  the mean window W over the first 47 positions plus 4.6 times its spread (from the
+//                 spread of those 47 customers' load over the scenarios) stays within 22, and under
+//                 every scenario the first route holds at most 18 customers: 8-state blocks keep
+//                 windows of up to 23, and a 16-state block would mostly see windows that start
+//                 inside it. A lane whose first 15 customers fill at most 15 / 22 of the capacity
+//                 decides against it from block 0 alone, before blocks 1 and 2 have arrived.
+// Windows of 14.6 under uniform demands (a coefficient of variation of 0.55) pass 23 a few times in
+// 10^5, and redoing their items made a call of 849 scenarios 121 us instead of 93.
 // The class only chooses a kernel: what outgrows its history all the same is redone by the long one.
 // Measured, whole calls: 200 customers, windows of 13, S = 10^5: 83 us (90 in blocks of 16);
 // 701 customers, windows of 60, S = 20,011: 181 us (14,760 with blocks of 16 first and the rest one
@@ -870,7 +920,18 @@ __device__ __forceinline__ int window_class(const uint16_t (&qA)[16], const uint
     count(qA);
     count(qB);
     count(qC);
-    return __any(len > 19 || 31 * load < 2 * min(n, 47) * Q) ? kWindowsMid : kWindowsShort;
+    if (__any(len > 19)) return kWindowsMid;
+    float s1 = (float)load, s2 = s1 * s1;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        s1 += __shfl_xor(s1, off, 64);
+        s2 += __shfl_xor(s2, off, 64);
+    }
+    const float k = (float)min(n, 47), m = s1 / 64.f;
+    const float W = k * (float)Q / m;
+    const float var = fmaxf(s2 / 64.f - m * m, 0.f) / (m * m) * k * W;
+    const float room = 22.f - W;
+    return __any(!(room > 0.f && 4.6f * 4.6f * var <= room * room)) ? kWindowsMid : kWindowsShort;
 }
 
 // One work item: the 64 scenarios sb*64 .. sb*64+63 of tour t. LB = 0: blocks of 8 or 16 states, or
@@ -890,37 +951,37 @@ __device__ __forceinline__ void lane_item(LaneLds<64> &L, const EvalArgs &a, int
         lane_load_block<8>(rsrc, tr.rowoff, lane_off, 2, qC);
         LaneState<8, 64> st;
         lane_run<8, 64>(L, tr, a.Q, rsrc, lane_off, qA, qB, qC, prio, st);
-        lane_finish<8>(a, t, scen, st, false);
+        lane_finish(a, t, scen, st.ovf != 0, st.err, st.gres, false);
     } else {
         uint16_t qA[16], qB[16], qC[16];
         lane_load_block<16>(rsrc, tr.rowoff, lane_off, 0, qA);
         lane_load_block<16>(rsrc, tr.rowoff, lane_off, 1, qB);
         lane_load_block<16>(rsrc, tr.rowoff, lane_off, 2, qC);
-        LaneState<16, 64> st;
-        if constexpr (LB == 0) {
-            const int cls = window_class(qA, qB, qC, tr.n, a.Q, scen < a.S);
-            if (cls == kWindowsShort) {
-                uint16_t rA[8], rB[8], rC[8];
+        int cls = kWindowsMid;
+        if constexpr (LB == 0) cls = window_class(qA, qB, qC, tr.n, a.Q, scen < a.S);
+        int ovf = 1, gres = 0;
+        bool err = false;
+        if (__builtin_expect(cls == kWindowsMid, 1)) {
+            LaneState<16, 64> st;
+            lane_run<16, 64>(L, tr, a.Q, rsrc, lane_off, qA, qB, qC, prio, st);
+            ovf = st.ovf;
+            err = st.err;
+            gres = st.gres;
+        } else if (cls == kWindowsShort) {
+            uint16_t rA[8], rB[8], rC[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    rA[j] = qA[j];
-                    rB[j] = qA[8 + j];
-                    rC[j] = qB[j];
-                }
-                LaneState<8, 64> st8;
-                lane_run<8, 64>(L, tr, a.Q, rsrc, lane_off, rA, rB, rC, prio, st8);
-                lane_finish<8>(a, t, scen, st8, true);
-                return;
+            for (int j = 0; j < 8; ++j) {
+                rA[j] = qA[j];
+                rB[j] = qA[8 + j];
+                rC[j] = qB[j];
             }
-            if (cls == kWindowsLong) {
-                st.ovf = 1;
-                st.err = false;
-                lane_finish<16>(a, t, scen, st, true);
-                return;
-            }
+            LaneState<8, 64> st;
+            lane_run<8, 64>(L, tr, a.Q, rsrc, lane_off, rA, rB, rC, prio, st);
+            ovf = st.ovf;
+            err = st.err;
+            gres = st.gres;
         }
-        lane_run<16, 64>(L, tr, a.Q, rsrc, lane_off, qA, qB, qC, prio, st);
-        lane_finish<16>(a, t, scen, st, true);
+        lane_finish(a, t, scen, ovf != 0, err, gres, true);
     }
 }
 
@@ -988,7 +1049,8 @@ __device__ __forceinline__ int wave_exclusive_sum(int v)
 // lanes loading demands in parallel (chunk per lane + wavefront scan). Then, state by state,
 // every lane runs the same two-pointer on the same data (uniform control flow), lane j reads
 // g of predecessor s + j (+ 64k for long windows) and the wavefront reduces them.
-__device__ void wave_one(const EvalArgs &a, int t, long long scen, int32_t *G, int32_t *PP)
+// Returns the scenario's cost, or 0 where a demand is infeasible (flagged).
+__device__ uint32_t wave_one(const EvalArgs &a, int t, long long scen, int32_t *G, int32_t *PP)
 {
     const int lane = threadIdx.x;
     const int64_t ab = tour_abase(a.tour.tptr, t);
@@ -1035,13 +1097,15 @@ __device__ void wave_one(const EvalArgs &a, int t, long long scen, int32_t *G, i
         }
         G[i] = wave_min(mn) + w[i];
     }
+    const int32_t cost = err ? 0 : G[n];
     if (lane == 0) {
         if (err)
             atomicOr(&a.stats[t].err_demand, 1);
         else
-            a.cost[(long long)t * a.ldc + scen] = G[n];
+            a.cost[(long long)t * a.ldc + scen] = cost;
     }
     __syncthreads();
+    return (uint32_t)cost;
 }
 
 // Every (tour, scenario) pair, k = t * S + s over k = blockIdx.x, blockIdx.x + gridDim.x, ...
@@ -1053,11 +1117,42 @@ __global__ __launch_bounds__(64) void split_wave_kernel(EvalArgs a)
     const long long T = *a.tour.nt;
     for (long long k = blockIdx.x; k < T * a.S; k += gridDim.x) {
         const int t = (int)(k / a.S);
-        wave_one(a, t, k - (long long)t * a.S, G, PP);
+        const long long scen = k - (long long)t * a.S;
+        const uint32_t c = wave_one(a, t, scen, G, PP);
+        if (threadIdx.x == 0) {
+            const unsigned long long q = (unsigned long long)c * c;
+            add_sums(sums_at(a.sums, t, scen & (kMaxSlots - 1)),
+                     CostSums{c, q & 0xFFFFFFFFull, q >> 32});
+        }
     }
 }
 
-// ------------------------------------------------------------------------- long kernel
+// ------------------------------------------------------------------------- tail kernel
+
+// Tour t's result from its slots, by one wavefront. The slots were added to at the device's scope,
+// by earlier launches or (once every workgroup is counted in) by this one: read there too.
+__device__ __forceinline__ void report_tour(const EvalArgs &a, int t)
+{
+    const int lane = threadIdx.x;
+    auto load = [](const auto *p) {
+        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    unsigned long long v[3] = {0, 0, 0};
+#pragma unroll 8
+    for (long long k = lane; k < a.sums.slots; k += 64) {
+        const CostSums *s = sums_at(a.sums, t, k);
+        v[0] += load(&s->sum);
+        v[1] += load(&s->sq_l32);
+        v[2] += load(&s->sq_h32);
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) v[j] += __shfl_xor(v[j], off, 64);
+    }
+    if (lane == 0)
+        a.out[t] = TourResult{v[0], v[1], v[2], load(&a.stats[t].err_demand),
+                              load(&a.stats[t].ovf_count)};
+}
 
 // The scenarios marked kCostOvf, 64 at a time with the lane kernel's blocks of 16 over a history of
 // 256 positions (windows of up to 239). Scenarios that outgrow this history too, or whose suffix
@@ -1067,55 +1162,79 @@ __global__ __launch_bounds__(64) void split_wave_kernel(EvalArgs a)
 //
 // Bound by the latency of one wavefront's serial chain: 75.5 KB of LDS leave two wavefronts a
 // compute unit, one on every other SIMD. That is still one state of 64 scenarios per step, where
-// one scenario per wavefront leaves most lanes idle: 701 customers, windows of 60,
+// one scenario per wavefront leaves most lanes idle: 701 customers, windows of about 60,
 // S = 20,011 took 14.76 ms as a call; with this kernel 0.18 ms, 0.12 of them here.
 // Counts go to memory once per item: one atomic per scenario took 240 us of this launch there.
-// When nothing is marked it only reads the flag.
-__global__ __launch_bounds__(64) void split_long_kernel(EvalArgs a)
+//
+// Then the tours' results, straight to the caller's (pinned host) memory. Where nothing was marked,
+// each workgroup reports its share at once; otherwise the last workgroup to finish reports all.
+__global__ __launch_bounds__(64) void split_tail_kernel(EvalArgs a)
 {
     __shared__ LaneLds<256> L;
     static_assert(sizeof(L) >= 2 * sizeof(int32_t) * (SPLIT_MAX_N + 1),
                   "the wavefront's prefix loads and g values of a maximal tour fit");
-    if (*(cu32 *)&a.ctl->ovf_total == 0) return;
     const int lane = threadIdx.x;
     const long long T = *(ci64 *)a.tour.nt;
+    if (*(cu32 *)&a.ctl->ovf_total == 0) {
+        for (int t = blockIdx.x; t < T; t += gridDim.x) report_tour(a, t);
+        return;
+    }
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void *)a.demand, (short)0, (int)a.lane_bytes, 0x00020000);
     const long long nsb = (a.S + 63) / 64;
     for (long long k = blockIdx.x; k < T * nsb; k += gridDim.x) {
         const int t = (int)(k / nsb);
-        const long long s0 = (k - (long long)t * nsb) * 64;
+        const long long sb = k - (long long)t * nsb, s0 = sb * 64;
         const bool active = s0 + lane < a.S;
         const long long scen = active ? s0 + lane : a.S - 1;
         int32_t *cost = a.cost + (long long)t * a.ldc;
         const bool todo = active && cost[scen] == kCostOvf;
         if (!__any(todo)) continue;
-        const LaneTour tr = lane_tour(a, t);
-        const uint32_t lane_off = (uint32_t)scen * 2u;
-        uint16_t qA[16], qB[16], qC[16];
-        lane_load_block<16>(rsrc, tr.rowoff, lane_off, 0, qA);
-        lane_load_block<16>(rsrc, tr.rowoff, lane_off, 1, qB);
-        lane_load_block<16>(rsrc, tr.rowoff, lane_off, 2, qC);
         LaneState<16, 256> st;
-        lane_run<16, 256>(L, tr, a.Q, rsrc, lane_off, qA, qB, qC, false, st);
+        st.ovf = 1;
+        st.past = false;
+        st.err = false;
+        st.gres = 0;
+        if (a.lane_bytes != 0) {  // the demands lie within a buffer descriptor's reach
+            const LaneTour tr = lane_tour(a, t);
+            const uint32_t lane_off = (uint32_t)scen * 2u;
+            uint16_t qA[16], qB[16], qC[16];
+            lane_load_block<16>(rsrc, tr.rowoff, lane_off, 0, qA);
+            lane_load_block<16>(rsrc, tr.rowoff, lane_off, 1, qB);
+            lane_load_block<16>(rsrc, tr.rowoff, lane_off, 2, qC);
+            lane_run<16, 256>(L, tr, a.Q, rsrc, lane_off, qA, qB, qC, false, st);
+        }
         if (a.recount) {
             const int past = (int)__popcll(__ballot(todo && (st.past || st.ovf)));
             if (lane == 0 && past) atomicAdd(&a.stats[t].ovf_count, past);
         }
+        uint32_t mine = 0;
         if (todo && st.ovf == 0) {
-            if (st.err)
+            if (st.err) {
                 atomicOr(&a.stats[t].err_demand, 1);
-            else
+            } else {
+                mine = (uint32_t)st.gres;
                 cost[scen] = st.gres;
+            }
         }
         unsigned long long m = __ballot(todo && st.ovf);
         int32_t *G = reinterpret_cast<int32_t *>(&L);
         while (m) {
             const int j = __builtin_ctzll(m);
             m &= m - 1;
-            wave_one(a, t, s0 + j, G, G + SPLIT_MAX_N + 1);
+            const uint32_t c = wave_one(a, t, s0 + j, G, G + SPLIT_MAX_N + 1);
+            if (lane == j) mine = c;
         }
+        const CostSums v = wave_costs(mine);
+        if (lane == 63)
+            add_sums(sums_at(a.sums, t, a.sums.by_item ? sb : sb & (kMaxSlots - 1)), v);
     }
+    __threadfence();
+    uint32_t before = 0;
+    if (lane == 0) before = atomicAdd(&a.ctl->done, 1u);
+    if (__builtin_amdgcn_readfirstlane(before) != gridDim.x - 1) return;
+    __threadfence();
+    for (int t = 0; t < T; ++t) report_tour(a, t);
 }
 
 // ------------------------------------------------------------------------- two-kernel form
@@ -1192,11 +1311,12 @@ __global__ __launch_bounds__(64) void split_masked_dp_kernel(EvalArgs a, const i
         g = w[i] + m;
         ring[i & 63][lane] = g;
     }
+    item_costs(a.sums, t, scen_raw >> 6, active && !ovf && !err ? (uint32_t)g : 0u);
     if (!active) return;
     if (ovf) {
         a.cost[(long long)t * a.ldc + scen] = kCostOvf;
         atomicAdd(&a.stats[t].ovf_count, 1);
-        atomicAdd(&a.ctl->ovf_total, 1u);
+        a.ctl->ovf_total = 1;
     } else if (err) {
         atomicOr(&a.stats[t].err_demand, 1);
     } else {
@@ -1204,86 +1324,11 @@ __global__ __launch_bounds__(64) void split_masked_dp_kernel(EvalArgs a, const i
     }
 }
 
-// ------------------------------------------------------------------------- moments
-
-__device__ __forceinline__ void add128(unsigned long long &lo, unsigned long long &hi,
-                                       unsigned long long xlo, unsigned long long xhi)
-{
-    const unsigned long long t = lo + xlo;
-    hi += xhi + (t < lo ? 1ull : 0ull);
-    lo = t;
-}
-
-__device__ void block_reduce3(unsigned long long &s, unsigned long long &lo,
-                              unsigned long long &hi)
-{
-    __shared__ unsigned long long rs[256], rl[256], rh[256];
-    const int t = threadIdx.x;
-    rs[t] = s;
-    rl[t] = lo;
-    rh[t] = hi;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (t < off) {
-            rs[t] += rs[t + off];
-            unsigned long long l = rl[t], h = rh[t];
-            add128(l, h, rl[t + off], rh[t + off]);
-            rl[t] = l;
-            rh[t] = h;
-        }
-        __syncthreads();
-    }
-    s = rs[0];
-    lo = rl[0];
-    hi = rh[0];
-}
-
-// grid (nblocks, T_grid): workgroup (b, t) sums a strided share of tour t's costs
-__global__ __launch_bounds__(256) void split_moments_partial(MomentArgs a)
-{
-    const int t = blockIdx.y;
-    if (t >= *a.nt) return;
-    const int32_t *cost = a.cost + (long long)t * a.ldc;
-    unsigned long long s = 0, lo = 0, hi = 0;
-    for (long long k = (long long)blockIdx.x * 256 + threadIdx.x; k < a.S;
-         k += (long long)gridDim.x * 256) {
-        const unsigned long long c = (unsigned int)cost[k];
-        s += c;
-        add128(lo, hi, c * c, 0);
-    }
-    block_reduce3(s, lo, hi);
-    if (threadIdx.x == 0) {
-        unsigned long long *p = a.partials + 3 * ((long long)t * a.nblocks + blockIdx.x);
-        p[0] = s;
-        p[1] = lo;
-        p[2] = hi;
-    }
-}
-
-// grid T_grid: workgroup t combines the partials of tour t
-__global__ __launch_bounds__(256) void split_moments_final(MomentArgs a)
-{
-    const int t = blockIdx.x;
-    if (t >= *a.nt) return;
-    const unsigned long long *p = a.partials + 3 * (long long)t * a.nblocks;
-    unsigned long long s = 0, lo = 0, hi = 0;
-    for (int b = threadIdx.x; b < a.nblocks; b += 256) {
-        s += p[3 * b + 0];
-        add128(lo, hi, p[3 * b + 1], p[3 * b + 2]);
-    }
-    block_reduce3(s, lo, hi);
-    if (threadIdx.x == 0) {
-        a.stats[t].sum = s;
-        a.stats[t].sq_lo = lo;
-        a.stats[t].sq_hi = hi;
-    }
-}
-
 // ------------------------------------------------------------------------- scratch
 
 // Fixed device scratch of the allocation-free evaluation (split_eval_noalloc): every per-call
 // device buffer of a one-tour evaluation (staged tour, per-position arrays, result block,
-// counters, moment partials) is carved from it. Each GPU holds its own copy for the life of the
+// counters, cost sums) is carved from it. Each GPU holds its own copy for the life of the
 // process; its device address is looked up once per device, with that device current.
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -1351,11 +1396,11 @@ hipError_t launch_wave_all(const EvalArgs &a, hipStream_t stream)
     return hipGetLastError();
 }
 
-hipError_t launch_long(const EvalArgs &a, hipStream_t stream)
+hipError_t launch_tail(const EvalArgs &a, hipStream_t stream)
 {
     const long long work = (a.S + 63) / 64 * a.tour.T_grid;
-    const long long nb = work < a.long_grid ? work : a.long_grid;
-    hipLaunchKernelGGL(split_long_kernel, dim3((unsigned)nb), dim3(64), 0, stream, a);
+    const long long nb = work < a.tail_grid ? work : a.tail_grid;
+    hipLaunchKernelGGL(split_tail_kernel, dim3((unsigned)nb), dim3(64), 0, stream, a);
     return hipGetLastError();
 }
 
@@ -1377,23 +1422,6 @@ hipError_t launch_masked_dp(const EvalArgs &a, const int16_t *mask, long long ma
 }
 
 const char *mask_kernel_name() { return "split_mask_kernel+split_masked_dp_kernel"; }
-
-int32_t moment_blocks(int64_t S)
-{
-    long long b = (S + 2047) / 2048;
-    if (b < 1) b = 1;
-    if (b > 1024) b = 1024;
-    return (int32_t)b;
-}
-
-hipError_t launch_moments(const MomentArgs &a, hipStream_t stream)
-{
-    hipLaunchKernelGGL(split_moments_partial, dim3(a.nblocks, a.T_grid), dim3(256), 0, stream, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(split_moments_final, dim3(a.T_grid), dim3(256), 0, stream, a);
-    return hipGetLastError();
-}
 
 const char *lane_kernel_name() { return "split_lane_kernel"; }
 const char *wave_kernel_name() { return "split_wave_kernel"; }
