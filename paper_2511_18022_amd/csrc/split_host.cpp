@@ -41,6 +41,9 @@ constexpr int32_t kMaxLanePerCu = 8;    // the lane kernel's LDS allows 8 workgr
 constexpr int32_t kLaneStaticPerCu = kMaxLanePerCu;  // fixed-stride grid: all resident at once
 constexpr int64_t kLaneStaticMaxRounds = 16;         // and at most this many items each
 constexpr int32_t kTailPerCu = 2;       // the tail kernel's LDS allows 2 workgroups per CU
+constexpr int32_t kPairPerCu = 4;       // as many of the pair kernel's: two wavefronts a SIMD
+constexpr int32_t kPairMinN = 320;
+constexpr int32_t kPairMaxQ = 2047;     // a demand of Q itself stays within the 16-bit bound
 constexpr int64_t kClassMaxArc = 2047;  // 16 states times 2 max_arc: below 2^16
 
 // Device buffers of one evaluation sequence. The context's grow with its calls; a graph owns
@@ -51,6 +54,9 @@ struct EvalBuffers {
     int64_t *d_rowoff = nullptr;
     uint32_t *d_rowoff32 = nullptr;
     int32_t *d_w = nullptr;
+    uint32_t *d_rowoff32_back = nullptr;  // pair kernel only, as the two after it
+    int32_t *d_w_back = nullptr;
+    int64_t cap_back = 0;
     int64_t cap_pos = 0;      // entries of the per-tour arrays
     DevStats *d_stats = nullptr;
     int32_t cap_T = 0;
@@ -67,6 +73,8 @@ void free_buffers(EvalBuffers &b)
     if (b.d_rowoff) (void)hipFree(b.d_rowoff);
     if (b.d_rowoff32) (void)hipFree(b.d_rowoff32);
     if (b.d_w) (void)hipFree(b.d_w);
+    if (b.d_rowoff32_back) (void)hipFree(b.d_rowoff32_back);
+    if (b.d_w_back) (void)hipFree(b.d_w_back);
     if (b.d_stats) (void)hipFree(b.d_stats);
     if (b.d_sums) (void)hipFree(b.d_sums);
     if (b.d_ctl) (void)hipFree(b.d_ctl);
@@ -102,7 +110,7 @@ struct Plan {
     int form = SPLIT_FORM_LANE;
     int32_t lane_grid = 0, wave_grid = 0, maxn = 0, lane_block = 16;
     int32_t tail_grid = 0;
-    bool lane_static = false, lane_uniform = false;
+    bool lane_static = false, lane_uniform = false, pair = false;
     uint32_t lane_bytes = 0;
 };
 
@@ -239,13 +247,14 @@ bool grow(P **ptr, size_t bytes)
 // of cost sums (exact sizes, or with room to grow). Growing waits for
 // enqueued work before replacing a buffer.
 split_status ensure_buffers(split_ctx *ctx, EvalBuffers &b, int32_t T, int64_t total_n,
-                            int64_t stage_bytes, int64_t sum_bytes, bool exact)
+                            int64_t stage_bytes, int64_t sum_bytes, bool pair, bool exact)
 {
     const int64_t pos = total_n + (int64_t)T * (1 + kRowPad);
     const bool g_pos = pos > b.cap_pos, g_stage = stage_bytes > b.cap_stage;
     const bool g_T = T > b.cap_T, g_sums = sum_bytes > b.cap_sums;
     const bool g_ctl = b.d_ctl == nullptr;
-    if (!g_pos && !g_stage && !g_T && !g_sums && !g_ctl) return SPLIT_OK;
+    const bool g_back = pair && pos > b.cap_back;
+    if (!g_pos && !g_stage && !g_T && !g_sums && !g_ctl && !g_back) return SPLIT_OK;
     HIP_TRY(ctx, hipDeviceSynchronize());
     auto room = [exact](int64_t need, int64_t floor) {
         return exact ? need : (need < floor ? floor : need + need / 4);
@@ -258,6 +267,15 @@ split_status ensure_buffers(split_ctx *ctx, EvalBuffers &b, int32_t T, int64_t t
             return fail(ctx, SPLIT_E_NOMEM, "device allocation for %lld tour positions failed",
                         (long long)np);
         b.cap_pos = np;
+    }
+    if (g_back) {
+        const int64_t np = room(pos, 4096);
+        b.cap_back = 0;
+        if (!grow(&b.d_rowoff32_back, sizeof(uint32_t) * np) ||
+            !grow(&b.d_w_back, sizeof(int32_t) * np))
+            return fail(ctx, SPLIT_E_NOMEM, "device allocation for %lld tour positions failed",
+                        (long long)np);
+        b.cap_back = np;
     }
     if (g_stage) {
         const int64_t nb = room(stage_bytes, 65536);
@@ -506,6 +524,12 @@ Plan make_plan(const split_ctx *ctx, const split_tuning &tu, int64_t S, int64_t 
     const bool by_class = tu.lane_block == 0 && max_arc <= kClassMaxArc;
     p.lane_block = by_class ? 0 : tu.lane_block == 8 ? 8 : 16;
     p.tail_grid = ctx->cus * kTailPerCu;
+    // Two wavefronts per item where they all run at once, at most two on a SIMD: more items than
+    // that keep the chip busy with one each. The join takes what half of a tour of fewer than about
+    // 300 positions saves (64 items: 31 us against 25 at 128 positions, 39 against 37 at 256, 48
+    // against 62 at 512, 71 against 108 at 1000).
+    p.pair = p.form == SPLIT_FORM_LANE && lib_choice && p.lane_block != 8 && maxn >= kPairMinN &&
+             max_arc <= kClassMaxArc && Q <= kPairMaxQ && items <= (int64_t)ctx->cus * kPairPerCu;
     p.wave_grid = tu.wave_grid > 0 ? tu.wave_grid : 65536;
     p.maxn = maxn;
     return p;
@@ -528,6 +552,8 @@ split_status enqueue_kernels(split_ctx *ctx, const Instance &in, const EvalBuffe
     td.rowoff = b.d_rowoff;
     td.rowoff32 = b.d_rowoff32;
     td.w = b.d_w;
+    td.rowoff32_back = b.d_rowoff32_back;
+    td.w_back = b.d_w_back;
 
     PrepArgs pa;
     pa.tour = td;
@@ -537,6 +563,7 @@ split_status enqueue_kernels(split_ctx *ctx, const Instance &in, const EvalBuffe
     pa.src_tours = reinterpret_cast<const int32_t *>(src + L.off_tours);
     pa.sums = sum_slots(p.form, L.capT, S);
     pa.sums.base = b.d_sums;
+    pa.pair = p.pair ? 1 : 0;
     pa.N = in.N;
     pa.kind = in.kind;
     pa.xy = in.d_xy;
@@ -584,7 +611,7 @@ split_status enqueue_kernels(split_ctx *ctx, const Instance &in, const EvalBuffe
         if (stop) HIP_TRY(ctx, hipEventRecord(stop, stream));
     } else {
         ctx->tname = lane_kernel_name();
-        HIP_TRY(ctx, launch_lane(ea, stream));
+        HIP_TRY(ctx, p.pair ? launch_pair(ea, stream) : launch_lane(ea, stream));
         if (stop) HIP_TRY(ctx, hipEventRecord(stop, stream));
     }
     HIP_TRY(ctx, launch_tail(ea, stream));
@@ -612,7 +639,7 @@ split_status eval_batch(split_ctx *ctx, const char *who, const int32_t *tours,
     // on the device the header ends before the tours
     const SumSlots ss = sum_slots(p.form, T, S);
     st = ensure_buffers(ctx, ctx->buf, T, bi.total_n, (int64_t)L.off_tours,
-                        ss.slots * ss.stride * T, false);
+                        ss.slots * ss.stride * T, p.pair, false);
     if (st != SPLIT_OK) return st;
     st = ensure_host(ctx, (int64_t)L.bytes, T);
     if (st != SPLIT_OK) return st;
@@ -897,8 +924,8 @@ split_status split_eval_noalloc(split_ctx *ctx, const int32_t *tour, int32_t n,
                                 hipMemcpyHostToDevice, stream));
     HIP_TRY(ctx, hipMemcpyAsync(b.d_stage + L.off_tours, tour, sizeof(int32_t) * (size_t)n,
                                 hipMemcpyHostToDevice, stream));
-    const Plan p = make_plan(ctx, tu, S, ld, Q, 1, bi.maxn, bi.max_id, true,
-                             ctx->inst.max_arc);
+    Plan p = make_plan(ctx, tu, S, ld, Q, 1, bi.maxn, bi.max_id, true, ctx->inst.max_arc);
+    p.pair = false;  // the scratch does not hold the mirrored arrays of a maximal tour
     // the prep kernel zeroes the sums and the counters of every call
     st = enqueue_kernels(ctx, ctx->inst, b, L, b.d_stage, d_out, p, demand, S, ld, Q, cost, S,
                          stream, false);
@@ -1259,7 +1286,7 @@ split_status split_graph_create(split_ctx *ctx, int32_t max_T, int64_t max_total
                          gr->inst.max_arc);
     const SumSlots ss = sum_slots(gr->plan.form, max_T, S);
     st = ensure_buffers(ctx, gr->buf, max_T, max_total_n, (int64_t)gr->layout.off_tours,
-                        ss.slots * ss.stride * max_T, true);
+                        ss.slots * ss.stride * max_T, gr->plan.pair, true);
     if (st != SPLIT_OK) return bail(st);
     if (gr->plan.form == SPLIT_FORM_MASK)
         return bail(fail(ctx, SPLIT_E_INVAL, "split_graph_create: the two-kernel form is an "

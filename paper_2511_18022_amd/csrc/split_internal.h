@@ -114,6 +114,8 @@ struct TourDev {
     int64_t *rowoff;       // concatenated, see above
     uint32_t *rowoff32;    // rowoff mod 2^32 (exact where it is used), kRowAbsent where absent
     int32_t *w;
+    uint32_t *rowoff32_back;  // the pair kernel's mirrored half, indexed like rowoff32 and w
+    int32_t *w_back;
 };
 
 struct PrepArgs {
@@ -123,6 +125,7 @@ struct PrepArgs {
     const int32_t *src_order;
     const int32_t *src_tours;
     SumSlots sums;
+    int32_t pair;              // 1: also the arrays of the mirrored half
     int32_t N;
     int32_t kind;          // 0: coordinates, 1: distance matrix
     const int32_t *xy;     // device [(N+1)*2]
@@ -159,6 +162,7 @@ struct EvalArgs {
 // Kernel launchers (split_kernels.hip). All are asynchronous on `stream`.
 hipError_t launch_prep(const PrepArgs &a, hipStream_t stream);
 hipError_t launch_lane(const EvalArgs &a, hipStream_t stream);
+hipError_t launch_pair(const EvalArgs &a, hipStream_t stream);
 hipError_t launch_wave_all(const EvalArgs &a, hipStream_t stream);
 hipError_t launch_tail(const EvalArgs &a, hipStream_t stream);
 // two-kernel form: mask int16 [rows][mask_ld], row abase(t) + i

@@ -15,6 +15,8 @@
 //                         the window minimum is answered in O(1) per state from block
 //                         suffix minima held in LDS; windows longer than its LDS history are
 //                         left to the long kernel.
+//  split_pair_kernel      the lane kernel with two wavefronts per 64 scenarios, from both ends of the
+//                         tour, for launches of few work items.
 //  split_tail_kernel      reports the sums; first the lane kernel's blocks over a history of 256 positions, for tours
 //                         whose windows outgrow the lane kernel's 64 and for the scenarios it
 //                         marks; what outgrows this history too is finished one scenario per
@@ -52,6 +54,16 @@ __device__ __forceinline__ int32_t arc_cost(const PrepArgs &a, int u, int v)
     if (a.kind == 0) return dist_coords(a.xy, u, v);
     return a.dist[(long long)u * (a.N + 1) + v];
 }
+
+// The pair kernel (below) splits a tour in two halves.
+// Last forward state of a tour of n >= 16 customers: about half of them, less the blocks that the
+// join takes, one state short of a multiple of 16.
+__host__ __device__ inline int pair_middle(int n)
+{
+    const int a = ((n + 1) >> 5) - 1;
+    return 16 * (a > 1 ? a : 1) - 1;
+}
+__host__ __device__ inline int pair_shift(int n) { return (14 - n) & 15; }
 
 // One workgroup per tour: the weights w, the row offsets and the padding of tour t, and the
 // zeroed result block of the tour. Workgroup 0 also resets the batch counters. Workgroups
@@ -95,6 +107,19 @@ __global__ __launch_bounds__(1024) void split_prep_kernel(PrepArgs a)
     __syncthreads();
     if (tid == 0) {
         for (int i = 1; i < 16; ++i) red[0] += red[i];
+    }
+    __syncthreads();
+    if (a.pair && n >= 16) {
+        // the mirrored half: position k stands for break n - k + d (break n up to k = d); its demand
+        // is that of the customer after the break
+        uint32_t *rb = a.tour.rowoff32_back + ab;
+        int32_t *wb = a.tour.w_back + ab;
+        const int d = pair_shift(n);
+        for (int k = tid; k <= n + kRowPad; k += 1024) {
+            const int i = n - k + d;  // break
+            rb[k] = k <= d || i < 0 ? kRowAbsent : rowoff32[i + 1];
+            wb[k] = k == 0 ? ends[1] : k <= d || i < 1 ? 0 : w[i];
+        }
     }
     // positions n+1 .. n+kRowPad: row 0 (valid memory), absent for the lane kernel, weight 0,
     // so that kernels can load whole blocks of positions past n without guards
@@ -641,12 +666,16 @@ struct LaneState {
     int ovf;         // nonzero: past the history or 16 bits (a lane mask in scalar registers
                      // measured 1% slower over the whole kernel)
     bool past;       // H = 256: a window start fell out of the lane kernel's 64 positions
+    int Send;        // half a tour: start of its last state, and Plast as of that state
+    uint32_t Pend;
 };
 
 // One block step (R = c mod kRing): demands of block c + 3, window starts of block c + 1, DP
-// of block c. qUse holds the demands of block c + 1, qLoad receives those of block c + 3.
-template <int LB, int H>
-__device__ __forceinline__ void lane_step(LaneLds<H> &L, int lane, int R, int c, int n, uint32_t QQ,
+// of block c. qUse holds the demands of block c + 1, qLoad receives those of block c + 3. HALF: the
+// run ends inside a tour, in the last state of a block or (`fill`) in the one before, so that the
+// last block's records are written too, and the tour goes on past it.
+template <int LB, int H, bool HALF>
+__device__ __forceinline__ void lane_step(LaneLds<H> &L, int lane, int R, int c, int n, bool fill, uint32_t QQ,
                                           __amdgpu_buffer_rsrc_t dem, __amdgpu_buffer_rsrc_t wrsrc,
                                           cu32 *__restrict__ rowoff, uint32_t lane_off,
                                           ci32 *__restrict__ w, const uint16_t (&qUse)[LB],
@@ -666,7 +695,13 @@ __device__ __forceinline__ void lane_step(LaneLds<H> &L, int lane, int R, int c,
     const uint32_t lane4 = (uint32_t)lane << 2, lane8 = (uint32_t)lane << 3;
     // the ring and the block records must still hold every window start of block c + 1
     // (state LB*c + LB-1 exists whenever block c + 1 does)
-    if (c + 1 <= nb) {
+    if constexpr (HALF) {
+        if (c == nb) {
+            st.Send = sCur[LB - 1];
+            st.Pend = st.Plast;
+        }
+    }
+    if (HALF || c + 1 <= nb) {
         st.ovf |= (sCur[LB - 1] - ((p0 - (C::kRecs - 2) * LB) << 7)) & INT_MIN;
         if constexpr (H > 64) st.past |= sCur[LB - 1] < ((p0 - 2 * LB) << 7);
     }
@@ -727,7 +762,10 @@ __device__ __forceinline__ void lane_step(LaneLds<H> &L, int lane, int R, int c,
         }
         // no later block reads the last block's records (and its suffix offsets would hold
         // g_n = f_n, which need not fit 16 bits)
-        if (c < nb) lane_block_end<LB, H>(L, lane, R, gb, st.bm, st.ovf);
+        if constexpr (HALF) {
+            if (c == nb && fill) gb[LB - 1] = gb[LB - 2];
+        }
+        if (HALF || c < nb) lane_block_end<LB, H>(L, lane, R, gb, st.bm, st.ovf);
         // the last pair counts positions up to its base + 9; the ring is written up to
         // first + LB-1. Either condition below is rare: redo the block's starts (16-state
         // blocks with wider pair counts first, then state by state where those fall short).
@@ -737,17 +775,20 @@ __device__ __forceinline__ void lane_step(LaneLds<H> &L, int lane, int R, int c,
             else
                 lane_starts_careful<LB, H>(L, lane, first, TT, sCur[LB - 1], sNext);
         }
-        if (c == nb) st.gres = block_g_at<LB>(gb, n & (LB - 1));
+        if (!HALF && c == nb) st.gres = block_g_at<LB>(gb, n & (LB - 1));
         return;
     }
     // careful step (positions past n load demand 0)
-    if (c + 1 <= nb) {
+    if (HALF || c + 1 <= nb) {
         uint32_t TT[LB / 2];
         lane_prefix<LB, H>(L, lane, (R + 1) % C::kRing, qUse, QQ, st.Plast, st.qor, TT);
         lane_starts_pairs<LB, H>(L, lane, first, TT, sCur[LB - 1], sNext);
     }
     lane_dp_careful<LB, H>(L, lane, c, w, sCur, gb, st.err);
-    if (c + 1 <= nb) {
+    if constexpr (HALF) {
+        if (c == nb && fill) gb[LB - 1] = gb[LB - 2];
+    }
+    if (HALF || c + 1 <= nb) {
         lane_block_end<LB, H>(L, lane, R, gb, st.bm, st.ovf);
     } else {
         st.gres = block_g_at<LB>(gb, n & (LB - 1));  // block c holds state n
@@ -801,12 +842,12 @@ __device__ __forceinline__ LaneTour lane_tour(const EvalArgs &a, int t)
 
 // States 0..n of a tour for the scenarios at byte offset lane_off (one per lane) of its demand
 // rows; qA, qB and qC hold the demands of blocks 0, 1 and 2.
-template <int LB, int H>
+template <int LB, int H, bool HALF = false>
 __device__ __forceinline__ void lane_run(LaneLds<H> &L, const LaneTour &tr, int Q,
                                          __amdgpu_buffer_rsrc_t rsrc, uint32_t lane_off,
                                          uint16_t (&qA)[LB], uint16_t (&qB)[LB],
                                          uint16_t (&qC)[LB], bool by_progress,
-                                         LaneState<LB, H> &st)
+                                         LaneState<LB, H> &st, bool fill = false)
 {
     using C = LaneCfg<LB, H>;
     const int lane = threadIdx.x & 63;
@@ -846,15 +887,15 @@ __device__ __forceinline__ void lane_run(LaneLds<H> &L, const LaneTour &tr, int 
     for (int c = 0; c <= nb; c += C::kSteps) {
         if (by_progress) item_priority(c, nb);
         const int R = H == 64 ? 0 : c & (C::kRing - 1);
-        lane_step<LB, H>(L, lane, R, c, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qB, qD, sA, sB, wA, wB, st);
-        lane_step<LB, H>(L, lane, R + 1, c + 1, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qC, qA, sB, sA, wB, wA, st);
-        lane_step<LB, H>(L, lane, R + 2, c + 2, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qD, qB, sA, sB, wA, wB, st);
-        lane_step<LB, H>(L, lane, R + 3, c + 3, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qA, qC, sB, sA, wB, wA, st);
+        lane_step<LB, H, HALF>(L, lane, R, c, n, fill, QQ, rsrc, wrsrc, rowoff, lane_off, w, qB, qD, sA, sB, wA, wB, st);
+        lane_step<LB, H, HALF>(L, lane, R + 1, c + 1, n, fill, QQ, rsrc, wrsrc, rowoff, lane_off, w, qC, qA, sB, sA, wB, wA, st);
+        lane_step<LB, H, HALF>(L, lane, R + 2, c + 2, n, fill, QQ, rsrc, wrsrc, rowoff, lane_off, w, qD, qB, sA, sB, wA, wB, st);
+        lane_step<LB, H, HALF>(L, lane, R + 3, c + 3, n, fill, QQ, rsrc, wrsrc, rowoff, lane_off, w, qA, qC, sB, sA, wB, wA, st);
         if constexpr (C::kSteps == 8) {
-            lane_step<LB, H>(L, lane, 4, c + 4, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qB, qD, sA, sB, wA, wB, st);
-            lane_step<LB, H>(L, lane, 5, c + 5, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qC, qA, sB, sA, wB, wA, st);
-            lane_step<LB, H>(L, lane, 6, c + 6, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qD, qB, sA, sB, wA, wB, st);
-            lane_step<LB, H>(L, lane, 7, c + 7, n, QQ, rsrc, wrsrc, rowoff, lane_off, w, qA, qC, sB, sA, wB, wA, st);
+            lane_step<LB, H, HALF>(L, lane, 4, c + 4, n, fill, QQ, rsrc, wrsrc, rowoff, lane_off, w, qB, qD, sA, sB, wA, wB, st);
+            lane_step<LB, H, HALF>(L, lane, 5, c + 5, n, fill, QQ, rsrc, wrsrc, rowoff, lane_off, w, qC, qA, sB, sA, wB, wA, st);
+            lane_step<LB, H, HALF>(L, lane, 6, c + 6, n, fill, QQ, rsrc, wrsrc, rowoff, lane_off, w, qD, qB, sA, sB, wA, wB, st);
+            lane_step<LB, H, HALF>(L, lane, 7, c + 7, n, fill, QQ, rsrc, wrsrc, rowoff, lane_off, w, qA, qC, sB, sA, wB, wA, st);
         }
     }
     // counts exact only while 8 * max(q) + Q < 2^15 (qor >= max(q)); bit 15 (a negative
@@ -1015,6 +1056,168 @@ __global__ __launch_bounds__(64) void split_lane_kernel(EvalArgs a)
         lane_item<LB>(L, a, t, (long long)k - r * nsb, rsrc);
         k = __builtin_amdgcn_readfirstlane(knext);
     }
+}
+
+// ------------------------------------------------------------------------- pair kernel
+//
+// A launch of few work items is bound by the serial chain of one wavefront per item, on a fraction
+// of the chip. Here two wavefronts share an item: one runs the DP from the depot forward over states
+// 0..m, the other from the tour's end backward over states n..m+1 (H_i = w_i + min of H over the
+// predecessors' mirror image, the states that a route starting at i can end in), and the best pair
+// of a forward and a backward state with one route between them joins them:
+//     f_n = D[n] + min { G_p + H_i : p <= m < i, P_i - P_p <= Q }.
+// The integers are the same, so is the minimum. The backward half is the same code on mirrored
+// arrays (prep kernel): position k holds break n - k + d, and the first d + 1 positions stand for
+// break n (no weight and a full vehicle's demand from one to the next: the same value); d makes the states k = 15, 31, ... those with
+// n - k + d = 15, 31, ..., whose windows reach over more than 47 positions exactly where a forward
+// state 48 positions on sees more than 47 predecessors: every scenario that the one-wavefront
+// form would mark is marked here. m + 1 is a multiple of 16; the backward half then ends one state
+// short of a full block.
+// Measured, this kernel against the lane kernel: 1000 customers, 157 items 72 us against 104, 1024
+// items 92 against 122. It is not half: the join takes about 10 us, and two wavefronts of one
+// compute unit run each state 10 to 20% slower than one.
+
+// The join, by the forward wavefront: window starts of the next (at most three) blocks of states
+// i > m, the forward minimum over their predecessors up to m, and the backward suffix minimum at
+// i (the least H from m + 1 to i in its block: a smaller i has an older start, so a minimum no
+// larger, and the least sum is the same). Starts left at or before m after three blocks are past
+// the history, and flagged by its test.
+template <int LB>
+__device__ __forceinline__ int pair_join(LaneLds<64> &F, LaneLds<64> &B, const LaneTour &tr, int Q,
+                                         __amdgpu_buffer_rsrc_t rsrc, uint32_t lane_off, int m,
+                                         LaneState<LB, 64> &st)
+{
+    using C = LaneCfg<LB, 64>;
+    const int lane = threadIdx.x & 63;
+    const uint32_t lane8 = (uint32_t)lane << 3;
+    const uint32_t QQ = (uint32_t)Q | ((uint32_t)Q << 16);
+    const int n = tr.n, k_of_0 = n + pair_shift(n);
+    uint16_t q[LB], qn[LB];
+    lane_load_block<LB>(rsrc, tr.rowoff, lane_off, (m + 1) / LB, q);
+    uint32_t P = st.Pend;
+    int Sp = st.Send, best = kInf;
+    // one copy of the block's code: run two or three times, unrolled it would cost its fetches
+#pragma unroll 1
+    for (int e = 0; e < 3; ++e) {
+        const int p0 = m + 1 + e * LB;
+        if (p0 > n || !__any(Sp < S_of(m + 1, 0))) break;
+        lane_load_block<LB>(rsrc, tr.rowoff, lane_off, p0 / LB + 1, qn);
+        uint32_t TT[LB / 2];
+        int s[LB];
+        lane_prefix<LB, 64>(F, lane, (p0 / LB) & (C::kRing - 1), q, QQ, P, st.qor, TT);
+        lane_starts_pairs<LB, 64>(F, lane, p0, TT, Sp, s);
+#pragma unroll
+        for (int t = 0; t < LB; ++t) {
+            const int i = p0 + t;
+            const int k = k_of_0 - i;  // the backward position of break i
+            uint32_t dlv;
+            uint64_t recv;
+            query_issue<LB, 64>(F, s[t], lane8, dlv, recv);
+            const int g = query_min(dlv, recv, kInf);
+            const int h = (int)(uint32_t)B.rec[(k >> C::kLog) & 3][lane] + (int)B.dl[k & 63][lane];
+            if (s_of(s[t]) <= m && i <= n) best = min(best, g + h);
+            if (t == 0) st.err |= e == 0 && s_of(s[t]) > m;  // customer m + 1 does not fit
+        }
+#pragma unroll
+        for (int t = 0; t < LB; ++t) q[t] = qn[t];
+        Sp = s[LB - 1];
+        st.ovf |= (Sp - ((p0 - 2 * LB) << 7)) & INT_MIN;
+    }
+    return best;
+}
+
+// Half of a work item in blocks of LB states; then, in the forward wavefront, the join: returns its
+// scenario's cost.
+template <int LB>
+__device__ __forceinline__ int pair_item(LaneLds<64> (&L)[2], const EvalArgs &a, const LaneTour &tr,
+                                         const LaneTour &half, int total, bool back, uint32_t lane_off,
+                                         __amdgpu_buffer_rsrc_t rsrc, uint16_t (&qA)[LB],
+                                         uint16_t (&qB)[LB], uint16_t (&qC)[LB], int &ovf,
+                                         bool &err)
+{
+    const int lane = threadIdx.x & 63;
+    LaneState<LB, 64> st;
+    lane_run<LB, 64, true>(L[back], half, a.Q, rsrc, lane_off, qA, qB, qC, false, st, back);
+    // the backward prefix loads are not needed any more: their first row takes its flags
+    if (back) L[1].pp[0][lane] = (st.ovf != 0 ? 1u : 0u) | (st.err ? 2u : 0u);
+    __syncthreads();
+    if (back) return 0;
+    const uint32_t flags = L[1].pp[0][lane];
+    const int best = pair_join<LB>(L[0], L[1], tr, a.Q, rsrc, lane_off, half.n, st);
+    ovf = st.ovf | (int)(flags & 1u) |
+          (8u * ((st.qor | (st.qor >> 16)) & 0xFFFFu) + (uint32_t)a.Q > 32767u ? 1 : 0);
+    err = st.err || (flags & 2u);
+    return total + best;
+}
+
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void split_pair_kernel(
+    EvalArgs a)
+{
+    __shared__ LaneLds<64> L[2];
+    __shared__ int s_class;
+    const bool back = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) != 0;
+    const int lane = threadIdx.x & 63;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)a.demand, (short)0, (int)a.lane_bytes, 0x00020000);
+    const long long nsb = (a.S + 63) / 64;
+    const long long k = blockIdx.x;
+    if (k >= nsb * *(ci64 *)a.tour.nt) return;
+    const int t = ((ci32 *)a.tour.order)[k / nsb];
+    const long long sb = k - k / nsb * nsb;
+    const LaneTour tr = lane_tour(a, t);
+    const long long scen = sb * 64 + lane;
+    const uint32_t lane_off = (uint32_t)min(scen, (long long)a.S - 1) * 2u;
+    int cost = 0, ovf = 1;
+    bool err = false;
+    if (tr.n >= 16) {  // shorter tours go to the tail kernel
+        const int m = pair_middle(tr.n);
+        const int64_t ab = ((ci64 *)a.tour.tptr)[t] + (int64_t)t * (1 + kRowPad);
+        LaneTour half = tr;
+        half.n = m;
+        ci32 *wb = (ci32 *)a.tour.w_back + ab;
+        if (back) {
+            half.n = tr.n - m - 1 + pair_shift(tr.n);
+            half.rowoff = (cu32 *)a.tour.rowoff32_back + ab;
+            half.w = wb;
+            half.wrsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.tour.w_back + ab), (short)0,
+                                                           (int)(sizeof(int32_t) * (tr.n + 1 + kRowPad)),
+                                                           0x00020000);
+        }
+        const int total = tr.w[tr.n] - wb[0];  // the tour's arcs
+        uint16_t qA[16], qB[16], qC[16];
+        lane_load_block<16>(rsrc, half.rowoff, lane_off, 0, qA);
+        lane_load_block<16>(rsrc, half.rowoff, lane_off, 1, qB);
+        lane_load_block<16>(rsrc, half.rowoff, lane_off, 2, qC);
+        if (back) {
+            // positions 1 .. d demand a full vehicle: each sees the one before it, the customers'
+            // windows none but the last
+            const int d = pair_shift(tr.n);
+#pragma unroll
+            for (int j = 1; j < 16; ++j) qA[j] = j <= d ? (uint16_t)a.Q : qA[j];
+        }
+        int cls = kWindowsMid;
+        if (a.lane_block == 0) {
+            if (!back) {
+                cls = window_class(qA, qB, qC, tr.n, a.Q, scen < a.S);
+                if (lane == 0) s_class = cls;
+            }
+            __syncthreads();
+            cls = __builtin_amdgcn_readfirstlane(s_class);
+        }
+        if (cls == kWindowsMid) {
+            cost = pair_item<16>(L, a, tr, half, total, back, lane_off, rsrc, qA, qB, qC, ovf, err);
+        } else if (cls == kWindowsShort) {
+            uint16_t rA[8], rB[8], rC[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                rA[j] = qA[j];
+                rB[j] = qA[8 + j];
+                rC[j] = qB[j];
+            }
+            cost = pair_item<8>(L, a, tr, half, total, back, lane_off, rsrc, rA, rB, rC, ovf, err);
+        }
+    }
+    if (!back) lane_finish(a, t, scen, ovf != 0, err, cost, true);
 }
 
 // ------------------------------------------------------------------------- wave kernel
@@ -1383,6 +1586,13 @@ static hipError_t wave_lds_allow(size_t bytes)
     if (bytes <= 65536) return hipSuccess;
     return hipFuncSetAttribute((const void *)split_wave_kernel,
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
+hipError_t launch_pair(const EvalArgs &a, hipStream_t stream)
+{
+    const long long items = (a.S + 63) / 64 * a.tour.T_grid;
+    hipLaunchKernelGGL(split_pair_kernel, dim3((unsigned)items), dim3(128), 0, stream, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_wave_all(const EvalArgs &a, hipStream_t stream)

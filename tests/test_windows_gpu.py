@@ -98,3 +98,35 @@ def test_infeasible_demand_under_long_windows(ctx):
     with pytest.raises(sg.SplitError) as ei:
         ctx.eval(tour, torch.from_numpy(dem).cuda(), Q)
     assert ei.value.status == sg.SPLIT_E_DEMAND
+
+
+@pytest.mark.parametrize("block", [0, 16])
+def test_two_wavefronts_per_item_over_every_remainder(ctx, block):
+    # few work items of long tours run from both ends: every n mod 32 (the middle, the shift of the
+    # mirrored half, the last block's tail), tours too short to be split, an asymmetric matrix
+    import paper_2511_18022_amd as sg
+    g = np.random.default_rng(77)
+    d = g.integers(1, 1500, size=(N + 1, N + 1)).astype(np.int32)
+    c = sg.SplitContext(0)
+    c.set_dist(d)
+    c.set_tuning(sg.SplitTuning(sg.FORM_AUTO, 0, 0, 0, block))
+    lens = [*range(321, 353), 700, 1, 2, 15, 16, 17, 31, 33, 47, 48]
+    tours = [g.permutation(np.arange(1, N + 1))[:n].astype(np.int32) for n in lens]
+    for mean, Q in ((8, 90), (8, 200), (8, 330)):
+        dem = g.integers(0, 2 * mean + 1, size=(N, S), dtype=np.int16)
+        cost, stats, status = c.eval_batch(tours, torch.from_numpy(dem).cuda(), Q)
+        assert status == [0] * len(tours)
+        for t, tour in enumerate(tours):
+            want = oracle.split(tour, d, dem, Q)
+            assert np.array_equal(cost[t].cpu().numpy(), want), (lens[t], Q)
+            assert stats[t].sumsq == oracle.moments(want)["sumsq"], (lens[t], Q)
+            assert stats[t].n_fallback == past_history(tour, dem, Q), (lens[t], Q)
+    # an infeasible demand at the customers around the middle, and at the ends
+    tour = tours[0]
+    for at in (0, 140, 143, 144, 145, 159, 160, 320):
+        bad = dem.copy()
+        bad[int(tour[at]) - 1, 99] = Q + 1
+        with pytest.raises(sg.SplitError) as ei:
+            c.eval(tour, torch.from_numpy(bad).cuda(), Q)
+        assert ei.value.status == sg.SPLIT_E_DEMAND, at
+    c.close()
