@@ -184,8 +184,8 @@ split_status check_call(split_nn *nn, const char *who, const void *tours, int32_
     return SPLIT_OK;
 }
 
-// Features, the four conv layers and the head for T tours. With pred (prediction) the layers
-// run fused per tile in LDS; without (training) every layer's output is kept for backward.
+// Features, the four conv layers (fused per tile in LDS) and the head for T tours. Without pred
+// (training) every layer's output is kept for backward.
 constexpr size_t kMaxTimingPairs = 4096;
 
 split_status collect_timing(split_nn *nn)
@@ -226,54 +226,49 @@ split_status timing_begin(split_nn *nn, hipStream_t st, hipEvent_t *stop)
     return SPLIT_OK;
 }
 
+// host_err (pinned, or NULL): where the head kernel hands the feature kernels' flag, which covers
+// every forward pass since it was last handed over.
 split_status forward(split_nn *nn, const NnInstance &in, const int32_t *tours, int32_t T,
-                     int32_t n, float *pred, hipStream_t st)
+                     int32_t n, float *pred, int32_t *host_err, hipStream_t st)
 {
-    split_status s = ensure_act(nn, T, n, pred == nullptr, st);
+    const bool train = pred == nullptr;
+    split_status s = ensure_act(nn, T, n, train, st);
     if (s != SPLIT_OK) return s;
-    if (pred) {
-        const int64_t need = (int64_t)T * nn_fused_tiles(n) * kNnWidth;
-        if (need > nn->cap_zpart) {
-            NN_TRY(nn, hipDeviceSynchronize());
-            nn->cap_zpart = 0;
-            if (!realloc_dev(&nn->zpart, sizeof(float) * (size_t)need))
-                return ctx_fail(nn->ctx, SPLIT_E_NOMEM, "surrogate: pooling buffer failed");
-            nn->cap_zpart = need;
-        }
-        const int64_t pos = (int64_t)T * n;
-        if (pos > nn->cap_xp) {
-            NN_TRY(nn, hipDeviceSynchronize());
-            const int64_t cap = pos + pos / 4;
-            nn->cap_xp = 0;
-            if (!realloc_dev(&nn->Xp, sizeof(uint16_t) * kNnFeatures * (size_t)cap))
-                return ctx_fail(nn->ctx, SPLIT_E_NOMEM, "surrogate: packed feature buffer failed");
-            nn->cap_xp = cap;
-        }
-        NN_TRY(nn, nn_launch_features(in, tours, T, n, nn->musd, nn->Q, nn->L, nn->Xp, true,
-                                      nn->err, st));
-        hipEvent_t stop = nullptr;
+    const int64_t need = (int64_t)T * nn_pool_groups(n) * kNnWidth;
+    if (need > nn->cap_zpart) {
+        NN_TRY(nn, hipDeviceSynchronize());
+        nn->cap_zpart = 0;
+        if (!realloc_dev(&nn->zpart, sizeof(float) * (size_t)need))
+            return ctx_fail(nn->ctx, SPLIT_E_NOMEM, "surrogate: pooling buffer failed");
+        nn->cap_zpart = need;
+    }
+    const int64_t pos = (int64_t)T * n;
+    if (!train && pos > nn->cap_xp) {
+        NN_TRY(nn, hipDeviceSynchronize());
+        const int64_t cap = pos + pos / 4;
+        nn->cap_xp = 0;
+        if (!realloc_dev(&nn->Xp, sizeof(uint16_t) * kNnFeatures * (size_t)cap))
+            return ctx_fail(nn->ctx, SPLIT_E_NOMEM, "surrogate: packed feature buffer failed");
+        nn->cap_xp = cap;
+    }
+    uint16_t *X = train ? nn->X : nn->Xp;
+    NN_TRY(nn, nn_launch_features(in, tours, T, n, nn->musd, nn->Q, nn->L, X, !train, nn->err, st));
+    const NnHidden H = {{nn->H[0], nn->H[1], nn->H[2], nn->H[3]}};
+    hipEvent_t stop = nullptr;
+    if (!train) {
         s = timing_begin(nn, st, &stop);
         if (s != SPLIT_OK) return s;
-        NN_TRY(nn, nn_launch_fwd_fused(nn->Xp, nn->w, nn->P, T, n, nn->zpart, st));
-        if (stop) NN_TRY(nn, hipEventRecord(stop, st));
-        NN_TRY(nn, nn_launch_head_pool(nn->zpart, T, n, nn->P, nn->z, nn->a, nn->y, pred,
-                                       nn->shift, nn->scale, st));
-        return SPLIT_OK;
     }
-    NN_TRY(nn, nn_launch_features(in, tours, T, n, nn->musd, nn->Q, nn->L, nn->X, false, nn->err,
-                                  st));
-    NN_TRY(nn, nn_launch_conv(kNnCi0, 0, nn->X, nn->w.f[0], nn->P + nn_off_b(0), nullptr, nn->H[0],
-                              T, n, st));
-    for (int l = 1; l < 4; ++l)
-        NN_TRY(nn, nn_launch_conv(kNnWidth, 0, nn->H[l - 1], nn->w.f[l], nn->P + nn_off_b(l),
-                                  nullptr, nn->H[l], T, n, st));
-    NN_TRY(nn, nn_launch_head_fwd(nn->H[3], T, n, nn->P, nn->z, nn->a, nn->y, pred, nn->shift,
-                                  nn->scale, st));
+    NN_TRY(nn, nn_launch_fwd_fused(X, nn->w, nn->P, T, n, nn->zpart, train ? &H : nullptr, st));
+    if (stop) NN_TRY(nn, hipEventRecord(stop, st));
+    NN_TRY(nn, nn_launch_head_pool(nn->zpart, T, n, nn->P, nn->z, nn->a, nn->y, pred, nn->shift,
+                                   nn->scale, nn->err, host_err, st));
     return SPLIT_OK;
 }
 
-// Loss terms and the full gradient into nn->G for the batch whose forward pass just ran.
-split_status backward(split_nn *nn, const float *labels, int32_t T, int32_t n, hipStream_t st)
+// The loss into *loss and the full gradient into nn->G for the batch whose forward pass just ran.
+split_status backward(split_nn *nn, const float *labels, int32_t T, int32_t n, float *loss,
+                      hipStream_t st)
 {
     const int64_t chunks = nn_wgrad_chunks(T, n, kWgradChunk);
     if (chunks > nn->cap_chunks) {
@@ -285,8 +280,8 @@ split_status backward(split_nn *nn, const float *labels, int32_t T, int32_t n, h
         nn->cap_chunks = chunks;
     }
     NN_TRY(nn, nn_launch_head_bwd(labels, T, n, nn->P, nn->z, nn->a, nn->y, nn->shift, nn->scale,
-                                  nn->da, nn->dz, nn->dy, nn->lterms, nn->H[3], nn->dP[0], nn->G,
-                                  st));
+                                  nn->da, nn->dz, nn->dy, nn->lterms, loss, nn->H[3], nn->dP[0],
+                                  nn->G, st));
     // layer l (0-based) reads input in[l] and the pre-activation gradient cur; for l > 0 the
     // input gradient goes into the other dP buffer
     const uint16_t *in_of[4] = {nn->X, nn->H[0], nn->H[1], nn->H[2]};
@@ -296,8 +291,8 @@ split_status backward(split_nn *nn, const float *labels, int32_t T, int32_t n, h
                                    kWgradChunk, (int32_t)chunks, nn->partW, nn->partB, nn->G,
                                    nn_off_w(l), nn_off_b(l), st));
         if (l > 0) {
-            NN_TRY(nn, nn_launch_conv(kNnWidth, 1, nn->dP[cur], nn->w.b[l], nullptr, in_of[l],
-                                      nn->dP[1 - cur], T, n, st));
+            NN_TRY(nn, nn_launch_conv_back(nn->dP[cur], nn->w.b[l], in_of[l], nn->dP[1 - cur], T,
+                                           n, st));
             cur = 1 - cur;
         }
     }
@@ -314,13 +309,30 @@ split_status adam_step(split_nn *nn, float lr, hipStream_t st)
     return SPLIT_OK;
 }
 
-// Waits for the stream and fails with SPLIT_E_TOUR if a feature kernel met a bad id.
+// Waits for the stream and fails with SPLIT_E_TOUR if a feature kernel met a bad id (the flag as the
+// head kernel handed it over).
 split_status check_ids(split_nn *nn, const char *who, hipStream_t st)
 {
-    NN_TRY(nn, hipMemcpyAsync(nn->h_err, nn->err, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     NN_TRY(nn, hipStreamSynchronize(st));
     if (*nn->h_err)
         return ctx_fail(nn->ctx, SPLIT_E_TOUR, "%s: a tour id is outside 1..N", who);
+    return SPLIT_OK;
+}
+
+// Predictions of C tours, kPredChunk at a time; the last pass hands the flag over.
+split_status predict_all(split_nn *nn, const NnInstance &in, const int32_t *tours, int64_t C,
+                         int32_t n, float *pred, hipStream_t st)
+{
+    for (int64_t t0 = 0; t0 < C; t0 += kPredChunk) {
+        const int32_t Tc = (int32_t)(C - t0 < kPredChunk ? C - t0 : kPredChunk);
+        const split_status s = forward(nn, in, tours + t0 * n, Tc, n, pred + t0,
+                                       t0 + Tc == C ? nn->h_err : nullptr, st);
+        if (s != SPLIT_OK) {
+            // a pass that never ran leaves the flag of those before it: not the next call's
+            (void)hipMemsetAsync(nn->err, 0, sizeof(int32_t), st);
+            return s;
+        }
+    }
     return SPLIT_OK;
 }
 
@@ -358,7 +370,6 @@ void free_nn(split_nn *nn)
                      nn->pred, nn->zpart})
         if (p) (void)hipFree(p);
     for (int l = 0; l < 4; ++l) {
-        if (nn->w.f[l]) (void)hipFree(nn->w.f[l]);
         if (nn->w.b[l]) (void)hipFree(nn->w.b[l]);
         if (nn->w.g[l]) (void)hipFree(nn->w.g[l]);
         if (nn->H[l]) (void)hipFree(nn->H[l]);
@@ -436,17 +447,16 @@ split_status split_nn_create(split_ctx *ctx, uint64_t seed, double length_scale,
     bool ok = g.ok;
     for (float **p : {&nn->P, &nn->m, &nn->v, &nn->G})
         ok = ok && hipMalloc(p, sizeof(float) * kNnParams) == hipSuccess;
-    ok = ok && hipMalloc(&nn->w.f[0], sizeof(uint16_t) * kNnSizeW1) == hipSuccess &&
-         hipMalloc(&nn->w.g[0], sizeof(uint16_t) * kNnSizeW1) == hipSuccess &&
+    ok = ok && hipMalloc(&nn->w.g[0], sizeof(uint16_t) * kNnSizeW1) == hipSuccess &&
          // the fused kernel's packed layer-1 weights: padding entries are never written
          hipMemset(nn->w.g[0], 0, sizeof(uint16_t) * kNnSizeW1) == hipSuccess;
     for (int l = 1; l < 4; ++l)
-        ok = ok && hipMalloc(&nn->w.f[l], sizeof(uint16_t) * kNnSizeWl) == hipSuccess &&
-             hipMalloc(&nn->w.b[l], sizeof(uint16_t) * kNnSizeWl) == hipSuccess &&
+        ok = ok && hipMalloc(&nn->w.b[l], sizeof(uint16_t) * kNnSizeWl) == hipSuccess &&
              hipMalloc(&nn->w.g[l], sizeof(uint16_t) * kNnSizeWl) == hipSuccess;
     ok = ok && hipMalloc(&nn->err, sizeof(int32_t)) == hipSuccess &&
+         hipMemset(nn->err, 0, sizeof(int32_t)) == hipSuccess &&
          hipMalloc(&nn->lout, sizeof(float)) == hipSuccess &&
-         hipHostMalloc((void **)&nn->h_err, sizeof(int32_t), 0) == hipSuccess;
+         hipHostMalloc((void **)&nn->h_err, sizeof(int32_t), hipHostMallocCoherent) == hipSuccess;
     if (!ok) {
         free_nn(nn);
         delete nn;
@@ -543,12 +553,8 @@ split_status split_nn_predict(split_nn *nn, const int32_t *tours, int32_t T, int
     if (s != SPLIT_OK) return s;
     Guard g(nn->device);
     hipStream_t st = (hipStream_t)hip_stream;
-    NN_TRY(nn, hipMemsetAsync(nn->err, 0, sizeof(int32_t), st));
-    for (int32_t t0 = 0; t0 < T; t0 += kPredChunk) {
-        const int32_t Tc = T - t0 < kPredChunk ? T - t0 : kPredChunk;
-        s = forward(nn, in, tours + (int64_t)t0 * n, Tc, n, pred + t0, st);
-        if (s != SPLIT_OK) return s;
-    }
+    s = predict_all(nn, in, tours, T, n, pred, st);
+    if (s != SPLIT_OK) return s;
     return check_ids(nn, "split_nn_predict", st);
 }
 
@@ -562,11 +568,9 @@ split_status split_nn_gradient(split_nn *nn, const int32_t *tours, const float *
     if (s != SPLIT_OK) return s;
     Guard g(nn->device);
     hipStream_t st = (hipStream_t)hip_stream;
-    NN_TRY(nn, hipMemsetAsync(nn->err, 0, sizeof(int32_t), st));
-    s = forward(nn, in, tours, T, n, nullptr, st);
-    if (s == SPLIT_OK) s = backward(nn, labels, T, n, st);
+    s = forward(nn, in, tours, T, n, nullptr, nn->h_err, st);
+    if (s == SPLIT_OK) s = backward(nn, labels, T, n, nn->lout, st);
     if (s != SPLIT_OK) return s;
-    NN_TRY(nn, nn_launch_loss(nn->lterms, T, nn->lout, st));
     s = check_ids(nn, "split_nn_gradient", st);
     if (s != SPLIT_OK) return s;
     if (grad) NN_TRY(nn, hipMemcpy(grad, nn->G, sizeof(float) * kNnParams, hipMemcpyDeviceToHost));
@@ -590,11 +594,9 @@ split_status split_nn_train_step(split_nn *nn, const int32_t *tours, const float
     if (s != SPLIT_OK) return s;
     Guard g(nn->device);
     hipStream_t st = (hipStream_t)hip_stream;
-    NN_TRY(nn, hipMemsetAsync(nn->err, 0, sizeof(int32_t), st));
-    s = forward(nn, in, tours, T, n, nullptr, st);
-    if (s == SPLIT_OK) s = backward(nn, labels, T, n, st);
+    s = forward(nn, in, tours, T, n, nullptr, nn->h_err, st);
+    if (s == SPLIT_OK) s = backward(nn, labels, T, n, nn->lout, st);
     if (s != SPLIT_OK) return s;
-    NN_TRY(nn, nn_launch_loss(nn->lterms, T, nn->lout, st));
     // ids are checked before the update touches the parameters
     s = check_ids(nn, "split_nn_train_step", st);
     if (s != SPLIT_OK) return s;
@@ -622,8 +624,9 @@ split_status split_nn_train(split_nn *nn, const int32_t *tours, const float *lab
     Guard g(nn->device);
     hipStream_t st = (hipStream_t)hip_stream;
     // every id of the training set, once, before any update
-    NN_TRY(nn, hipMemsetAsync(nn->err, 0, sizeof(int32_t), st));
     NN_TRY(nn, nn_launch_check_ids(tours, count * n, in.N, nn->err, st));
+    NN_TRY(nn, hipMemcpyAsync(nn->h_err, nn->err, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    NN_TRY(nn, hipMemsetAsync(nn->err, 0, sizeof(int32_t), st));
     s = check_ids(nn, "split_nn_train", st);
     if (s != SPLIT_OK) return s;
     NN_TRY(nn, hipDeviceSynchronize());
@@ -670,10 +673,9 @@ split_status split_nn_train(split_nn *nn, const int32_t *tours, const float *lab
         }
         NN_TRY(nn, nn_launch_gather(tours, labels, nn->perm + pos * batch, batch, n, nn->btours,
                                     nn->blabels, st));
-        s = forward(nn, in, nn->btours, batch, n, nullptr, st);
-        if (s == SPLIT_OK) s = backward(nn, nn->blabels, batch, n, st);
+        s = forward(nn, in, nn->btours, batch, n, nullptr, nullptr, st);
+        if (s == SPLIT_OK) s = backward(nn, nn->blabels, batch, n, nn->losshist + k, st);
         if (s != SPLIT_OK) return s;
-        NN_TRY(nn, nn_launch_loss(nn->lterms, batch, nn->losshist + k, st));
         s = adam_step(nn, lr, st);
         if (s != SPLIT_OK) return s;
     }
@@ -791,12 +793,8 @@ split_status split_nn_shortlist(split_nn *nn, const int32_t *tours, int32_t T, i
         }
         pr = nn->pred;
     }
-    NN_TRY(nn, hipMemsetAsync(nn->err, 0, sizeof(int32_t), st));
-    for (int32_t t0 = 0; t0 < T; t0 += kPredChunk) {
-        const int32_t Tc = T - t0 < kPredChunk ? T - t0 : kPredChunk;
-        s = forward(nn, in, tours + (int64_t)t0 * n, Tc, n, pr + t0, st);
-        if (s != SPLIT_OK) return s;
-    }
+    s = predict_all(nn, in, tours, T, n, pr, st);
+    if (s != SPLIT_OK) return s;
     s = check_ids(nn, "split_nn_shortlist", st);
     if (s != SPLIT_OK) return s;
     return topk_run(nn->ctx, &nn->tk, pr, T, K, idx, st);
@@ -826,12 +824,8 @@ split_status split_nn_screen(split_nn *nn, const int32_t *cands, int64_t C, int3
         }
         pr = nn->pred;
     }
-    NN_TRY(nn, hipMemsetAsync(nn->err, 0, sizeof(int32_t), st));
-    for (int64_t t0 = 0; t0 < C; t0 += kPredChunk) {
-        const int32_t Tc = (int32_t)(C - t0 < kPredChunk ? C - t0 : kPredChunk);
-        s = forward(nn, in, cands + t0 * n, Tc, n, pr + t0, st);
-        if (s != SPLIT_OK) return s;
-    }
+    s = predict_all(nn, in, cands, C, n, pr, st);
+    if (s != SPLIT_OK) return s;
     s = check_ids(nn, "split_nn_screen", st);
     if (s != SPLIT_OK) return s;
     if (K > nn->cap_sidx || K * n > nn->cap_stours) {

@@ -38,12 +38,16 @@ struct NnInstance {
     const int32_t *dist;  // device [(N+1)^2]
 };
 
-// bf16 weight copies: f[l] = forward layout [co][tap * CI + ci]; b[l] (l >= 1) = backward-data
-// layout [ci][tap' * 128 + co] with tap' = 4 - tap.
+// bf16 weight copies: g[l] for the forward pass; b[l] (l >= 1) = backward-data layout
+// [ci][tap' * 128 + co] with tap' = 4 - tap.
 struct NnWeights {
-    uint16_t *f[4];  // layer l: bf16 [co][tap * CI + ci]
     uint16_t *b[4];  // layers 1..3: the flipped, transposed taps for the data gradient
-    uint16_t *g[4];  // layer l in MFMA fragment order (the fused prediction kernel's reads)
+    uint16_t *g[4];  // layer l in MFMA fragment order (the fused forward kernel's reads)
+};
+
+// The outputs of the four conv layers, bf16 [T][n + 4][128] each (interior rows written).
+struct NnHidden {
+    uint16_t *h[4];
 };
 
 // Device scratch of one top-k selection (all zero before the first). After `pass` + 1 digit passes,
@@ -69,23 +73,22 @@ hipError_t nn_launch_dstats(const int16_t *demand, int64_t ld, int64_t S, int32_
 hipError_t nn_launch_features(const NnInstance &in, const int32_t *tours, int32_t T, int32_t n,
                               const double *musd, int32_t Q, double L, uint16_t *X, bool packed,
                               int32_t *err, hipStream_t st);
-hipError_t nn_launch_conv(int ci, int mode, const uint16_t *X, const uint16_t *Wt,
-                          const float *bias, const uint16_t *mask, uint16_t *Y, int32_t T,
-                          int32_t n, hipStream_t st);
-// prediction only: the four conv layers per tile in LDS, pooled into per-tile channel sums
-// (zpart [T][tiles][128]) from the packed features X [T][n][8]; then the pooled mean and the head
-int32_t nn_fused_tiles(int32_t n);
+// data gradient of a hidden layer: Y = conv(X, Wt) where mask > 0, else 0
+hipError_t nn_launch_conv_back(const uint16_t *X, const uint16_t *Wt, const uint16_t *mask,
+                               uint16_t *Y, int32_t T, int32_t n, hipStream_t st);
+// the four conv layers per tile in LDS, pooled into channel sums of 64 positions each
+// (zpart [T][nn_pool_groups(n)][128]). Without H from the packed features X [T][n][8]; with H
+// (training) from the padded ones, storing every layer's output. Then the pooled mean and the head,
+// which hands *err to host_err (unless NULL) and clears it.
+int32_t nn_pool_groups(int32_t n);
 hipError_t nn_launch_fwd_fused(const uint16_t *X, const NnWeights &w, const float *P, int32_t T,
-                               int32_t n, float *zpart, hipStream_t st);
+                               int32_t n, float *zpart, const NnHidden *H, hipStream_t st);
 hipError_t nn_launch_head_pool(const float *zpart, int32_t T, int32_t n, const float *P, float *z,
                                float *a, float *y, float *pred, double shift, double scale,
-                               hipStream_t st);
-hipError_t nn_launch_head_fwd(const uint16_t *H4, int32_t T, int32_t n, const float *P, float *z,
-                              float *a, float *y, float *pred, double shift, double scale,
-                              hipStream_t st);
+                               int32_t *err, int32_t *host_err, hipStream_t st);
 hipError_t nn_launch_head_bwd(const float *labels, int32_t T, int32_t n, const float *P,
                               const float *z, const float *a, const float *y, double shift,
-                              double scale, float *da, float *dz, float *dy, float *loss_terms,
+                              double scale, float *da, float *dz, float *dy, float *loss_terms, float *loss,
                               const uint16_t *H4, uint16_t *dP4, float *G, hipStream_t st);
 // number of weight-gradient partials for a batch: chunks of `chunk` padded rows
 int32_t nn_wgrad_chunks(int32_t T, int32_t n, int32_t chunk);
@@ -97,7 +100,6 @@ hipError_t nn_launch_adam(float *P, float *m, float *v, const float *G, float lr
 hipError_t nn_launch_pack(const float *P, const NnWeights &w, hipStream_t st);
 hipError_t nn_launch_gather(const int32_t *src, const float *lab, const int32_t *idx, int32_t B,
                             int32_t n, int32_t *dst, float *dlab, hipStream_t st);
-hipError_t nn_launch_loss(const float *terms, int32_t T, float *out, hipStream_t st);
 // candidates [count][n] from cur [n] and moves [count][3] = (type, i, j), validated by the caller
 hipError_t nn_launch_moves(const int32_t *cur, const int32_t *moves, int32_t count, int32_t n,
                            int32_t *out, hipStream_t st);

@@ -5,7 +5,7 @@
 // Layout: activations are bf16 [T][n + 4][C] (position-major, channels fastest) with two zero
 // rows before and after every tour. The 5-tap window of output position j is then the
 // contiguous span of 5 * C values starting at padded row j, so the conv is a GEMM whose A rows
-// overlap in memory (no im2col copy): out[j][co] = sum_kk X[(row j) * C + kk] * Wf[co][kk],
+// overlap in memory (no im2col copy): out[j][co] = sum_kk X[(row j) * C + kk] * W[kk][co],
 // kk = tap * C + ci. The backward-data conv is the same GEMM with the flipped, transposed
 // weights Wb[ci][tap' * 128 + co] = W[4 - tap'][ci][co].
 //
@@ -174,17 +174,16 @@ __global__ __launch_bounds__(256) void nn_features_kernel(NnInstance in, const i
 // covers the other's waits.
 // LDS holds a block as [k quarter][co] so that the 16-byte reads of the 16 lanes of a column
 // group hit consecutive addresses.
-// MODE 0: Y = bf16(relu(acc + bias[co]))       (forward)
-// MODE 1: Y = bf16(acc) where mask > 0, else 0 (backward data: mask = the layer's input H)
+// Y = bf16(acc) where mask > 0, else 0 (backward data: mask = the layer's input H).
 // Wavefronts past the last position run the loop on a clamped row (every barrier is reached)
 // and store nothing.
 constexpr int kConvDepth = 2;  // K blocks of activation loads in flight
 
-template <int CI, int MODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void nn_conv_kernel(
-    const uint16_t *__restrict__ X, const uint16_t *__restrict__ Wt, const float *__restrict__ bias,
+    const uint16_t *__restrict__ X, const uint16_t *__restrict__ Wt,
     const uint16_t *__restrict__ mask, uint16_t *__restrict__ Y, int32_t T, int32_t n)
 {
+    constexpr int CI = kNnWidth;
     constexpr int K = kNnTaps * CI;
     constexpr int KB = K / 32;
     constexpr int D = KB < kConvDepth ? KB : kConvDepth;
@@ -281,16 +280,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void n
     if (m0 >= M) return;
     // D rows (lane / 16) * 4 + i of each 16-row tile, column lane % 16 of each 16-column tile.
     // Row mb + off (off <= 51) is position jb + off of tour tb, carried into the next tours
-    // past their ends: one division per lane. The bias values (MODE 0) are loaded once, and a
-    // tile's 32 mask values (MODE 1) are all requested before the first is used.
+    // past their ends: one division per lane. A tile's 32 mask values are all requested before the
+    // first is used.
     const long long mb = m0 + (lane >> 4) * 4;
     const long long tb = mb / n;
     const int jb = (int)(mb - tb * n);
-    float bco[8];
-    if (MODE == 0) {
-#pragma unroll
-        for (int nt = 0; nt < 8; ++nt) bco[nt] = bias[nt * 16 + r16];
-    }
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
         long long base[4];
@@ -305,29 +299,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void n
                 j -= n;
                 ++t;
             }
-            // a row past the last position addresses row 0 (read only under MODE 1's mask,
-            // never written)
+            // a row past the last position addresses row 0 (its mask is read, nothing written)
             base[i] = live[i] ? (t * (n + 4) + j + 2) * kNnWidth : 0;
         }
         uint16_t mk[4][8];
-        if (MODE == 1) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int nt = 0; nt < 8; ++nt) mk[i][nt] = mask[base[i] + nt * 16 + r16];
-        }
+            for (int nt = 0; nt < 8; ++nt) mk[i][nt] = mask[base[i] + nt * 16 + r16];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (!live[i]) continue;
 #pragma unroll
             for (int nt = 0; nt < 8; ++nt) {
                 float v = acc[mt][nt][i];
-                if (MODE == 0) {
-                    v += bco[nt];
-                    v = v > 0.f ? v : 0.f;
-                } else {
-                    if (mk[i][nt] == 0 || (mk[i][nt] & 0x8000u)) v = 0.f;
-                }
+                if (mk[i][nt] == 0 || (mk[i][nt] & 0x8000u)) v = 0.f;
                 Y[base[i] + nt * 16 + r16] = bf16_bits_hw(v);
             }
         }
@@ -336,8 +322,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void n
 
 // ------------------------------------------------------------------------- fused inference
 
-// All four conv layers of one tile of kFuseTP positions of one tour in LDS, for prediction only
-// (training keeps every layer's output for the backward pass). The input tile carries a halo
+// All four conv layers of one tile of TP positions of one tour in LDS. For training every layer's
+// output is also stored, for the backward pass: from LDS, 16 bytes a thread, once the layer is
+// complete there. The input tile carries a halo
 // of 8 rows (2 per layer); layer l's output row r is position j0 - 6 + 2l + r, and rows at
 // positions outside the tour are set to zero, which is the zero padding of the next layer. Each
 // layer is a GEMM over 16-row m-tiles x 128 channels: wave p owns channel pair p (tiles 2p and
@@ -347,18 +334,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void n
 // with its first fragments already loaded and the K loop has no barrier (one per layer). The
 // input tile shares its LDS with the second hidden buffer, which is first written by layer 2,
 // after every wave has passed layer 2's barrier and so finished reading the input. The last
-// layer rounds its outputs to bfloat16 (as the layer-by-layer path stores them) and sums them
-// per channel over the tile's positions, in a fixed order, into zpart[t][tile][co].
-constexpr int kFuseTP = 128;                       // output positions per tile
-constexpr int kFuseMT = (kFuseTP + 12 + 15) / 16;  // m-tiles of layers 1..3 (TP + 12, 8, 4 rows)
-constexpr int kFuseRows = kFuseMT * 16 + 4;        // rows of an LDS buffer (taps read 4 past)
-constexpr int kFuseDepth = 2;                      // K blocks of weight fragments in flight
+// layer rounds its outputs to bfloat16 and sums them per channel over each 64 positions, in a fixed
+// order, into zpart[t][position / 64][co]: the same bits for either tile length.
+// TP = 128 where the tiles fill the chip; 64, with twice the weight reads a position, where they leave
+// compute units idle: calls of 10 tours of 26 positions took 34 us with it and 44 before, of 100 of
+// 203 positions 42 and 47, of 64 of 1000 55 and 60 (the feature flag's clearing and copy, which went
+// with the same change, are 6 of each).
+// For training, storing costs little: 64 us for 128 tours of 1000 (50 without), where a kernel per
+// layer and one for the pooled mean took 143.
+constexpr int fuse_mt(int tp) { return (tp + 12 + 15) / 16; }  // m-tiles of layers 1..3 (TP + 12, 8, 4 rows)
+constexpr int fuse_rows(int tp) { return fuse_mt(tp) * 16 + 4; }  // rows of an LDS buffer (taps read 4 past)
+constexpr int kFuseDepth = 2;                      // K blocks of weight fragments in flight (3, 6
+                                                   // and 10 measured the same, for either tile)
 constexpr int kFuseThreads = 256;                  // four waves, one per channel pair
 constexpr int kFuseOcc = 2;                        // waves per SIMD the register budget allows
 constexpr int kFuseK1 = 64;  // layer 1's K: 5 taps x 8 features, zero-padded to 2 blocks of 32
 constexpr int kFuseStrideX = kNnCi0 + 8;    // bf16 per input row (16 bytes of padding)
 constexpr int kFuseStrideH = kNnWidth + 8;  // bf16 per hidden row (16 bytes of padding)
-static_assert(kFuseTP % 16 == 0, "the last layer covers the tile in whole m-tiles");
 static_assert(kNnFeatures == 8 && kNnTaps * kNnFeatures <= kFuseK1,
               "a tap's features are one 16-byte fragment; the taps fit layer 1's packed K");
 static_assert(kFuseDepth >= 1 && kFuseDepth <= kFuseK1 / 32,
@@ -396,12 +388,12 @@ __device__ __forceinline__ void fuse_frag(const uint16_t *Wg, int cp, int kb, bf
 // The MC m-tiles of one layer for channel pair cp. Fragment kb of this layer
 // sits in ring slot (R0 + kb) % depth; the slot it frees is refilled with the fragment depth
 // blocks later in the stream, which is in the next layer (weights Wn, CIN input channels; none
-// when CIN == 0) near the end. Without POOL the outputs go to `out`; with POOL, sum[h] receives
-// this lane's share of the channel sums of tile 2cp + h (its 4 rows of each m-tile).
-template <int CI, int MC, int R0, int CIN, bool POOL>
+// when CIN == 0) near the end. The outputs go to `out` (OUT); with POOL, sum[g][h] receives this
+// lane's share of the channel sums of tile 2cp + h over m-tiles 4g .. 4g + 3 (its 4 rows of each).
+template <int CI, int MC, int R0, int CIN, bool POOL, bool OUT, int NG>
 __device__ __forceinline__ void fused_part(const uint16_t *in, uint16_t *out, const uint16_t *Wt,
                                            const uint16_t *Wn, const float *bias, int pos0,
-                                           int n, int cp, FuseRing &ring, float (&sum)[2])
+                                           int n, int cp, FuseRing &ring, float (&sum)[NG][2])
 {
     constexpr int K = fuse_k(CI);
     constexpr int KB = K / 32;
@@ -472,11 +464,13 @@ __device__ __forceinline__ void fused_part(const uint16_t *in, uint16_t *out, co
                 }
                 const uint32_t p01 = bf16x2_bits(v[0], v[1]), p23 = bf16x2_bits(v[2], v[3]);
                 if (POOL) {
-                    sum[h] += __uint_as_float(p01 << 16);
-                    sum[h] += __uint_as_float(p01 & 0xFFFF0000u);
-                    sum[h] += __uint_as_float(p23 << 16);
-                    sum[h] += __uint_as_float(p23 & 0xFFFF0000u);
-                } else {
+                    float &z = sum[mt / 4][h];
+                    z += __uint_as_float(p01 << 16);
+                    z += __uint_as_float(p01 & 0xFFFF0000u);
+                    z += __uint_as_float(p23 << 16);
+                    z += __uint_as_float(p23 & 0xFFFF0000u);
+                }
+                if (OUT) {
                     uint16_t *o = out + r0 * kFuseStrideH + co;
                     o[0] = (uint16_t)p01;
                     o[kFuseStrideH] = (uint16_t)(p01 >> 16);
@@ -492,78 +486,115 @@ __device__ __forceinline__ void fused_part(const uint16_t *in, uint16_t *out, co
         epilogue(std::true_type{});
 }
 
-// One layer over MT m-tiles (see fused_part). With POOL the tile's channel sums go to
-// pool_out[128].
-template <int CI, int MT, int R0, int CIN, bool POOL>
+// One layer over MT m-tiles (see fused_part). With POOL the channel sums of each 64 positions go to
+// pool_out[MT / 4][128] (the first `groups` of them).
+template <int CI, int MT, int R0, int CIN, bool POOL, bool OUT>
 __device__ __forceinline__ void fused_layer(const uint16_t *in, uint16_t *out,
                                             const uint16_t *Wt, const uint16_t *Wn,
                                             const float *bias, int pos0, int n, float *pool_out,
-                                            FuseRing &ring)
+                                            int groups, FuseRing &ring)
 {
+    constexpr int NG = (MT + 3) / 4;
     const int cp = threadIdx.x >> 6;
-    float sum[2] = {0.f, 0.f};
+    float sum[NG][2] = {};
     __syncthreads();  // the input rows of this layer are in LDS
-    fused_part<CI, MT, R0, CIN, POOL>(in, out, Wt, Wn, bias, pos0, n, cp, ring, sum);
+    fused_part<CI, MT, R0, CIN, POOL, OUT, NG>(in, out, Wt, Wn, bias, pos0, n, cp, ring, sum);
     if (POOL) {
         // the 4 row groups of a column, added in a fixed order
         const int lane = threadIdx.x & 63;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            float v = sum[h];
-            v += __shfl_xor(v, 16, 64);
-            v += __shfl_xor(v, 32, 64);
-            if (lane < 16) pool_out[(2 * cp + h) * 16 + lane] = v;
-        }
+        for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                float v = sum[g][h];
+                v += __shfl_xor(v, 16, 64);
+                v += __shfl_xor(v, 32, 64);
+                if (lane < 16 && g < groups) pool_out[g * kNnWidth + (2 * cp + h) * 16 + lane] = v;
+            }
     }
 }
 
+// The tile's own rows of a layer's output, from LDS row r0 on, to H [n + 4][128] of the tour.
+template <int TP>
+__device__ __forceinline__ void fused_store(const uint16_t *buf, int r0, int j0, int n, uint16_t *H)
+{
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < TP * 16 / kFuseThreads; ++u) {
+        const int e = u * kFuseThreads + (int)threadIdx.x, r = e >> 4, c = (e & 15) * 8;
+        if (j0 + r < n)
+            *reinterpret_cast<u16x8 *>(H + (long long)(j0 + r + 2) * kNnWidth + c) =
+                *reinterpret_cast<const u16x8 *>(buf + (r0 + r) * kFuseStrideH + c);
+    }
+}
+
+// TRAIN: X is the padded [T][n + 4][32] input, and H takes every layer's output; else X is packed.
+template <int TP, bool TRAIN>
 __global__ __launch_bounds__(kFuseThreads) __attribute__((amdgpu_waves_per_eu(kFuseOcc)))
 void nn_fwd_fused_kernel(const uint16_t *X, NnWeights w, const float *P, int32_t n,
-                         int32_t tiles, float *zpart)
+                         int32_t tiles, float *zpart, NnHidden H)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t ha[kFuseRows * kFuseStrideH];
-    __shared__ __attribute__((aligned(16))) uint16_t hb[kFuseRows * kFuseStrideH];
+    static_assert(TP % 64 == 0, "whole groups of 64 pooled positions");
+    constexpr int MT = fuse_mt(TP), ROWS = fuse_rows(TP);
+    __shared__ __attribute__((aligned(16))) uint16_t ha[ROWS * kFuseStrideH];
+    __shared__ __attribute__((aligned(16))) uint16_t hb[ROWS * kFuseStrideH];
     uint16_t *xs = hb;  // the input tile, until layer 2 writes hb
     const int tid = threadIdx.x;
     const int t = blockIdx.x / tiles, k = blockIdx.x - t * tiles;
-    const int j0 = k * kFuseTP;
+    const int j0 = k * TP;
     const int cp = tid >> 6;
     constexpr int KB1 = kFuseK1 / 32, KBH = kNnTaps * kNnWidth / 32;
     constexpr int D = kFuseDepth;
     FuseRing ring;
 #pragma unroll
     for (int d = 0; d < D; ++d) fuse_frag<kFuseK1>(w.g[0], cp, d, ring.b0[d], ring.b1[d]);
-    // input rows: position j0 - 8 + r (zero outside the tour), its 8 features from the packed
-    // [T][n][8] input (16 bytes)
-    for (int r = tid; r < kFuseRows; r += kFuseThreads) {
+    // input rows: position j0 - 8 + r (zero outside the tour), its 8 features (16 bytes)
+    for (int r = tid; r < ROWS; r += kFuseThreads) {
         const int pos = j0 - 8 + r;
         u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
         if (pos >= 0 && pos < n)
-            v = *reinterpret_cast<const u16x8 *>(X + ((long long)t * n + pos) * kNnFeatures);
+            v = *reinterpret_cast<const u16x8 *>(
+                X + (TRAIN ? ((long long)t * (n + 4) + pos + 2) * kNnCi0
+                           : ((long long)t * n + pos) * kNnFeatures));
         *reinterpret_cast<u16x8 *>(xs + r * kFuseStrideX) = v;
     }
-    fused_layer<kNnCi0, kFuseMT, 0, kNnWidth, false>(xs, ha, w.g[0], w.g[1], P + nn_off_b(0),
-                                                      j0 - 6, n, nullptr, ring);
-    fused_layer<kNnWidth, kFuseMT, KB1 % D, kNnWidth, false>(ha, hb, w.g[1], w.g[2],
-                                                             P + nn_off_b(1), j0 - 4, n, nullptr,
-                                                             ring);
-    fused_layer<kNnWidth, kFuseMT, (KB1 + KBH) % D, kNnWidth, false>(
-        hb, ha, w.g[2], w.g[3], P + nn_off_b(2), j0 - 2, n, nullptr, ring);
-    fused_layer<kNnWidth, kFuseTP / 16, (KB1 + 2 * KBH) % D, 0, true>(
-        ha, nullptr, w.g[3], nullptr, P + nn_off_b(3), j0, n,
-        zpart + ((long long)t * tiles + k) * kNnWidth, ring);
+    const long long tour = (long long)t * (n + 4) * kNnWidth;
+    fused_layer<kNnCi0, MT, 0, kNnWidth, false, true>(xs, ha, w.g[0], w.g[1], P + nn_off_b(0),
+                                                      j0 - 6, n, nullptr, 0, ring);
+    if (TRAIN) fused_store<TP>(ha, 6, j0, n, H.h[0] + tour);
+    fused_layer<kNnWidth, MT, KB1 % D, kNnWidth, false, true>(ha, hb, w.g[1], w.g[2],
+                                                              P + nn_off_b(1), j0 - 4, n, nullptr,
+                                                              0, ring);
+    if (TRAIN) fused_store<TP>(hb, 4, j0, n, H.h[1] + tour);
+    fused_layer<kNnWidth, MT, (KB1 + KBH) % D, kNnWidth, false, true>(
+        hb, ha, w.g[2], w.g[3], P + nn_off_b(2), j0 - 2, n, nullptr, 0, ring);
+    if (TRAIN) fused_store<TP>(ha, 2, j0, n, H.h[2] + tour);
+    const int groups = (n + 63) / 64;  // of the whole tour
+    fused_layer<kNnWidth, TP / 16, (KB1 + 2 * KBH) % D, 0, true, TRAIN>(
+        ha, hb, w.g[3], nullptr, P + nn_off_b(3), j0, n,
+        zpart + ((long long)t * groups + j0 / 64) * kNnWidth, groups - j0 / 64, ring);
+    if (TRAIN) fused_store<TP>(hb, 0, j0, n, H.h[3] + tour);
 }
 
-// Head from the per-tile sums: z[c] = (sum over tiles, in order) / n, then as nn_head_fwd_kernel.
+// Head from the sums of 64 positions each: z[c] = (their sum, in order) / n, a = Wa z + ba,
+// u = relu(a), y = wb . u + bb, pred = y * scale + shift. One workgroup per tour. The first one also
+// hands the flag that the feature kernels raised to the host (pinned memory) and clears it: a
+// clearing and a copy of their own were 8 us of a 46 us call.
 __global__ __launch_bounds__(128) void nn_head_pool_kernel(const float *zpart, int32_t tiles,
                                                            int32_t n, const float *P, float *z,
                                                            float *a, float *y, float *pred,
-                                                           double shift, double scale)
+                                                           double shift, double scale,
+                                                           int32_t *err, int32_t *host_err)
 {
     __shared__ float zs[kNnWidth];
     __shared__ float red[kNnWidth];
     const int t = blockIdx.x, c = threadIdx.x;
+    if (host_err && t == 0 && c == 0) {
+        *host_err = *err;
+        *err = 0;
+    }
     float sum = 0.f;
+#pragma unroll 4
     for (int k = 0; k < tiles; ++k) sum += zpart[((long long)t * tiles + k) * kNnWidth + c];
     const float zc = sum / (float)n;
     zs[c] = zc;
@@ -586,69 +617,7 @@ __global__ __launch_bounds__(128) void nn_head_pool_kernel(const float *zpart, i
     }
 }
 
-// ------------------------------------------------------------------------- pool and head
-
-// One workgroup of 256 threads per tour: z = mean over positions of H4, a = Wa z + ba,
-// u = relu(a), y = wb . u + bb, pred = y * scale + shift. Thread (r, g) = (tid / 16, tid % 16)
-// sums channels 8g .. 8g+7 over positions r, r + 16, ... with 16-byte loads; the 16 partial
-// sums of a channel are then added in order r = 0..15 (a fixed order: bitwise reproducible).
-__global__ __launch_bounds__(256) void nn_head_fwd_kernel(const uint16_t *H4, int32_t T,
-                                                          int32_t n, const float *P, float *z,
-                                                          float *a, float *y, float *pred,
-                                                          double shift, double scale)
-{
-    __shared__ float part[16][kNnWidth];
-    __shared__ float zs[kNnWidth];
-    __shared__ float red[kNnWidth];
-    const int t = blockIdx.x, tid = threadIdx.x;
-    const int r = tid >> 4, g = tid & 15;
-    const u16x8 *h = reinterpret_cast<const u16x8 *>(H4 + ((long long)t * (n + 4) + 2) * kNnWidth) + g;
-    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    int j = r;
-    for (; j + 48 < n; j += 64) {  // rows j, j + 16, j + 32, j + 48: loads first, adds in order
-        u16x8 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = h[(long long)(j + 16 * u) * (kNnWidth / 8)];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) s[e] += bf16_to_f32(v[u][e]);
-    }
-    for (; j < n; j += 16) {
-        const u16x8 v = h[(long long)j * (kNnWidth / 8)];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s[e] += bf16_to_f32(v[e]);
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) part[r][8 * g + e] = s[e];
-    __syncthreads();
-    const int c = tid;
-    if (c < kNnWidth) {
-        float sum = 0.f;
-        for (int k = 0; k < 16; ++k) sum += part[k][c];
-        const float zc = sum / (float)n;
-        zs[c] = zc;
-        z[(long long)t * kNnWidth + c] = zc;
-    }
-    __syncthreads();
-    if (c < kNnWidth) {
-        const float *Wa = P + kNnOffWa;
-        float acc = P[kNnOffBa + c];
-        for (int i = 0; i < kNnWidth; ++i) acc += Wa[c * kNnWidth + i] * zs[i];
-        a[(long long)t * kNnWidth + c] = acc;
-        red[c] = P[kNnOffWb + c] * (acc > 0.f ? acc : 0.f);
-    }
-    __syncthreads();
-    for (int off = 64; off > 0; off >>= 1) {
-        if (c < off) red[c] += red[c + off];
-        __syncthreads();
-    }
-    if (c == 0) {
-        const float yt = red[0] + P[kNnOffBb];
-        y[t] = yt;
-        if (pred) pred[t] = (float)((double)yt * scale + shift);
-    }
-}
+// ------------------------------------------------------------------------- head, backward
 
 // Loss and head backward of a batch: dy_t = 2 (y_t - yhat_t) / T with yhat = (label - shift) /
 // scale; da = dy wb [a > 0]; dz = Wa^T da. One workgroup per tour; loss terms per tour.
@@ -678,17 +647,33 @@ __global__ __launch_bounds__(128) void nn_head_bwd_kernel(const float *labels, i
     dz[(long long)t * kNnWidth + c] = s;
 }
 
-// Head parameter gradients, summed over the batch in tour order. Grid kNnWidth + 1 workgroups of
-// 128: workgroup o < 128 writes gWa[o][*] and gba[o]; the last writes gwb and gbb.
+// Head parameter gradients and the loss, summed over the batch in tour order. Grid kNnWidth + 2
+// workgroups of 128: workgroup o < 128 writes gWa[o][*] and gba[o]; the next gwb and gbb; the last
+// *loss = (sum of terms, in order) / T, 128 terms at a time from LDS (one thread reading them from
+// memory was a launch of 6.5 us).
 // The sums run in tour order; the loads of 8 tours are issued before their products.
 __global__ __launch_bounds__(128) void nn_head_grad_kernel(int32_t T, const float *__restrict__ z,
                                                            const float *__restrict__ a,
                                                            const float *__restrict__ da,
                                                            const float *__restrict__ dy,
+                                                           const float *__restrict__ terms,
+                                                           float *__restrict__ loss,
                                                            float *__restrict__ G)
 {
+    __shared__ float part[128];
     const int o = blockIdx.x, i = threadIdx.x;
-    if (o < kNnWidth) {
+    if (o == kNnWidth + 1) {
+        float s = 0.f;
+        for (int t0 = 0; t0 < T; t0 += 128) {
+            part[i] = t0 + i < T ? terms[t0 + i] : 0.f;
+            __syncthreads();
+            if (i == 0) {
+                for (int k = 0; k < 128; ++k) s += part[k];  // + 0.0 past the last: no change
+            }
+            __syncthreads();
+        }
+        if (i == 0) *loss = s / (float)T;
+    } else if (o < kNnWidth) {
         float s = 0.f, sb = 0.f;
         int t = 0;
         for (; t + 8 <= T; t += 8) {
@@ -737,27 +722,36 @@ __global__ __launch_bounds__(128) void nn_head_grad_kernel(int32_t T, const floa
     }
 }
 
-// dP4[t][j][c] = bf16(dz[t][c] / n) where H4 > 0, else 0 (interior rows only); a thread takes
-// 8 consecutive channels of one position (16-byte loads and stores)
+// dP4[t][j][c] = bf16(dz[t][c] / n) where H4 > 0, else 0 (interior rows only). A workgroup takes 128
+// positions of a tour, a thread 8 consecutive channels of every 16th (16-byte loads and stores,
+// all requested before the first is used): the quotients, once per thread. Bound by the 66 MB it
+// moves for 128 tours of 1000: 10.8 us, 25.5 with a division per value.
 __global__ __launch_bounds__(256) void nn_dp4_kernel(const float *__restrict__ dz,
-                                                     const uint16_t *__restrict__ H4, int32_t T,
-                                                     int32_t n, uint16_t *__restrict__ dP)
+                                                     const uint16_t *__restrict__ H4, int32_t n,
+                                                     uint16_t *__restrict__ dP)
 {
-    const long long e = (long long)blockIdx.x * 256 + threadIdx.x;  // (position, channel octet)
-    if (e >= (long long)T * n * (kNnWidth / 8)) return;
-    const int c0 = (int)(e % (kNnWidth / 8)) * 8;
-    const long long m = e / (kNnWidth / 8);
-    const long long t = m / n, j = m - t * n;
-    const long long idx = (t * (n + 4) + j + 2) * kNnWidth + c0;
-    const u16x8 h = *reinterpret_cast<const u16x8 *>(H4 + idx);
-    const float *dzt = dz + t * kNnWidth + c0;
-    u16x8 out;
+    const int t = blockIdx.y, c0 = (threadIdx.x & 15) * 8;
+    const int j0 = blockIdx.x * 128 + (threadIdx.x >> 4);
+    const long long base = ((long long)t * (n + 4) + 2) * kNnWidth + c0;
+    u16x8 h[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const bool on = h[k] != 0 && !(h[k] & 0x8000u);
-        out[k] = on ? bf16_bits_f32(dzt[k] / (float)n) : (uint16_t)0;
+    for (int u = 0; u < 8; ++u) {
+        const int j = j0 + 16 * u < n ? j0 + 16 * u : n - 1;
+        h[u] = *reinterpret_cast<const u16x8 *>(H4 + base + (long long)j * kNnWidth);
     }
-    *reinterpret_cast<u16x8 *>(dP + idx) = out;
+    uint16_t g[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        g[k] = bf16_bits_f32(dz[(long long)t * kNnWidth + c0 + k] / (float)n);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        const int j = j0 + 16 * u;
+        u16x8 out;
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            out[k] = h[u][k] != 0 && !(h[u][k] & 0x8000u) ? g[k] : (uint16_t)0;
+        if (j < n) *reinterpret_cast<u16x8 *>(dP + base + (long long)j * kNnWidth) = out;
+    }
 }
 
 // ------------------------------------------------------------------------- weight gradients
@@ -952,7 +946,7 @@ __global__ __launch_bounds__(256) void nn_adam_kernel(float *P, float *m, float 
     P[e] -= lr * (mm / bc1) / (sqrtf(vv / bc2) + 1e-8f);
 }
 
-// bf16 copies of the conv weights: Wf_l[co][tap * CI + ci] (forward) and, for layers 2..4,
+// bf16 copies of the conv weights: fragment order (forward) and, for layers 2..4,
 // Wb_l[ci][tap' * 128 + co] = W_l[4 - tap'][ci][co] (backward data). One thread per weight.
 // Position of weight (co, k) of a layer with K = 32 KB in MFMA fragment order: the 16-byte
 // B operand of lane kq * 16 + r16 for channel tile 2 cp + h and K block kb holds
@@ -973,7 +967,6 @@ __global__ __launch_bounds__(256) void nn_pack_kernel(const float *P, NnWeights 
         const int tap = e / (kNnCi0 * kNnWidth), r = e % (kNnCi0 * kNnWidth);
         const int ci = r / kNnWidth, co = r % kNnWidth;
         const uint16_t b = bf16_bits_f32(P[nn_off_w(0) + e]);
-        w.f[0][co * (kNnTaps * kNnCi0) + tap * kNnCi0 + ci] = b;
         if (ci < kNnFeatures)  // the fused kernel's packed K (the rest of w.g[0] stays zero)
             w.g[0][nn_frag_index(co, tap * kNnFeatures + ci, kFuseK1 / 32)] = b;
         return;
@@ -984,7 +977,6 @@ __global__ __launch_bounds__(256) void nn_pack_kernel(const float *P, NnWeights 
     const int tap = r0 / (kNnWidth * kNnWidth), r = r0 % (kNnWidth * kNnWidth);
     const int ci = r / kNnWidth, co = r % kNnWidth;
     const uint16_t b = bf16_bits_f32(P[nn_off_w(l) + r0]);
-    w.f[l][co * (kNnTaps * kNnWidth) + tap * kNnWidth + ci] = b;
     w.b[l][ci * (kNnTaps * kNnWidth) + (kNnTaps - 1 - tap) * kNnWidth + co] = b;
     w.g[l][nn_frag_index(co, tap * kNnWidth + ci, kNnTaps * kNnWidth / 32)] = b;
 }
@@ -1335,14 +1327,6 @@ __global__ __launch_bounds__(256) void nn_moves_kernel(const int32_t *cur, const
     }
 }
 
-// out[0] = (sum of terms[0..T-1], in order) / T
-__global__ void nn_loss_kernel(const float *terms, int32_t T, float *out)
-{
-    float s = 0.f;
-    for (int t = 0; t < T; ++t) s += terms[t];
-    out[0] = s / (float)T;
-}
-
 // ------------------------------------------------------------------------- launchers
 
 hipError_t nn_launch_gather(const int32_t *src, const float *lab, const int32_t *idx, int32_t B,
@@ -1370,12 +1354,6 @@ hipError_t nn_launch_moves(const int32_t *cur, const int32_t *moves, int32_t cou
     return hipGetLastError();
 }
 
-hipError_t nn_launch_loss(const float *terms, int32_t T, float *out, hipStream_t st)
-{
-    hipLaunchKernelGGL(nn_loss_kernel, dim3(1), dim3(1), 0, st, terms, T, out);
-    return hipGetLastError();
-}
-
 static inline unsigned grid_of(long long work, int per) { return (unsigned)((work + per - 1) / per); }
 
 hipError_t nn_launch_dstats(const int16_t *demand, int64_t ld, int64_t S, int32_t N, double *musd,
@@ -1394,66 +1372,58 @@ hipError_t nn_launch_features(const NnInstance &in, const int32_t *tours, int32_
     return hipGetLastError();
 }
 
-hipError_t nn_launch_conv(int ci, int mode, const uint16_t *X, const uint16_t *Wt,
-                          const float *bias, const uint16_t *mask, uint16_t *Y, int32_t T,
-                          int32_t n, hipStream_t st)
+hipError_t nn_launch_conv_back(const uint16_t *X, const uint16_t *Wt, const uint16_t *mask,
+                               uint16_t *Y, int32_t T, int32_t n, hipStream_t st)
 {
-    const dim3 g(grid_of((long long)T * n, 256)), b(256);
-    if (ci == kNnCi0 && mode == 0)
-        hipLaunchKernelGGL((nn_conv_kernel<kNnCi0, 0>), g, b, 0, st, X, Wt, bias, mask, Y, T, n);
-    else if (ci == kNnWidth && mode == 0)
-        hipLaunchKernelGGL((nn_conv_kernel<kNnWidth, 0>), g, b, 0, st, X, Wt, bias, mask, Y, T, n);
-    else if (ci == kNnWidth && mode == 1)
-        hipLaunchKernelGGL((nn_conv_kernel<kNnWidth, 1>), g, b, 0, st, X, Wt, bias, mask, Y, T, n);
-    else
-        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(nn_conv_kernel, dim3(grid_of((long long)T * n, 256)), dim3(256), 0, st, X, Wt,
+                       mask, Y, T, n);
     return hipGetLastError();
 }
 
-int32_t nn_fused_tiles(int32_t n) { return (n + kFuseTP - 1) / kFuseTP; }
+int32_t nn_pool_groups(int32_t n) { return (n + 63) / 64; }
 
 hipError_t nn_launch_fwd_fused(const uint16_t *X, const NnWeights &w, const float *P, int32_t T,
-                               int32_t n, float *zpart, hipStream_t st)
+                               int32_t n, float *zpart, const NnHidden *H, hipStream_t st)
 {
-    const int32_t tiles = nn_fused_tiles(n);
-    hipLaunchKernelGGL(nn_fwd_fused_kernel, dim3((unsigned)((long long)T * tiles)),
-                       dim3(kFuseThreads), 0, st, X, w, P, n, tiles, zpart);
+    // 128-position tiles from 512 of them on (two on every compute unit)
+    const long long t128 = (long long)T * ((n + 127) / 128);
+    const int32_t tiles = t128 >= 512 ? (n + 127) / 128 : (n + 63) / 64;
+    const dim3 g((unsigned)((long long)T * tiles)), b(kFuseThreads);
+    const NnHidden h = H ? *H : NnHidden{};
+    if (t128 >= 512 && H)
+        hipLaunchKernelGGL((nn_fwd_fused_kernel<128, true>), g, b, 0, st, X, w, P, n, tiles, zpart, h);
+    else if (t128 >= 512)
+        hipLaunchKernelGGL((nn_fwd_fused_kernel<128, false>), g, b, 0, st, X, w, P, n, tiles, zpart, h);
+    else if (H)
+        hipLaunchKernelGGL((nn_fwd_fused_kernel<64, true>), g, b, 0, st, X, w, P, n, tiles, zpart, h);
+    else
+        hipLaunchKernelGGL((nn_fwd_fused_kernel<64, false>), g, b, 0, st, X, w, P, n, tiles, zpart, h);
     return hipGetLastError();
 }
 
 hipError_t nn_launch_head_pool(const float *zpart, int32_t T, int32_t n, const float *P, float *z,
                                float *a, float *y, float *pred, double shift, double scale,
-                               hipStream_t st)
+                               int32_t *err, int32_t *host_err, hipStream_t st)
 {
-    hipLaunchKernelGGL(nn_head_pool_kernel, dim3(T), dim3(128), 0, st, zpart,
-                       nn_fused_tiles(n), n, P, z, a, y, pred, shift, scale);
-    return hipGetLastError();
-}
-
-hipError_t nn_launch_head_fwd(const uint16_t *H4, int32_t T, int32_t n, const float *P, float *z,
-                              float *a, float *y, float *pred, double shift, double scale,
-                              hipStream_t st)
-{
-    hipLaunchKernelGGL(nn_head_fwd_kernel, dim3(T), dim3(256), 0, st, H4, T, n, P, z, a, y, pred,
-                       shift, scale);
+    hipLaunchKernelGGL(nn_head_pool_kernel, dim3(T), dim3(128), 0, st, zpart, nn_pool_groups(n), n,
+                       P, z, a, y, pred, shift, scale, err, host_err);
     return hipGetLastError();
 }
 
 hipError_t nn_launch_head_bwd(const float *labels, int32_t T, int32_t n, const float *P,
                               const float *z, const float *a, const float *y, double shift,
-                              double scale, float *da, float *dz, float *dy, float *loss_terms,
+                              double scale, float *da, float *dz, float *dy, float *loss_terms, float *loss,
                               const uint16_t *H4, uint16_t *dP4, float *G, hipStream_t st)
 {
     hipLaunchKernelGGL(nn_head_bwd_kernel, dim3(T), dim3(128), 0, st, labels, T, P, a, y, shift,
                        scale, da, dz, dy, loss_terms);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(nn_head_grad_kernel, dim3(kNnWidth + 1), dim3(128), 0, st, T, z, a, da, dy,
-                       G);
+    hipLaunchKernelGGL(nn_head_grad_kernel, dim3(kNnWidth + 2), dim3(128), 0, st, T, z, a, da, dy,
+                       loss_terms, loss, G);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(nn_dp4_kernel, dim3(grid_of((long long)T * n * (kNnWidth / 8), 256)),
-                       dim3(256), 0, st, dz, H4, T, n, dP4);
+    hipLaunchKernelGGL(nn_dp4_kernel, dim3(grid_of(n, 128), T), dim3(256), 0, st, dz, H4, n, dP4);
     return hipGetLastError();
 }
 
