@@ -155,6 +155,7 @@ struct split_ctx {
     bool have_call = false;
     int64_t last_S = 0;
     int32_t last_T = 0;
+    int32_t last_parts = 0;  // nonzero: h_stats holds this many parts of one tour's result
 
     // timing of the dominant kernel
     bool timing = false;
@@ -392,6 +393,22 @@ void fill_stats(const TourResult &d, int64_t S, split_stats *out)
     out->n_fallback = d.ovf_count;
 }
 
+// The latest call's results (its end has been waited for): adds up the parts of a small evaluation.
+const TourResult *last_results(split_ctx *ctx)
+{
+    TourResult &r = ctx->h_stats[0];
+    for (int32_t k = 1; k < ctx->last_parts; ++k) {
+        const TourResult &x = ctx->h_stats[k];
+        r.sum += x.sum;
+        r.sq_l32 += x.sq_l32;
+        r.sq_h32 += x.sq_h32;
+        r.err_demand |= x.err_demand;
+        r.ovf_count += x.ovf_count;
+    }
+    ctx->last_parts = 0;
+    return ctx->h_stats;
+}
+
 // Per-tour statistics and status of T result blocks; SPLIT_E_DEMAND names the first bad tour.
 split_status report(split_ctx *ctx, const TourResult *h, int32_t T, int64_t S, split_stats *stats,
                     int32_t *tour_status)
@@ -618,6 +635,46 @@ split_status enqueue_kernels(split_ctx *ctx, const Instance &in, const EvalBuffe
     return SPLIT_OK;
 }
 
+// One short tour in one launch. The tour travels with the arguments; a slot's event marks the end.
+split_status eval_small(split_ctx *ctx, const int32_t *tour, int32_t n, const Plan &p,
+                        const int16_t *demand, int64_t S, int64_t ld, int32_t Q, int32_t *cost,
+                        hipStream_t stream)
+{
+    const int32_t parts = (int32_t)((S + kSmallPer - 1) / kSmallPer);
+    split_status st = ensure_host(ctx, 1, parts);
+    if (st != SPLIT_OK) return st;
+    SmallArgs a;
+    a.demand = reinterpret_cast<const uint16_t *>(demand);
+    a.ld = ld;
+    a.S = S;
+    a.Q = Q;
+    a.n = n;
+    a.N = ctx->inst.N;
+    a.kind = ctx->inst.kind;
+    a.xy = ctx->inst.d_xy;
+    a.dist = ctx->inst.d_dist;
+    a.cost = cost;
+    a.out = ctx->h_stats;
+    a.count_bound = p.form == SPLIT_FORM_LANE ? 1 : 0;
+    for (int32_t k = 0; k < kSmallN; ++k) a.tour[k] = tour[k < n ? k : n - 1];
+    const int slot = ctx->stage;
+    ctx->stage = (ctx->stage + 1) % kStages;
+    hipEvent_t stop = nullptr;
+    st = timing_begin(ctx, stream, &stop);
+    if (st != SPLIT_OK) return st;
+    ctx->tname = p.form == SPLIT_FORM_LANE ? lane_kernel_name() : wave_kernel_name();
+    HIP_TRY(ctx, launch_small(a, stream));
+    if (stop) HIP_TRY(ctx, hipEventRecord(stop, stream));
+    HIP_TRY(ctx, hipEventRecord(ctx->stage_ev[slot], stream));
+    ctx->stage_ev_used[slot] = true;
+    ctx->last_ev = ctx->stage_ev[slot];
+    ctx->have_call = true;
+    ctx->last_S = S;
+    ctx->last_T = 1;
+    ctx->last_parts = parts;
+    return SPLIT_OK;
+}
+
 // The common path of split_eval and split_eval_batch on the context's own buffers.
 split_status eval_batch(split_ctx *ctx, const char *who, const int32_t *tours,
                         const int64_t *tour_ptr, int32_t T, const int16_t *demand, int64_t S,
@@ -636,6 +693,14 @@ split_status eval_batch(split_ctx *ctx, const char *who, const int32_t *tours,
     const StageLayout L = stage_layout(T, bi.total_n);
     const Plan p = make_plan(ctx, ctx->tuning, S, ld, Q, T, bi.maxn, bi.max_id,
                              bi.minn == bi.maxn, ctx->inst.max_arc);
+    // A short tour over few scenarios, all choices left to the library: one launch instead of three,
+    // which take longer than the work (20 customers, S = 1000: 27.7 us a call against 40.5; the bounds
+    // keep the scan of 32 predecessors and the 128 parts to add up small). Short arcs keep every
+    // suffix offset within 16 bits, so only the demand bound can count towards n_fallback.
+    const split_tuning &tu = ctx->tuning;
+    if (T == 1 && bi.maxn <= kSmallN && S <= kSmallS && ctx->inst.max_arc <= kClassMaxArc &&
+        tu.form == SPLIT_FORM_AUTO && tu.lane_per_cu == 0 && tu.lane_block == 0 && tu.wave_grid == 0)
+        return eval_small(ctx, tours, bi.maxn, p, demand, S, ld, Q, cost, stream);
     // on the device the header ends before the tours
     const SumSlots ss = sum_slots(p.form, T, S);
     st = ensure_buffers(ctx, ctx->buf, T, bi.total_n, (int64_t)L.off_tours,
@@ -673,6 +738,7 @@ split_status eval_batch(split_ctx *ctx, const char *who, const int32_t *tours,
     ctx->have_call = true;
     ctx->last_S = S;
     ctx->last_T = T;
+    ctx->last_parts = 0;
     return SPLIT_OK;
 }
 
@@ -960,7 +1026,7 @@ split_status split_batch_stats_get(split_ctx *ctx, split_stats *stats, int32_t *
     if (!ctx->have_call) return fail(ctx, SPLIT_E_INVAL, "split_batch_stats_get: no evaluation yet");
     DeviceGuard g(ctx->device);
     HIP_TRY(ctx, hipEventSynchronize(ctx->last_ev));
-    return report(ctx, ctx->h_stats, ctx->last_T, ctx->last_S, stats, tour_status);
+    return report(ctx, last_results(ctx), ctx->last_T, ctx->last_S, stats, tour_status);
 }
 
 split_status split_stats_get(split_ctx *ctx, split_stats *stats)
@@ -970,7 +1036,7 @@ split_status split_stats_get(split_ctx *ctx, split_stats *stats)
     if (!ctx->have_call) return fail(ctx, SPLIT_E_INVAL, "split_stats_get: no evaluation yet");
     DeviceGuard g(ctx->device);
     HIP_TRY(ctx, hipEventSynchronize(ctx->last_ev));
-    const TourResult d = ctx->h_stats[0];
+    const TourResult d = last_results(ctx)[0];
     fill_stats(d, ctx->last_S, stats);
     if (d.err_demand)
         return fail(ctx, SPLIT_E_DEMAND,

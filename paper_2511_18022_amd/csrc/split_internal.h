@@ -159,9 +159,25 @@ struct EvalArgs {
     int32_t maxn;            // bound on the tour lengths (sizes the wave kernel's LDS)
 };
 
+// A whole evaluation of one short tour over few scenarios in one launch.
+constexpr int32_t kSmallN = 32;        // customers at most
+constexpr int64_t kSmallS = 32768;     // scenarios at most: 128 workgroups
+constexpr int32_t kSmallPer = 256;     // scenarios per workgroup
+struct SmallArgs {
+    const uint16_t *demand;
+    int64_t ld, S;
+    int32_t Q, n, N, kind;
+    const int32_t *xy, *dist;
+    int32_t *cost;                     // [S]
+    TourResult *out;                   // one per workgroup
+    int32_t count_bound;               // 1: count demands past the lane kernel's bound (n_fallback)
+    int32_t tour[kSmallN];             // past n: the last customer again
+};
+
 // Kernel launchers (split_kernels.hip). All are asynchronous on `stream`.
 hipError_t launch_prep(const PrepArgs &a, hipStream_t stream);
 hipError_t launch_lane(const EvalArgs &a, hipStream_t stream);
+hipError_t launch_small(const SmallArgs &a, hipStream_t stream);
 hipError_t launch_pair(const EvalArgs &a, hipStream_t stream);
 hipError_t launch_wave_all(const EvalArgs &a, hipStream_t stream);
 hipError_t launch_tail(const EvalArgs &a, hipStream_t stream);

@@ -17,6 +17,7 @@
 //                         left to the long kernel.
 //  split_pair_kernel      the lane kernel with two wavefronts per 64 scenarios, from both ends of the
 //                         tour, for launches of few work items.
+//  split_small_kernel     a whole evaluation of a short tour over few scenarios.
 //  split_tail_kernel      reports the sums; first the lane kernel's blocks over a history of 256 positions, for tours
 //                         whose windows outgrow the lane kernel's 64 and for the scenarios it
 //                         marks; what outgrows this history too is finished one scenario per
@@ -49,7 +50,8 @@ __device__ __forceinline__ int32_t dist_coords(const int32_t *xy, int u, int v)
     return (int32_t)(m - k * k > k ? k + 1 : k);
 }
 
-__device__ __forceinline__ int32_t arc_cost(const PrepArgs &a, int u, int v)
+template <class A>
+__device__ __forceinline__ int32_t arc_cost(const A &a, int u, int v)
 {
     if (a.kind == 0) return dist_coords(a.xy, u, v);
     return a.dist[(long long)u * (a.N + 1) + v];
@@ -1440,6 +1442,100 @@ __global__ __launch_bounds__(64) void split_tail_kernel(EvalArgs a)
     for (int t = 0; t < T; ++t) report_tour(a, t);
 }
 
+// ------------------------------------------------------------------------- small evaluations
+
+// One tour of at most kSmallN customers, one scenario per thread, in one launch: the tour comes with
+// the arguments, every workgroup computes the weights for itself, prefix loads and g stay in
+// registers, each state takes the minimum over its predecessors one by one (496 of them at most),
+// and every workgroup reports its part to pinned host memory, where the host adds up at most 128 of
+// them: with atomic sums, a count of the finished workgroups and the window scan in LDS the kernel
+// took 30 us. Bound by launch and memory latency: 20 customers, S = 1000 takes 7.6 us here.
+__global__ __launch_bounds__(kSmallPer) void split_small_kernel(SmallArgs a)
+{
+    __shared__ int32_t w[kSmallN + 1];
+    __shared__ CostSums part[kSmallPer / 64];
+    __shared__ int32_t flags[kSmallPer / 64][2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = a.n;
+    const long long scen = (long long)blockIdx.x * kSmallPer + tid;
+    const bool active = scen < a.S;
+    const int s32 = (int)min(scen, (long long)a.S - 1);
+    uint32_t q[kSmallN];
+#pragma unroll
+    for (int i = 0; i < kSmallN; ++i) {  // past the tour: its last customer again, not used
+        const uint16_t *row = a.demand + (long long)(a.tour[i] - 1) * a.ld;
+        q[i] = row[s32];
+    }
+    if (wave == 0) {
+        // lane k's customer, from scalar registers (an indexed read of the arguments is a round trip
+        // to memory)
+        int after = 0;
+#pragma unroll
+        for (int i = 0; i < kSmallN; ++i) after = lane == i ? a.tour[i] : after;
+        const int up = __shfl_up(after, 1, 64);
+        const int before = lane > 0 ? up : 0;
+        after = lane < n ? after : 0;
+        int link = 0;
+        if (lane <= n) {
+            const int in = lane > 0 ? arc_cost(a, before, 0) : 0;
+            const int out = lane < n ? arc_cost(a, 0, after) : 0;
+            if (lane > 0 && lane < n) link = arc_cost(a, before, after);
+            w[lane] = in + out - link;
+        }
+        for (int off = 32; off > 0; off >>= 1) link += __shfl_xor(link, off, 64);
+        if (lane == n) w[n] += link;  // the arcs of the tour: turns g back into f
+    }
+    __syncthreads();
+    uint32_t qor = 0;
+    bool err = false;
+    int P[kSmallN + 1], G[kSmallN + 1];
+    P[0] = 0;
+    G[0] = w[0];
+    int cost = 0;
+#pragma unroll
+    for (int i = 1; i <= kSmallN; ++i) {
+        if (i <= n) {
+            P[i] = P[i - 1] + (int)q[i - 1];
+            qor |= q[i - 1];
+            err |= (int)q[i - 1] > a.Q;
+            const int over = P[i] - a.Q;  // predecessors with a smaller prefix load are out
+            int m = kInf;
+#pragma unroll
+            for (int p = i - 1; p >= 0; --p) m = min(m, P[p] >= over ? G[p] : kInf);
+            G[i] = w[i] + m;
+            cost = G[i];
+        } else {
+            P[i] = 0;
+            G[i] = 0;
+        }
+    }
+    err |= (qor & 0x8000u) != 0;  // a negative int16 demand, for any Q
+    const bool ok = active && !err;
+    if (ok) a.cost[scen] = cost;
+    const CostSums v = wave_costs(ok ? (uint32_t)cost : 0u);
+    const unsigned long long bad = __ballot(active && err);
+    const unsigned long long past =
+        __ballot(active && a.count_bound && 8u * qor + (uint32_t)a.Q > 32767u);
+    if (lane == 63) {
+        part[wave] = v;
+        flags[wave][0] = bad != 0;
+        flags[wave][1] = (int)__popcll(past);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        TourResult r = {0, 0, 0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < kSmallPer / 64; ++k) {
+            r.sum += part[k].sum;
+            r.sq_l32 += part[k].sq_l32;
+            r.sq_h32 += part[k].sq_h32;
+            r.err_demand |= flags[k][0];
+            r.ovf_count += flags[k][1];
+        }
+        a.out[blockIdx.x] = r;
+    }
+}
+
 // ------------------------------------------------------------------------- two-kernel form
 
 // The paper's literal two-kernel form, kept as an ablation of the fused lane kernel: first the
@@ -1586,6 +1682,13 @@ static hipError_t wave_lds_allow(size_t bytes)
     if (bytes <= 65536) return hipSuccess;
     return hipFuncSetAttribute((const void *)split_wave_kernel,
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
+hipError_t launch_small(const SmallArgs &a, hipStream_t stream)
+{
+    hipLaunchKernelGGL(split_small_kernel, dim3((unsigned)((a.S + kSmallPer - 1) / kSmallPer)),
+                       dim3(kSmallPer), 0, stream, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_pair(const EvalArgs &a, hipStream_t stream)

@@ -130,3 +130,36 @@ def test_two_wavefronts_per_item_over_every_remainder(ctx, block):
             c.eval(tour, torch.from_numpy(bad).cuda(), Q)
         assert ei.value.status == sg.SPLIT_E_DEMAND, at
     c.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 20, 31, 32, 33])
+def test_short_tours_in_one_launch(ctx, n):
+    # edges of the tour length and of the workgroups' scenario counts, windows from one customer to
+    # the whole tour, a demand row stride, large capacities (the lane kernel's demand bound), calls
+    # after one another (the counters are left at zero), infeasible and negative demands
+    import paper_2511_18022_amd as sg
+    g = np.random.default_rng(n)
+    d = oracle.dist_matrix(gen.coords(21, N))
+    tour = g.permutation(np.arange(1, N + 1))[:n].astype(np.int32)
+    for s, Q, top in ((1, 10, 10), (255, 40, 20), (256, 1000, 20), (257, 60, 60), (4099, 90, 20),
+                      (32768, 45, 20), (32769, 45, 20), (300, 16383, 4000), (300, 32767, 32767)):
+        dem = g.integers(0, top + 1, size=(N, s), dtype=np.int16)
+        want = oracle.split(tour, d, dem, Q)
+        pad = torch.zeros((N, s + 5), dtype=torch.int16, device="cuda")
+        pad[:, :s] = torch.from_numpy(dem).cuda()
+        mom = oracle.moments(want)
+        for _ in range(2):
+            cost, st = ctx.eval(tour, pad[:, :s], Q)
+            assert np.array_equal(cost.cpu().numpy(), want), (n, s, Q)
+            assert (st.sum, st.sumsq, st.mean, st.var) == (mom["sum"], mom["sumsq"], mom["mean"],
+                                                          mom["var"])
+        lane = not (n <= (32 if s <= 256 else 24 if s <= 1024 else 16 if s <= 4096 else 0)
+                    or Q > 16383)
+        over = 8 * np.bitwise_or.reduce(dem[tour - 1].astype(np.int64), axis=0) + Q > 32767
+        assert st.n_fallback == (int(over.sum()) if lane else 0), (n, s, Q)
+        for value in (Q + 1 if Q < 32767 else -1, -1):
+            bad = pad.clone()
+            bad[int(tour[n // 2]) - 1, s // 2] = value
+            with pytest.raises(sg.SplitError) as ei:
+                ctx.eval(tour, bad[:, :s], Q)
+            assert ei.value.status == sg.SPLIT_E_DEMAND
