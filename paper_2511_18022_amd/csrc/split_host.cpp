@@ -501,9 +501,15 @@ SumSlots sum_slots(int form, int32_t T_grid, int64_t S)
 {
     SumSlots s;
     s.base = nullptr;
-    s.by_item = form == SPLIT_FORM_LANE && T_grid > 1 ? 1 : 0;
-    s.slots = s.by_item ? (S + 63) / 64 : kMaxSlots;
-    s.stride = s.by_item ? (int32_t)sizeof(CostSums) : kSlotStride;
+    // an entry per item up to 128 MiB of them (or 64 a tour); batches beyond that, whose cost matrix
+    // takes a GiB and more, keep 64 entries a tour
+    const int64_t nsb = (S + 63) / 64;
+    s.by_item = form == SPLIT_FORM_LANE && T_grid > 1 &&
+                        (nsb <= kMaxSlots || nsb * T_grid <= ((int64_t)1 << 22))
+                    ? 1
+                    : 0;
+    s.slots = s.by_item ? nsb : kMaxSlots;
+    s.stride = s.by_item || T_grid > 1 ? (int32_t)sizeof(CostSums) : kSlotStride;
     return s;
 }
 
