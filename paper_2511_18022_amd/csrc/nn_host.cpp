@@ -21,6 +21,7 @@ namespace {
 
 constexpr int32_t kPredChunk = 1024;   // tours per forward pass when predicting many tours
 constexpr int32_t kWgradChunk = 1024;  // padded rows per weight-gradient partial sum
+constexpr int64_t kTablePositions = 1 << 20;
 constexpr int32_t kExactChunk = 256;   // shortlisted tours per exact batch evaluation
 const char kMagic[8] = {'S', 'P', 'L', 'I', 'T', 'N', 'N', '1'};
 
@@ -44,6 +45,7 @@ struct split_nn {
     float *P = nullptr, *m = nullptr, *v = nullptr, *G = nullptr;
     NnWeights w = {};
     double *musd = nullptr;
+    uint16_t *table = nullptr;  // [musd_N][8], made by the prediction calls that read it
     int32_t musd_N = 0, Q = 0;
     bool have_scen = false;
     // activations [T][n + 4][C]
@@ -227,9 +229,10 @@ split_status timing_begin(split_nn *nn, hipStream_t st, hipEvent_t *stop)
 }
 
 // host_err (pinned, or NULL): where the head kernel hands the feature kernels' flag, which covers
-// every forward pass since it was last handed over.
+// every forward pass since it was last handed over. table: the customers' features, or NULL.
 split_status forward(split_nn *nn, const NnInstance &in, const int32_t *tours, int32_t T,
-                     int32_t n, float *pred, int32_t *host_err, hipStream_t st)
+                     int32_t n, float *pred, int32_t *host_err, const uint16_t *table,
+                     hipStream_t st)
 {
     const bool train = pred == nullptr;
     split_status s = ensure_act(nn, T, n, train, st);
@@ -252,7 +255,8 @@ split_status forward(split_nn *nn, const NnInstance &in, const int32_t *tours, i
         nn->cap_xp = cap;
     }
     uint16_t *X = train ? nn->X : nn->Xp;
-    NN_TRY(nn, nn_launch_features(in, tours, T, n, nn->musd, nn->Q, nn->L, X, !train, nn->err, st));
+    NN_TRY(nn, nn_launch_features(in, tours, T, n, nn->musd, nn->Q, nn->L, table, X, !train,
+                                  nn->err, st));
     const NnHidden H = {{nn->H[0], nn->H[1], nn->H[2], nn->H[3]}};
     hipEvent_t stop = nullptr;
     if (!train) {
@@ -323,10 +327,17 @@ split_status check_ids(split_nn *nn, const char *who, hipStream_t st)
 split_status predict_all(split_nn *nn, const NnInstance &in, const int32_t *tours, int64_t C,
                          int32_t n, float *pred, hipStream_t st)
 {
+    // from kTablePositions on, a launch for the customers' own features (3 us) pays for itself: it
+    // saves 6 us per 2^20 positions
+    const uint16_t *table = nullptr;
+    if (C * n >= kTablePositions) {
+        NN_TRY(nn, nn_launch_customers(in, nn->musd, nn->Q, nn->L, nn->table, st));
+        table = nn->table;
+    }
     for (int64_t t0 = 0; t0 < C; t0 += kPredChunk) {
         const int32_t Tc = (int32_t)(C - t0 < kPredChunk ? C - t0 : kPredChunk);
         const split_status s = forward(nn, in, tours + t0 * n, Tc, n, pred + t0,
-                                       t0 + Tc == C ? nn->h_err : nullptr, st);
+                                       t0 + Tc == C ? nn->h_err : nullptr, table, st);
         if (s != SPLIT_OK) {
             // a pass that never ran leaves the flag of those before it: not the next call's
             (void)hipMemsetAsync(nn->err, 0, sizeof(int32_t), st);
@@ -379,6 +390,7 @@ void free_nn(split_nn *nn)
     for (int32_t *p : {nn->err, nn->btours, nn->perm, nn->sidx, nn->stours, nn->ecost})
         if (p) (void)hipFree(p);
     if (nn->musd) (void)hipFree(nn->musd);
+    if (nn->table) (void)hipFree(nn->table);
     if (nn->h_err) (void)hipHostFree(nn->h_err);
     if (nn->tk) (void)hipFree(nn->tk);
     for (auto &pr : nn->tpairs) {
@@ -532,7 +544,8 @@ split_status split_nn_set_scenarios(split_nn *nn, const int16_t *demand, int64_t
     Guard g(nn->device);
     NN_TRY(nn, hipDeviceSynchronize());
     if (in.N > nn->musd_N || !nn->musd) {
-        if (!realloc_dev(&nn->musd, sizeof(double) * 2 * (size_t)in.N))
+        if (!realloc_dev(&nn->musd, sizeof(double) * 2 * (size_t)in.N) ||
+            !realloc_dev(&nn->table, sizeof(uint16_t) * kNnFeatures * (size_t)in.N))
             return ctx_fail(nn->ctx, SPLIT_E_NOMEM, "split_nn_set_scenarios: allocation failed");
     }
     NN_TRY(nn, nn_launch_dstats(demand, ld, S, in.N, nn->musd, nullptr));
@@ -568,7 +581,7 @@ split_status split_nn_gradient(split_nn *nn, const int32_t *tours, const float *
     if (s != SPLIT_OK) return s;
     Guard g(nn->device);
     hipStream_t st = (hipStream_t)hip_stream;
-    s = forward(nn, in, tours, T, n, nullptr, nn->h_err, st);
+    s = forward(nn, in, tours, T, n, nullptr, nn->h_err, nullptr, st);
     if (s == SPLIT_OK) s = backward(nn, labels, T, n, nn->lout, st);
     if (s != SPLIT_OK) return s;
     s = check_ids(nn, "split_nn_gradient", st);
@@ -594,7 +607,7 @@ split_status split_nn_train_step(split_nn *nn, const int32_t *tours, const float
     if (s != SPLIT_OK) return s;
     Guard g(nn->device);
     hipStream_t st = (hipStream_t)hip_stream;
-    s = forward(nn, in, tours, T, n, nullptr, nn->h_err, st);
+    s = forward(nn, in, tours, T, n, nullptr, nn->h_err, nullptr, st);
     if (s == SPLIT_OK) s = backward(nn, labels, T, n, nn->lout, st);
     if (s != SPLIT_OK) return s;
     // ids are checked before the update touches the parameters
@@ -673,7 +686,7 @@ split_status split_nn_train(split_nn *nn, const int32_t *tours, const float *lab
         }
         NN_TRY(nn, nn_launch_gather(tours, labels, nn->perm + pos * batch, batch, n, nn->btours,
                                     nn->blabels, st));
-        s = forward(nn, in, nn->btours, batch, n, nullptr, nullptr, st);
+        s = forward(nn, in, nn->btours, batch, n, nullptr, nullptr, nullptr, st);
         if (s == SPLIT_OK) s = backward(nn, nn->blabels, batch, n, nn->losshist + k, st);
         if (s != SPLIT_OK) return s;
         s = adam_step(nn, lr, st);

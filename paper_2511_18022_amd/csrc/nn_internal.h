@@ -71,8 +71,11 @@ hipError_t nn_launch_dstats(const int16_t *demand, int64_t ld, int64_t S, int32_
 // the 8 bf16 features of every position: packed [T][n][8] for prediction, else the padded
 // training layout [T][n + 4][32] (rows 0, 1, n + 2, n + 3 and channels 8..31 left untouched)
 hipError_t nn_launch_features(const NnInstance &in, const int32_t *tours, int32_t T, int32_t n,
-                              const double *musd, int32_t Q, double L, uint16_t *X, bool packed,
-                              int32_t *err, hipStream_t st);
+                              const double *musd, int32_t Q, double L, const uint16_t *table,
+                              uint16_t *X, bool packed, int32_t *err, hipStream_t st);
+// table [N][8]: the customers' own features, for nn_launch_features (which takes NULL too)
+hipError_t nn_launch_customers(const NnInstance &in, const double *musd, int32_t Q, double L,
+                               uint16_t *table, hipStream_t st);
 // data gradient of a hidden layer: Y = conv(X, Wt) where mask > 0, else 0
 hipError_t nn_launch_conv_back(const uint16_t *X, const uint16_t *Wt, const uint16_t *mask,
                                uint16_t *Y, int32_t T, int32_t n, hipStream_t st);

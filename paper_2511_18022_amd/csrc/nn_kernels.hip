@@ -110,16 +110,55 @@ __device__ __forceinline__ long long nn_dist(const NnInstance &in, int u, int v)
     return m - k * k > k ? k + 1 : k;
 }
 
-// One thread per (tour, position): the 8 features in double, rounded once to bf16, written
-// with the 24 zero channels as 64 contiguous bytes. Out-of-range ids set *err and read id 1.
+// The features of a customer that do not depend on the tour, in double, rounded once to bf16: 0..3, 6
+// and 7 (4 and 5, the arcs along the tour, are left zero).
+__device__ __forceinline__ u16x8 nn_customer(const NnInstance &in, int c, const double *musd,
+                                             int32_t Q, double L)
+{
+    double f[8];
+    if (in.kind == 0) {
+        f[0] = ((double)in.xy[2 * c] - (double)in.xy[0]) / L;
+        f[1] = ((double)in.xy[2 * c + 1] - (double)in.xy[1]) / L;
+    } else {
+        f[0] = 0.0;
+        f[1] = 0.0;
+    }
+    f[2] = musd[2 * (c - 1)] / (double)Q;
+    f[3] = musd[2 * (c - 1) + 1] / (double)Q;
+    f[4] = 0.0;
+    f[5] = 0.0;
+    f[6] = (double)nn_dist(in, 0, c) / L;
+    f[7] = 1.0;
+    u16x8 v;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = bf16_bits_f64(f[k]);
+    return v;
+}
+
+// table[c - 1] = nn_customer of every customer
+__global__ __launch_bounds__(256) void nn_customers_kernel(NnInstance in, const double *musd,
+                                                           int32_t Q, double L, uint16_t *table)
+{
+    const int c = blockIdx.x * 256 + threadIdx.x + 1;
+    if (c <= in.N)
+        *reinterpret_cast<u16x8 *>(table + (c - 1) * kNnFeatures) = nn_customer(in, c, musd, Q, L);
+}
+
+// One thread per (tour, position): the 8 features, written with 24 zero channels as 64 contiguous
+// bytes, or packed. Out-of-range ids set *err and read id 1. An arc is computed once, by the thread
+// of the position it leads to, and handed to the one before it; with a table the customers' own
+// features are looked up. Bound by the double divisions
+// and roots: 15.6 us for 1024 tours of 1000, 21.8 with seven of one and three of the other each.
 __global__ __launch_bounds__(256) void nn_features_kernel(NnInstance in, const int32_t *tours,
                                                           int32_t T, int32_t n,
                                                           const double *musd, int32_t Q, double L,
-                                                          uint16_t *X, int32_t packed,
-                                                          int32_t *err)
+                                                          const uint16_t *table, uint16_t *X,
+                                                          int32_t packed, int32_t *err)
 {
-    const long long m = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (m >= (long long)T * n) return;
+    const long long total = (long long)T * n;
+    const long long mm = (long long)blockIdx.x * 256 + threadIdx.x;
+    const bool live = mm < total;
+    const long long m = live ? mm : total - 1;  // every lane stays for the exchange
     const int t = (int)(m / n), j = (int)(m - (long long)t * n);
     const int32_t *tour = tours + (long long)t * n;
     auto id = [&](int k) {
@@ -132,24 +171,16 @@ __global__ __launch_bounds__(256) void nn_features_kernel(NnInstance in, const i
     };
     const int c = id(j);
     const int prev = j > 0 ? id(j - 1) : 0;
-    const int nxt = j + 1 < n ? id(j + 1) : 0;
-    double f[8];
-    if (in.kind == 0) {
-        f[0] = ((double)in.xy[2 * c] - (double)in.xy[0]) / L;
-        f[1] = ((double)in.xy[2 * c + 1] - (double)in.xy[1]) / L;
-    } else {
-        f[0] = 0.0;
-        f[1] = 0.0;
-    }
-    f[2] = musd[2 * (c - 1)] / (double)Q;
-    f[3] = musd[2 * (c - 1) + 1] / (double)Q;
-    f[4] = (double)nn_dist(in, prev, c) / L;
-    f[5] = (double)nn_dist(in, c, nxt) / L;
-    f[6] = (double)nn_dist(in, 0, c) / L;
-    f[7] = 1.0;
-    u16x8 v;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = bf16_bits_f64(f[k]);
+    u16x8 v = table ? *reinterpret_cast<const u16x8 *>(table + (c - 1) * kNnFeatures)
+                    : nn_customer(in, c, musd, Q, L);
+    const uint16_t in_arc = bf16_bits_f64((double)nn_dist(in, prev, c) / L);
+    const uint32_t next_arc = __shfl_down((uint32_t)in_arc, 1, 64);
+    v[4] = in_arc;
+    if ((threadIdx.x & 63) < 63 && j + 1 < n && m + 1 < total)
+        v[5] = (uint16_t)next_arc;
+    else
+        v[5] = bf16_bits_f64((double)nn_dist(in, c, j + 1 < n ? id(j + 1) : 0) / L);
+    if (!live) return;
     if (packed) {  // prediction input: [T][n][8], no padding rows or channels
         *reinterpret_cast<u16x8 *>(X + m * kNnFeatures) = v;
         return;
@@ -1363,12 +1394,20 @@ hipError_t nn_launch_dstats(const int16_t *demand, int64_t ld, int64_t S, int32_
     return hipGetLastError();
 }
 
+hipError_t nn_launch_customers(const NnInstance &in, const double *musd, int32_t Q, double L,
+                               uint16_t *table, hipStream_t st)
+{
+    hipLaunchKernelGGL(nn_customers_kernel, dim3(grid_of(in.N, 256)), dim3(256), 0, st, in, musd, Q,
+                       L, table);
+    return hipGetLastError();
+}
+
 hipError_t nn_launch_features(const NnInstance &in, const int32_t *tours, int32_t T, int32_t n,
-                              const double *musd, int32_t Q, double L, uint16_t *X, bool packed,
-                              int32_t *err, hipStream_t st)
+                              const double *musd, int32_t Q, double L, const uint16_t *table,
+                              uint16_t *X, bool packed, int32_t *err, hipStream_t st)
 {
     hipLaunchKernelGGL(nn_features_kernel, dim3(grid_of((long long)T * n, 256)), dim3(256), 0, st,
-                       in, tours, T, n, musd, Q, L, X, (int32_t)packed, err);
+                       in, tours, T, n, musd, Q, L, table, X, (int32_t)packed, err);
     return hipGetLastError();
 }
 
