@@ -230,9 +230,9 @@ split_status timing_begin(split_nn *nn, hipStream_t st, hipEvent_t *stop)
 
 // host_err (pinned, or NULL): where the head kernel hands the feature kernels' flag, which covers
 // every forward pass since it was last handed over. table: the customers' features, or NULL.
-split_status forward(split_nn *nn, const NnInstance &in, const int32_t *tours, int32_t T,
-                     int32_t n, float *pred, int32_t *host_err, const uint16_t *table,
-                     hipStream_t st)
+split_status forward_pass(split_nn *nn, const NnInstance &in, const int32_t *tours, int32_t T,
+                          int32_t n, float *pred, int32_t *host_err, const uint16_t *table,
+                          hipStream_t st)
 {
     const bool train = pred == nullptr;
     split_status s = ensure_act(nn, T, n, train, st);
@@ -268,6 +268,16 @@ split_status forward(split_nn *nn, const NnInstance &in, const int32_t *tours, i
     NN_TRY(nn, nn_launch_head_pool(nn->zpart, T, n, nn->P, nn->z, nn->a, nn->y, pred, nn->shift,
                                    nn->scale, nn->err, host_err, st));
     return SPLIT_OK;
+}
+
+// A pass that does not reach its head leaves the flag of the ids it read: not the next call's.
+split_status forward(split_nn *nn, const NnInstance &in, const int32_t *tours, int32_t T,
+                     int32_t n, float *pred, int32_t *host_err, const uint16_t *table,
+                     hipStream_t st)
+{
+    const split_status s = forward_pass(nn, in, tours, T, n, pred, host_err, table, st);
+    if (s != SPLIT_OK) (void)hipMemsetAsync(nn->err, 0, sizeof(int32_t), st);
+    return s;
 }
 
 // The loss into *loss and the full gradient into nn->G for the batch whose forward pass just ran.
@@ -338,11 +348,7 @@ split_status predict_all(split_nn *nn, const NnInstance &in, const int32_t *tour
         const int32_t Tc = (int32_t)(C - t0 < kPredChunk ? C - t0 : kPredChunk);
         const split_status s = forward(nn, in, tours + t0 * n, Tc, n, pred + t0,
                                        t0 + Tc == C ? nn->h_err : nullptr, table, st);
-        if (s != SPLIT_OK) {
-            // a pass that never ran leaves the flag of those before it: not the next call's
-            (void)hipMemsetAsync(nn->err, 0, sizeof(int32_t), st);
-            return s;
-        }
+        if (s != SPLIT_OK) return s;
     }
     return SPLIT_OK;
 }
@@ -638,8 +644,10 @@ split_status split_nn_train(split_nn *nn, const int32_t *tours, const float *lab
     hipStream_t st = (hipStream_t)hip_stream;
     // every id of the training set, once, before any update
     NN_TRY(nn, nn_launch_check_ids(tours, count * n, in.N, nn->err, st));
-    NN_TRY(nn, hipMemcpyAsync(nn->h_err, nn->err, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    const hipError_t copied =
+        hipMemcpyAsync(nn->h_err, nn->err, sizeof(int32_t), hipMemcpyDeviceToHost, st);
     NN_TRY(nn, hipMemsetAsync(nn->err, 0, sizeof(int32_t), st));
+    NN_TRY(nn, copied);
     s = check_ids(nn, "split_nn_train", st);
     if (s != SPLIT_OK) return s;
     NN_TRY(nn, hipDeviceSynchronize());
