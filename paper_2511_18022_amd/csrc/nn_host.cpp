@@ -549,7 +549,10 @@ split_status split_nn_set_scenarios(split_nn *nn, const int16_t *demand, int64_t
                         "ld, Q >= 1");
     Guard g(nn->device);
     NN_TRY(nn, hipDeviceSynchronize());
-    if (in.N > nn->musd_N || !nn->musd) {
+    // until the statistics of this call are there, none are: the two buffers grow together
+    nn->have_scen = false;
+    if (in.N > nn->musd_N) {
+        nn->musd_N = 0;
         if (!realloc_dev(&nn->musd, sizeof(double) * 2 * (size_t)in.N) ||
             !realloc_dev(&nn->table, sizeof(uint16_t) * kNnFeatures * (size_t)in.N))
             return ctx_fail(nn->ctx, SPLIT_E_NOMEM, "split_nn_set_scenarios: allocation failed");

@@ -335,12 +335,34 @@ void flag_of_a_failed_pass()
     CHECK(split_nn_predict(s.nn, good, 2, 2, pred, nullptr) == SPLIT_OK);
 }
 
+// An allocation that fails while the customers' statistics grow leaves no scenario set behind (and
+// no half of the buffers): predictions are refused until a call has made both.
+void scenarios_after_a_failed_allocation()
+{
+    for (int at = 1; at <= 2; ++at) {
+        Nn s(20);
+        std::vector<int32_t> tours((size_t)1 << 20, 1);
+        std::vector<float> pred((size_t)1 << 18);
+        s.ctx.coords(60);
+        fail_malloc = at;
+        CHECK(s.scenarios() == SPLIT_E_NOMEM);
+        CHECK(fail_malloc == 0);
+        s.ctx.coords(20);
+        CHECK(split_nn_predict(s.nn, tours.data(), 2, 2, pred.data(), nullptr) == SPLIT_E_INVAL);
+        // fewer customers than before the failure, and a call large enough to read the table
+        CHECK(s.scenarios() == SPLIT_OK);
+        CHECK(split_nn_predict(s.nn, tours.data(), 1 << 18, 4, pred.data(), nullptr) == SPLIT_OK);
+        CHECK(count("customers") == at);
+    }
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
 };
 const Scenario kScenarios[] = {
     {"flag-of-a-failed-pass", flag_of_a_failed_pass},
+    {"scenarios-after-a-failed-allocation", scenarios_after_a_failed_allocation},
 };
 
 }  // namespace

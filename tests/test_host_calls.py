@@ -20,7 +20,9 @@ def driver(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("scenario", ["flag-of-a-failed-pass"])
+@pytest.mark.parametrize("scenario", [
+    "flag-of-a-failed-pass", "scenarios-after-a-failed-allocation",
+])
 def test_host_calls(driver, scenario):
     # nothing preloaded comes before the sanitizer's runtime, which the driver links first
     env = {**os.environ, "ASAN_OPTIONS": "detect_leaks=0:verify_asan_link_order=0"}
