@@ -761,8 +761,9 @@ __global__ __launch_bounds__(256) void nn_dp4_kernel(const float *__restrict__ d
                                                      const uint16_t *__restrict__ H4, int32_t n,
                                                      uint16_t *__restrict__ dP)
 {
-    const int t = blockIdx.y, c0 = (threadIdx.x & 15) * 8;
-    const int j0 = blockIdx.x * 128 + (threadIdx.x >> 4);
+    const int tiles = (n + 127) >> 7;
+    const int t = blockIdx.x / tiles, c0 = (threadIdx.x & 15) * 8;
+    const int j0 = ((int)blockIdx.x - t * tiles) * 128 + (threadIdx.x >> 4);
     const long long base = ((long long)t * (n + 4) + 2) * kNnWidth + c0;
     u16x8 h[8];
 #pragma unroll
@@ -1462,7 +1463,8 @@ hipError_t nn_launch_head_bwd(const float *labels, int32_t T, int32_t n, const f
                        loss_terms, loss, G);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(nn_dp4_kernel, dim3(grid_of(n, 128), T), dim3(256), 0, st, dz, H4, n, dP4);
+    // one dimension: a batch may hold more tours than a grid's second dimension
+    hipLaunchKernelGGL(nn_dp4_kernel, dim3(T * grid_of(n, 128)), dim3(256), 0, st, dz, H4, n, dP4);
     return hipGetLastError();
 }
 
