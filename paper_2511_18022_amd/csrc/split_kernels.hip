@@ -924,9 +924,51 @@ __device__ __forceinline__ void lane_finish(const EvalArgs &a, int t, long long 
     if (active && !left && err) atomicOr(&a.stats[t].err_demand, 1);
 }
 
+// Whether windows are so long that an item of 64 scenarios almost surely has one of more than 47
+// predecessors, from the 47 customers of positions 1 .. 47 in every scenario: the load of 48
+// customers is about normal, its mean and its spread (per customer, over scenarios and positions,
+// or of the whole load over the scenarios where that is wider) are those of the 47. A lane checks
+// one window in 16, (n - 48) / 18 of them about independent; the item is expected to have 1.7 past
+// the history where the capacity lies z standard deviations under the mean load of 48 with
+// z^2 = 1.8 ln(n - 48) - 1.7 (within 0.3 for n of 65 to 5000). One in five such items has none.
+// The line: an item left to the long kernel takes 5 to 6 times the lane kernel's share of the chip,
+// one that the lane kernel marks after all, both. Measured, whole calls, 1000 customers,
+// S = 2^20, mean windows of 41, 43, 44 and 60 under Poisson demands: 1.66, 6.65, 6.01 and 6.01 ms;
+// 0.95 ms under constant demands and windows of up to 47. A rule by the first 15 customers' share of
+// the capacity alone (at most 15 / 40) sent every item of these away: 6.0 to 6.2 ms.
+__device__ __forceinline__ bool windows_long(const uint16_t (&qA)[16], const uint16_t (&qB)[16],
+                                             const uint16_t (&qC)[16], int n, int Q)
+{
+    float load = 0.f, sq = 0.f;
+    auto add = [&](const uint16_t (&q)[16]) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const float x = (float)q[j];
+            load += x;
+            sq += x * x;
+        }
+    };
+    add(qA);  // position 0 has no demand
+    add(qB);
+    add(qC);
+    float s1 = load, s2 = load * load;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        s1 += __shfl_xor(s1, off, 64);
+        s2 += __shfl_xor(s2, off, 64);
+        sq += __shfl_xor(sq, off, 64);
+    }
+    const float m = s1 / 64.f;  // mean load of 47 customers
+    if (!(m > 0.f)) return true;
+    const float cv2 = fmaxf(47.f * sq / (64.f * m * m) - 1.f, 47.f * (s2 / (64.f * m * m) - 1.f));
+    const float room = 48.f - 47.f * (float)Q / m;
+    const float z2 = 1.8f * __logf((float)(n - 48)) - 1.7f;
+    return room <= 0.f || room * room <= z2 * 48.f * (cv2 - 1e-5f);
+}
+
 // The windows of a work item, from the demands of its first positions (loaded anyway):
-//  kWindowsLong   under half of the scenarios or more, the first 15 customers fill at most 15 / 40 of
-//                 the capacity: some window will outgrow 47 positions;
+//  kWindowsLong   see windows_long; looked at only where under half of the scenarios or more the
+//                 first 15 customers fill at most 15 / 32 of the capacity;
 //  kWindowsShort  the mean window W over the first 47 positions plus 4.6 times its spread (from the
 //                 spread of those 47 customers' load over the scenarios) stays within 22, and under
 //                 every scenario the first route holds at most 18 customers: 8-state blocks keep
@@ -947,11 +989,12 @@ __device__ __forceinline__ int window_class(const uint16_t (&qA)[16], const uint
     int load = 0, len = 0;
 #pragma unroll
     for (int j = 0; j < 16; ++j) load += qA[j];  // position 0 has no demand
-    if (__any(22 * load <= 15 * Q))
-        return n > 64 && 2 * __popcll(__ballot(active && 40 * load <= 15 * Q)) >=
-                             __popcll(__ballot(active))
-                   ? kWindowsLong
-                   : kWindowsMid;
+    if (__any(22 * load <= 15 * Q)) {
+        if (n <= 64 || 2 * __popcll(__ballot(active && 32 * load <= 15 * Q)) <
+                           __popcll(__ballot(active)))
+            return kWindowsMid;
+        return windows_long(qA, qB, qC, n, Q) ? kWindowsLong : kWindowsMid;
+    }
     load = 0;
     auto count = [&](const uint16_t (&q)[16]) {
 #pragma unroll

@@ -1,0 +1,84 @@
+"""The library's own launch choices against explicit ones, by time: a choice left to the library is
+not much slower than another route that the same call could take. Sizes and margins are such that
+the faults these tests are for (a factor of 1.4 and more) show well above the noise of a few
+percent. Each time is the least of several means."""
+import time
+
+import numpy as np
+import pytest
+
+import gen
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sg():
+    import paper_2511_18022_amd as sg
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    return sg
+
+
+def least_ms(call, reps=5, inner=4):
+    call()
+    torch.cuda.synchronize()
+    best = float("inf")
+    for _ in range(reps):
+        t0 = time.perf_counter()
+        for _ in range(inner):
+            call()
+        torch.cuda.synchronize()
+        best = min(best, (time.perf_counter() - t0) * 1e3 / inner)
+    return best
+
+
+def poisson(N, S, mean, seed=7):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    out = torch.empty((N, S), dtype=torch.int16, device="cuda")
+    for c in range(0, N, 100):
+        rate = torch.full((min(100, N - c), S), float(mean), device="cuda")
+        out[c:c + 100] = torch.poisson(rate, generator=g).to(torch.int16)
+    return out
+
+
+@pytest.mark.parametrize("law,Q", [("poisson", 820), ("constant", 880), ("constant", 955)])
+def test_windows_that_fit_the_lane_kernel_stay_there(sg, law, Q):
+    # windows of 41, 44 and 47: under Poisson demands of 20 about one scenario in 5000 has one of
+    # more than 47, under constant demands none
+    N, S = 1000, 1 << 18
+    ctx = sg.SplitContext(0)
+    ctx.set_coords(gen.coords(61, N))
+    dem = (poisson(N, S, 20.0) if law == "poisson"
+           else torch.full((N, S), 20, dtype=torch.int16, device="cuda"))
+    tour = gen.tour(61, N, N)
+    cost = torch.empty(S, dtype=torch.int32, device="cuda")
+    _, st = ctx.eval(tour, dem, Q, cost=cost)
+    ms = least_ms(lambda: ctx.eval(tour, dem, Q, cost=cost))
+    want = cost.clone()
+    ctx.set_tuning(sg.SplitTuning(lane_block=16))
+    _, st16 = ctx.eval(tour, dem, Q, cost=cost)
+    ms16 = least_ms(lambda: ctx.eval(tour, dem, Q, cost=cost))
+    print(f"[routes] {law} Q={Q}: {ms:.3f} ms, blocks of 16 {ms16:.3f} ms, "
+          f"fallback {st.n_fallback}", flush=True)
+    assert torch.equal(cost, want) and st.n_fallback == st16.n_fallback
+    assert ms <= 1.3 * ms16
+    ctx.close()
+
+
+@pytest.mark.parametrize("S", [10_000, 1 << 18])
+def test_windows_past_the_lane_kernel_go_to_the_long_kernel_at_once(sg, S):
+    N = 1000
+    ctx = sg.SplitContext(0)
+    ctx.set_coords(gen.coords(61, N))
+    dem = poisson(N, S, 20.0)
+    tour = gen.tour(61, N, N)
+    cost = torch.empty(S, dtype=torch.int32, device="cuda")
+    ms = least_ms(lambda: ctx.eval(tour, dem, 1200, cost=cost))
+    ctx.set_tuning(sg.SplitTuning(lane_block=16))
+    ms16 = least_ms(lambda: ctx.eval(tour, dem, 1200, cost=cost))
+    print(f"[routes] windows of 60, S={S}: {ms:.3f} ms, blocks of 16 first {ms16:.3f} ms",
+          flush=True)
+    assert ms <= 1.05 * ms16
+    ctx.close()
