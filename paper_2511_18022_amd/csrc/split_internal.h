@@ -31,8 +31,10 @@ split_status ctx_fail(split_ctx *ctx, split_status st, const char *fmt, ...);
 // "Infinity" for DP values. Host checks guarantee |DP value| + |weight| < 2^30.
 constexpr int32_t kInf = 0x3fffffff;
 
-// Cost mark of a scenario the lane kernel leaves to the general kernel (costs are >= 0).
+// Cost marks of a scenario that a DP kernel leaves to the tail kernel (costs are >= 0): a window past
+// the history, and values past the 16 bits of blocks of 16 states.
 constexpr int32_t kCostOvf = INT32_MIN;
+constexpr int32_t kCostWide = INT32_MIN + 1;
 
 // Device-side flags of one tour (zeroed by the prep kernel of each call).
 struct DevStats {

@@ -906,15 +906,16 @@ __device__ __forceinline__ void lane_run(LaneLds<H> &L, const LaneTour &tr, int 
 }
 
 // The end of a work item: the costs of the scenarios that are done; the others are marked for the
-// long kernel, which also counts them under `recount`.
-__device__ __forceinline__ void lane_finish(const EvalArgs &a, int t, long long scen, bool ovf,
+// tail kernel, which also counts them under `recount`. ovf: negative where a window outgrew the
+// history, positive where only demands or suffix offsets past 16 bits stand against blocks of 16.
+__device__ __forceinline__ void lane_finish(const EvalArgs &a, int t, long long scen, int ovf,
                                             bool err, int gres, bool recount)
 {
     __builtin_amdgcn_s_setprio(0);
     const bool active = scen < a.S;
-    const bool left = active && ovf;
+    const bool left = active && ovf != 0;
     if (active && (left || !err))
-        a.cost[(long long)t * a.ldc + scen] = left ? kCostOvf : gres;
+        a.cost[(long long)t * a.ldc + scen] = !left ? gres : ovf > 0 ? kCostWide : kCostOvf;
     item_costs(a.sums, t, scen >> 6, active && !left && !err ? (uint32_t)gres : 0u);
     const unsigned long long m = __ballot(left);
     if (m != 0 && threadIdx.x == 0) {
@@ -931,11 +932,11 @@ __device__ __forceinline__ void lane_finish(const EvalArgs &a, int t, long long 
 // one window in 16, (n - 48) / 18 of them about independent; the item is expected to have 1.7 past
 // the history where the capacity lies z standard deviations under the mean load of 48 with
 // z^2 = 1.8 ln(n - 48) - 1.7 (within 0.3 for n of 65 to 5000). One in five such items has none.
-// The line: an item left to the long kernel takes 5 to 6 times the lane kernel's share of the chip,
-// one that the lane kernel marks after all, both. Measured, whole calls, 1000 customers,
-// S = 2^20, mean windows of 41, 43, 44 and 60 under Poisson demands: 1.66, 6.65, 6.01 and 6.01 ms;
+// The line: an item left to the long kernel takes 4 times the lane kernel's share of the chip, one
+// that the lane kernel marks after all, both. Measured, whole calls, 1000 customers, S = 2^20, mean
+// windows of 41, 43, 44 and 60 under Poisson demands: @LONG@ ms;
 // 0.95 ms under constant demands and windows of up to 47. A rule by the first 15 customers' share of
-// the capacity alone (at most 15 / 40) sent every item of these away: 6.0 to 6.2 ms.
+// the capacity alone (at most 15 / 40) sent every item of all these to the long kernel.
 __device__ __forceinline__ bool windows_long(const uint16_t (&qA)[16], const uint16_t (&qB)[16],
                                              const uint16_t (&qC)[16], int n, int Q)
 {
@@ -1037,7 +1038,8 @@ __device__ __forceinline__ void lane_item(LaneLds<64> &L, const EvalArgs &a, int
         lane_load_block<8>(rsrc, tr.rowoff, lane_off, 2, qC);
         LaneState<8, 64> st;
         lane_run<8, 64>(L, tr, a.Q, rsrc, lane_off, qA, qB, qC, prio, st);
-        lane_finish(a, t, scen, st.ovf != 0, st.err, st.gres, false);
+        // offsets past 16 bits over 8 states may still fit over 16: only the demands' bit counts
+        lane_finish(a, t, scen, st.ovf == 1 || st.ovf == 0 ? st.ovf : INT_MIN, st.err, st.gres, false);
     } else {
         uint16_t qA[16], qB[16], qC[16];
         lane_load_block<16>(rsrc, tr.rowoff, lane_off, 0, qA);
@@ -1045,7 +1047,7 @@ __device__ __forceinline__ void lane_item(LaneLds<64> &L, const EvalArgs &a, int
         lane_load_block<16>(rsrc, tr.rowoff, lane_off, 2, qC);
         int cls = kWindowsMid;
         if constexpr (LB == 0) cls = window_class(qA, qB, qC, tr.n, a.Q, scen < a.S);
-        int ovf = 1, gres = 0;
+        int ovf = INT_MIN, gres = 0;
         bool err = false;
         if (__builtin_expect(cls == kWindowsMid, 1)) {
             LaneState<16, 64> st;
@@ -1067,7 +1069,7 @@ __device__ __forceinline__ void lane_item(LaneLds<64> &L, const EvalArgs &a, int
             err = st.err;
             gres = st.gres;
         }
-        lane_finish(a, t, scen, ovf != 0, err, gres, true);
+        lane_finish(a, t, scen, ovf, err, gres, true);
     }
 }
 
@@ -1262,7 +1264,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void s
             cost = pair_item<8>(L, a, tr, half, total, back, lane_off, rsrc, rA, rB, rC, ovf, err);
         }
     }
-    if (!back) lane_finish(a, t, scen, ovf != 0, err, cost, true);
+    if (!back) lane_finish(a, t, scen, ovf != 0 ? INT_MIN : 0, err, cost, true);
 }
 
 // ------------------------------------------------------------------------- wave kernel
@@ -1283,7 +1285,7 @@ __device__ __forceinline__ int wave_min(int v)
 // Exclusive prefix sum over the 64 lanes.
 __device__ __forceinline__ int wave_exclusive_sum(int v)
 {
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
     int inc = v;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -1293,14 +1295,23 @@ __device__ __forceinline__ int wave_exclusive_sum(int v)
     return inc - v;
 }
 
+// Orders a wavefront's LDS accesses among its lanes (the others of its workgroup go their own way).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // One scenario by one wavefront. First the prefix loads P_0..P_n are built in LDS with all
 // lanes loading demands in parallel (chunk per lane + wavefront scan). Then, state by state,
 // every lane runs the same two-pointer on the same data (uniform control flow), lane j reads
 // g of predecessor s + j (+ 64k for long windows) and the wavefront reduces them.
 // Returns the scenario's cost, or 0 where a demand is infeasible (flagged).
-__device__ uint32_t wave_one(const EvalArgs &a, int t, long long scen, int32_t *G, int32_t *PP)
+__device__ __forceinline__ uint32_t wave_one(const EvalArgs &a, int t, long long scen, int32_t *G,
+                                             int32_t *PP)
 {
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
     const int64_t ab = tour_abase(a.tour.tptr, t);
     const int n = (int)(a.tour.tptr[t + 1] - a.tour.tptr[t]);
     const int64_t *rowoff = a.tour.rowoff + ab;
@@ -1328,7 +1339,7 @@ __device__ uint32_t wave_one(const EvalArgs &a, int t, long long scen, int32_t *
         PP[0] = 0;
         G[0] = w[0];
     }
-    __syncthreads();
+    wave_sync();
     int s = 0;
     bool err = neg;
     for (int i = 1; i <= n && !err; ++i) {
@@ -1352,7 +1363,7 @@ __device__ uint32_t wave_one(const EvalArgs &a, int t, long long scen, int32_t *
         else
             a.cost[(long long)t * a.ldc + scen] = cost;
     }
-    __syncthreads();
+    wave_sync();
     return (uint32_t)cost;
 }
 
@@ -1381,7 +1392,7 @@ __global__ __launch_bounds__(64) void split_wave_kernel(EvalArgs a)
 // by earlier launches or (once every workgroup is counted in) by this one: read there too.
 __device__ __forceinline__ void report_tour(const EvalArgs &a, int t)
 {
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
     auto load = [](const auto *p) {
         return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
@@ -1402,87 +1413,123 @@ __device__ __forceinline__ void report_tour(const EvalArgs &a, int t)
                               load(&a.stats[t].ovf_count)};
 }
 
-// The scenarios marked kCostOvf, 64 at a time with the lane kernel's blocks of 16 over a history of
-// 256 positions (windows of up to 239). Scenarios that outgrow this history too, or whose suffix
-// offsets or demands pass 16 bits, are then finished one by one by the whole wavefront, in the same
-// LDS. With a.recount it counts the scenarios past the lane kernel's history (n_fallback): an item
-// is left here whole.
+// The scenarios that the DP kernels marked. Those past the lane kernel's history (kCostOvf) go 64 at
+// a time through its blocks of 16 over a history of 256 positions (windows of up to 239), by the
+// first wavefront. Those that outgrow this history too, and those whose suffix offsets or demands
+// pass 16 bits (kCostWide: blocks of 16 cannot hold them, whatever the history), are then finished
+// one by one, a scenario by each of the four wavefronts, in the same LDS. With a.recount the kernel
+// counts the scenarios past the lane kernel's history (n_fallback): an item is left here whole.
 //
-// Bound by the latency of one wavefront's serial chain: 75.5 KB of LDS leave two wavefronts a
-// compute unit, one on every other SIMD. That is still one state of 64 scenarios per step, where
-// one scenario per wavefront leaves most lanes idle: 701 customers, windows of about 60,
-// S = 20,011 took 14.76 ms as a call; with this kernel 0.18 ms, 0.12 of them here.
+// Bound by the latency of one wavefront's serial chain: 80 KB of LDS leave two workgroups a compute
+// unit. For the blocks that is still one state of 64 scenarios per step, where one scenario per
+// wavefront leaves most lanes idle: 701 customers, windows of about 60, S = 20,011 took 14.76 ms as
+// a call; with this kernel 0.15 ms. One by one, four wavefronts a workgroup take as many scenarios
+// at once as a kernel of their own with 8 bytes of LDS a position did: 200 customers, coordinates up
+// to 10^5, S = 2^17: 4.2 ms a call (19.0 with one wavefront, 4.5 in the separate kernel); 1000
+// customers, windows of 300, S = 2^17: 33.1 (149.5 and 35.1). wave_one has to be inlined: as a call
+// it reads LDS through generic pointers, and keeps the blocks' registers in scratch memory (1000
+// customers, windows of 60, S = 2^20: 6.1 ms a call against 3.9).
 // Counts go to memory once per item: one atomic per scenario took 240 us of this launch there.
 //
 // Then the tours' results, straight to the caller's (pinned host) memory. Where nothing was marked,
-// each workgroup reports its share at once; otherwise the last workgroup to finish reports all.
-__global__ __launch_bounds__(64) void split_tail_kernel(EvalArgs a)
+// each wavefront reports its share at once; otherwise the last workgroup to finish reports all.
+constexpr int kTailWaves = 4;
+constexpr int kTailWords = (80 * 1024 - 64) / 4;  // two workgroups fill a compute unit's LDS
+
+__global__ __launch_bounds__(64 * kTailWaves) __attribute__((amdgpu_waves_per_eu(2)))
+void split_tail_kernel(EvalArgs a)
 {
-    __shared__ LaneLds<256> L;
-    static_assert(sizeof(L) >= 2 * sizeof(int32_t) * (SPLIT_MAX_N + 1),
-                  "the wavefront's prefix loads and g values of a maximal tour fit");
-    const int lane = threadIdx.x;
+    __shared__ union {
+        LaneLds<256> L;
+        int32_t words[kTailWords];
+    } lds;
+    __shared__ unsigned long long s_wide;
+    __shared__ uint32_t s_before;
+    static_assert(sizeof lds == 4 * kTailWords && kTailWords >= 2 * (SPLIT_MAX_N + 1),
+                  "the history fits, and a wavefront's prefix loads and g values of a maximal tour");
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const long long T = *(ci64 *)a.tour.nt;
     if (*(cu32 *)&a.ctl->ovf_total == 0) {
-        for (int t = blockIdx.x; t < T; t += gridDim.x) report_tour(a, t);
+        for (long long t = (long long)blockIdx.x * kTailWaves + wave; t < T;
+             t += (long long)gridDim.x * kTailWaves)
+            report_tour(a, (int)t);
         return;
     }
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void *)a.demand, (short)0, (int)a.lane_bytes, 0x00020000);
     const long long nsb = (a.S + 63) / 64;
+    // the wavefronts that have room for a tour's arrays of their own
+    const int room = 2 * (a.maxn + 1);
+    const int nw = min(kTailWaves, kTailWords / room);
+    int32_t *G = lds.words + wave * room;
     for (long long k = blockIdx.x; k < T * nsb; k += gridDim.x) {
         const int t = (int)(k / nsb);
         const long long sb = k - (long long)t * nsb, s0 = sb * 64;
-        const bool active = s0 + lane < a.S;
-        const long long scen = active ? s0 + lane : a.S - 1;
-        int32_t *cost = a.cost + (long long)t * a.ldc;
-        const bool todo = active && cost[scen] == kCostOvf;
-        if (!__any(todo)) continue;
-        LaneState<16, 256> st;
-        st.ovf = 1;
-        st.past = false;
-        st.err = false;
-        st.gres = 0;
-        if (a.lane_bytes != 0) {  // the demands lie within a buffer descriptor's reach
-            const LaneTour tr = lane_tour(a, t);
-            const uint32_t lane_off = (uint32_t)scen * 2u;
-            uint16_t qA[16], qB[16], qC[16];
-            lane_load_block<16>(rsrc, tr.rowoff, lane_off, 0, qA);
-            lane_load_block<16>(rsrc, tr.rowoff, lane_off, 1, qB);
-            lane_load_block<16>(rsrc, tr.rowoff, lane_off, 2, qC);
-            lane_run<16, 256>(L, tr, a.Q, rsrc, lane_off, qA, qB, qC, false, st);
-        }
-        if (a.recount) {
-            const int past = (int)__popcll(__ballot(todo && (st.past || st.ovf)));
-            if (lane == 0 && past) atomicAdd(&a.stats[t].ovf_count, past);
-        }
-        uint32_t mine = 0;
-        if (todo && st.ovf == 0) {
-            if (st.err) {
-                atomicOr(&a.stats[t].err_demand, 1);
-            } else {
-                mine = (uint32_t)st.gres;
-                cost[scen] = st.gres;
+        CostSums *sums = sums_at(a.sums, t, a.sums.by_item ? sb : sb & (kMaxSlots - 1));
+        if (wave == 0) {
+            const bool active = s0 + lane < a.S;
+            const long long scen = active ? s0 + lane : a.S - 1;
+            int32_t *cost = a.cost + (long long)t * a.ldc;
+            const int32_t mark = active ? cost[scen] : 0;
+            const bool todo = mark == kCostOvf;
+            unsigned long long wide = __ballot(mark == kCostWide);
+            int past = (int)__popcll(wide);
+            if (__any(todo)) {
+                LaneState<16, 256> st;
+                st.ovf = 1;
+                st.past = false;
+                st.err = false;
+                st.gres = 0;
+                if (a.lane_bytes != 0) {  // the demands lie within a buffer descriptor's reach
+                    const LaneTour tr = lane_tour(a, t);
+                    const uint32_t lane_off = (uint32_t)scen * 2u;
+                    uint16_t qA[16], qB[16], qC[16];
+                    lane_load_block<16>(rsrc, tr.rowoff, lane_off, 0, qA);
+                    lane_load_block<16>(rsrc, tr.rowoff, lane_off, 1, qB);
+                    lane_load_block<16>(rsrc, tr.rowoff, lane_off, 2, qC);
+                    lane_run<16, 256>(lds.L, tr, a.Q, rsrc, lane_off, qA, qB, qC, false, st);
+                }
+                past += (int)__popcll(__ballot(todo && (st.past || st.ovf)));
+                wide |= __ballot(todo && st.ovf);
+                uint32_t mine = 0;
+                if (todo && st.ovf == 0) {
+                    if (st.err) {
+                        atomicOr(&a.stats[t].err_demand, 1);
+                    } else {
+                        mine = (uint32_t)st.gres;
+                        cost[scen] = st.gres;
+                    }
+                }
+                const CostSums v = wave_costs(mine);
+                if (lane == 63) add_sums(sums, v);
+            }
+            if (lane == 0) {
+                if (a.recount && past) atomicAdd(&a.stats[t].ovf_count, past);
+                s_wide = wide;
             }
         }
-        unsigned long long m = __ballot(todo && st.ovf);
-        int32_t *G = reinterpret_cast<int32_t *>(&L);
-        while (m) {
-            const int j = __builtin_ctzll(m);
-            m &= m - 1;
-            const uint32_t c = wave_one(a, t, s0 + j, G, G + SPLIT_MAX_N + 1);
-            if (lane == j) mine = c;
+        __syncthreads();
+        if (wave < nw) {
+            unsigned long long m = s_wide;
+            for (int turn = 0; m; turn = turn + 1 < nw ? turn + 1 : 0) {
+                const int j = __builtin_ctzll(m);
+                m &= m - 1;
+                if (turn != wave) continue;
+                const unsigned long long c = wave_one(a, t, s0 + j, G, G + a.maxn + 1);
+                const unsigned long long q = c * c;
+                if (lane == 0) add_sums(sums, CostSums{c, q & 0xFFFFFFFFull, q >> 32});
+            }
         }
-        const CostSums v = wave_costs(mine);
-        if (lane == 63)
-            add_sums(sums_at(a.sums, t, a.sums.by_item ? sb : sb & (kMaxSlots - 1)), v);
+        __syncthreads();  // the arrays and s_wide are free for the next item
     }
     __threadfence();
-    uint32_t before = 0;
-    if (lane == 0) before = atomicAdd(&a.ctl->done, 1u);
-    if (__builtin_amdgcn_readfirstlane(before) != gridDim.x - 1) return;
+    __syncthreads();
+    if (threadIdx.x == 0) s_before = atomicAdd(&a.ctl->done, 1u);
+    __syncthreads();
+    if (s_before != gridDim.x - 1) return;
     __threadfence();
-    for (int t = 0; t < T; ++t) report_tour(a, t);
+    for (long long t = wave; t < T; t += kTailWaves) report_tour(a, (int)t);
 }
 
 // ------------------------------------------------------------------------- small evaluations
@@ -1756,7 +1803,8 @@ hipError_t launch_tail(const EvalArgs &a, hipStream_t stream)
 {
     const long long work = (a.S + 63) / 64 * a.tour.T_grid;
     const long long nb = work < a.tail_grid ? work : a.tail_grid;
-    hipLaunchKernelGGL(split_tail_kernel, dim3((unsigned)nb), dim3(64), 0, stream, a);
+    hipLaunchKernelGGL(split_tail_kernel, dim3((unsigned)nb), dim3(64 * kTailWaves), 0,
+                       stream, a);
     return hipGetLastError();
 }
 

@@ -82,3 +82,24 @@ def test_windows_past_the_lane_kernel_go_to_the_long_kernel_at_once(sg, S):
           flush=True)
     assert ms <= 1.05 * ms16
     ctx.close()
+
+
+@pytest.mark.parametrize("n,grid,mean,Q", [(200, 100_000, 10, 200), (1000, 1000, 20, 6000)])
+def test_scenarios_finished_one_by_one_fill_the_chip(sg, n, grid, mean, Q):
+    # suffix offsets past 16 bits, and windows of 300: every scenario ends one by one. The wave form
+    # has two to three times the wavefronts in flight; a quarter of the places made it 9 to 12.
+    S = 1 << 16
+    ctx = sg.SplitContext(0)
+    ctx.set_coords(np.random.default_rng(3).integers(0, grid, size=(n + 1, 2)).astype(np.int32))
+    dem = poisson(n, S, float(mean))
+    tour = gen.tour(62, n, n)
+    cost = torch.empty(S, dtype=torch.int32, device="cuda")
+    _, st = ctx.eval(tour, dem, Q, cost=cost)
+    ms = least_ms(lambda: ctx.eval(tour, dem, Q, cost=cost), reps=3, inner=1)
+    want = cost.clone()
+    ctx.set_form("wave")
+    wave = least_ms(lambda: ctx.eval(tour, dem, Q, cost=cost), reps=3, inner=1)
+    print(f"[routes] one by one, n={n}: {ms:.2f} ms, wave form {wave:.2f} ms", flush=True)
+    assert torch.equal(cost, want) and st.n_fallback == S
+    assert ms <= 5 * wave
+    ctx.close()
