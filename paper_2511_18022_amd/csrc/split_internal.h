@@ -40,6 +40,7 @@ constexpr int32_t kCostWide = INT32_MIN + 1;
 struct DevStats {
     int32_t err_demand;  // nonzero: some scenario has q > Q (or q < 0) on the tour
     int32_t ovf_count;   // scenarios of this tour past the lane kernel's history
+    uint32_t done;       // the tour's items that the tail kernel has finished
 };
 
 // Sums of some of a tour's costs: of the costs, and of their squares' low and high 32 bits (each
@@ -80,7 +81,7 @@ struct TourResult {
 struct BatchCtl {
     uint32_t head;       // next work item of the lane kernel's queue
     uint32_t ovf_total;  // nonzero: some scenario is marked kCostOvf
-    uint32_t done;       // tail kernel workgroups that have finished their items
+    uint32_t tail_head;  // next chunk of items of the tail kernel's queue
 };
 
 // Per-tour arrays built on the device by the prep kernel from the tours and the instance.

@@ -135,7 +135,7 @@ __global__ __launch_bounds__(1024) void split_prep_kernel(PrepArgs a)
         rowoff32[0] = kRowAbsent;
         w[0] = ends[0];
         w[n] = (int32_t)(red[0] + ends[1]);
-        a.stats[t] = DevStats{0, 0};
+        a.stats[t] = DevStats{0, 0, 0};
         a.tour.tptr[t] = p0;
         a.tour.order[t] = ord;
         if (t == T - 1) a.tour.tptr[T] = p1;
@@ -843,13 +843,15 @@ __device__ __forceinline__ LaneTour lane_tour(const EvalArgs &a, int t)
 }
 
 // States 0..n of a tour for the scenarios at byte offset lane_off (one per lane) of its demand
-// rows; qA, qB and qC hold the demands of blocks 0, 1 and 2.
+// rows; qA, qB and qC hold the demands of blocks 0, 1 and 2. H = 256: ends where every lane that is
+// wanted has outgrown the history (one scenario with windows of 500 among 2^20: 1.70 ms a call
+// without, 1.67 with).
 template <int LB, int H, bool HALF = false>
 __device__ __forceinline__ void lane_run(LaneLds<H> &L, const LaneTour &tr, int Q,
                                          __amdgpu_buffer_rsrc_t rsrc, uint32_t lane_off,
                                          uint16_t (&qA)[LB], uint16_t (&qB)[LB],
                                          uint16_t (&qC)[LB], bool by_progress,
-                                         LaneState<LB, H> &st, bool fill = false)
+                                         LaneState<LB, H> &st, bool fill = false, bool wanted = true)
 {
     using C = LaneCfg<LB, H>;
     const int lane = threadIdx.x & 63;
@@ -888,6 +890,7 @@ __device__ __forceinline__ void lane_run(LaneLds<H> &L, const LaneTour &tr, int 
     // kSteps steps per iteration keep these roles constant (H = 64: and the LDS rows of a step)
     for (int c = 0; c <= nb; c += C::kSteps) {
         if (by_progress) item_priority(c, nb);
+        if (H > 64 && !__any(wanted && st.ovf == 0)) break;
         const int R = H == 64 ? 0 : c & (C::kRing - 1);
         lane_step<LB, H, HALF>(L, lane, R, c, n, fill, QQ, rsrc, wrsrc, rowoff, lane_off, w, qB, qD, sA, sB, wA, wB, st);
         lane_step<LB, H, HALF>(L, lane, R + 1, c + 1, n, fill, QQ, rsrc, wrsrc, rowoff, lane_off, w, qC, qA, sB, sA, wB, wA, st);
@@ -934,7 +937,7 @@ __device__ __forceinline__ void lane_finish(const EvalArgs &a, int t, long long 
 // z^2 = 1.8 ln(n - 48) - 1.7 (within 0.3 for n of 65 to 5000). One in five such items has none.
 // The line: an item left to the long kernel takes 4 times the lane kernel's share of the chip, one
 // that the lane kernel marks after all, both. Measured, whole calls, 1000 customers, S = 2^20, mean
-// windows of 41, 43, 44 and 60 under Poisson demands: @LONG@ ms;
+// windows of 41, 43, 44 and 60 under Poisson demands: 1.26, 4.84, 4.24 and 4.25 ms;
 // 0.95 ms under constant demands and windows of up to 47. A rule by the first 15 customers' share of
 // the capacity alone (at most 15 / 40) sent every item of all these to the long kernel.
 __device__ __forceinline__ bool windows_long(const uint16_t (&qA)[16], const uint16_t (&qB)[16],
@@ -1428,13 +1431,23 @@ __device__ __forceinline__ void report_tour(const EvalArgs &a, int t)
 // to 10^5, S = 2^17: 4.2 ms a call (19.0 with one wavefront, 4.5 in the separate kernel); 1000
 // customers, windows of 300, S = 2^17: 33.1 (149.5 and 35.1). wave_one has to be inlined: as a call
 // it reads LDS through generic pointers, and keeps the blocks' registers in scratch memory (1000
-// customers, windows of 60, S = 2^20: 6.1 ms a call against 3.9).
+// customers, windows of 60, S = 2^20: 6.1 ms a call against 4.3).
 // Counts go to memory once per item: one atomic per scenario took 240 us of this launch there.
 //
-// Then the tours' results, straight to the caller's (pinned host) memory. Where nothing was marked,
-// each wavefront reports its share at once; otherwise the last workgroup to finish reports all.
+// Where something is marked, workgroups take chunks of items from a queue: marks are mostly few and
+// may come at any stride (the same scenarios of every tour, say). Up to kTailChunk items a chunk, so
+// that the queue's counter is no bottleneck, and about 16 chunks a workgroup.
+// 256 tours over 65,536 scenarios, four of them with windows of 500: 10.1 ms a call (8.9 without
+// them; 228 with items at a fixed stride and the last workgroup reporting every tour, 51 with 2,048
+// workgroups at a fixed stride); 1000 customers, S = 2^20, windows of 42, 3,279 marks: 2.1 ms (3.9
+// and 3.4).
+//
+// The tours' results go straight to the caller's (pinned host) memory. Where nothing was marked, each
+// wavefront reports its share at once; otherwise whoever finishes the last of a tour's items reports
+// the tour.
 constexpr int kTailWaves = 4;
-constexpr int kTailWords = (80 * 1024 - 64) / 4;  // two workgroups fill a compute unit's LDS
+constexpr int kTailChunk = 32;
+constexpr int kTailWords = (80 * 1024 - 16 * kTailChunk - 64) / 4;  // two workgroups fill a compute unit's LDS
 
 __global__ __launch_bounds__(64 * kTailWaves) __attribute__((amdgpu_waves_per_eu(2)))
 void split_tail_kernel(EvalArgs a)
@@ -1443,8 +1456,9 @@ void split_tail_kernel(EvalArgs a)
         LaneLds<256> L;
         int32_t words[kTailWords];
     } lds;
-    __shared__ unsigned long long s_wide;
-    __shared__ uint32_t s_before;
+    // the scenarios of a chunk's items that are left, for the history and one by one
+    __shared__ unsigned long long s_todo[kTailChunk], s_wide[kTailChunk];
+    __shared__ uint32_t s_chunk, s_marks;
     static_assert(sizeof lds == 4 * kTailWords && kTailWords >= 2 * (SPLIT_MAX_N + 1),
                   "the history fits, and a wavefront's prefix loads and g values of a maximal tour");
     const int lane = threadIdx.x & 63;
@@ -1458,78 +1472,131 @@ void split_tail_kernel(EvalArgs a)
     }
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void *)a.demand, (short)0, (int)a.lane_bytes, 0x00020000);
-    const long long nsb = (a.S + 63) / 64;
+    const long long nsb = (a.S + 63) / 64, items = T * nsb;
+    const int per = (int)min((long long)kTailChunk, max(1ll, items / (16ll * gridDim.x)));
     // the wavefronts that have room for a tour's arrays of their own
     const int room = 2 * (a.maxn + 1);
     const int nw = min(kTailWaves, kTailWords / room);
     int32_t *G = lds.words + wave * room;
-    for (long long k = blockIdx.x; k < T * nsb; k += gridDim.x) {
-        const int t = (int)(k / nsb);
-        const long long sb = k - (long long)t * nsb, s0 = sb * 64;
-        CostSums *sums = sums_at(a.sums, t, a.sums.by_item ? sb : sb & (kMaxSlots - 1));
-        if (wave == 0) {
-            const bool active = s0 + lane < a.S;
-            const long long scen = active ? s0 + lane : a.S - 1;
-            int32_t *cost = a.cost + (long long)t * a.ldc;
-            const int32_t mark = active ? cost[scen] : 0;
-            const bool todo = mark == kCostOvf;
-            unsigned long long wide = __ballot(mark == kCostWide);
-            int past = (int)__popcll(wide);
-            if (__any(todo)) {
-                LaneState<16, 256> st;
-                st.ovf = 1;
-                st.past = false;
-                st.err = false;
-                st.gres = 0;
-                if (a.lane_bytes != 0) {  // the demands lie within a buffer descriptor's reach
-                    const LaneTour tr = lane_tour(a, t);
-                    const uint32_t lane_off = (uint32_t)scen * 2u;
-                    uint16_t qA[16], qB[16], qC[16];
-                    lane_load_block<16>(rsrc, tr.rowoff, lane_off, 0, qA);
-                    lane_load_block<16>(rsrc, tr.rowoff, lane_off, 1, qB);
-                    lane_load_block<16>(rsrc, tr.rowoff, lane_off, 2, qC);
-                    lane_run<16, 256>(lds.L, tr, a.Q, rsrc, lane_off, qA, qB, qC, false, st);
-                }
-                past += (int)__popcll(__ballot(todo && (st.past || st.ovf)));
-                wide |= __ballot(todo && st.ovf);
-                uint32_t mine = 0;
-                if (todo && st.ovf == 0) {
-                    if (st.err) {
-                        atomicOr(&a.stats[t].err_demand, 1);
-                    } else {
-                        mine = (uint32_t)st.gres;
-                        cost[scen] = st.gres;
-                    }
-                }
-                const CostSums v = wave_costs(mine);
-                if (lane == 63) add_sums(sums, v);
-            }
+    for (;;) {
+        __syncthreads();  // the last chunk's LDS is free
+        if (threadIdx.x == 0) {
+            s_chunk = atomicAdd(&a.ctl->tail_head, 1u);
+            s_marks = 0;
+        }
+        __syncthreads();
+        const long long k0 = (long long)s_chunk * per;
+        if (k0 >= items) return;
+        const int cnt = (int)min((long long)per, items - k0);
+        const int t0 = (int)(k0 / nsb);
+        const long long sb0 = k0 - (long long)t0 * nsb;
+        // tour, scenario block and sums of the chunk's item i
+        auto item = [&](int i, int &t, long long &sb) {
+            const long long past = sb0 + i;  // within the tour, or past its end
+            const int dt = past < nsb ? 0 : (int)((uint32_t)past / (uint32_t)nsb);
+            t = t0 + dt;
+            sb = past - dt * nsb;
+        };
+        auto sums = [&](int t, long long sb) {
+            return sums_at(a.sums, t, a.sums.by_item ? sb : sb & (kMaxSlots - 1));
+        };
+        for (int i = wave; i < cnt; i += kTailWaves) {
+            int t;
+            long long sb;
+            item(i, t, sb);
+            const long long scen = sb * 64 + lane;
+            const int32_t mark = scen < a.S ? a.cost[(long long)t * a.ldc + scen] : 0;
+            const unsigned long long todo = __ballot(mark == kCostOvf), wide = __ballot(mark == kCostWide);
             if (lane == 0) {
-                if (a.recount && past) atomicAdd(&a.stats[t].ovf_count, past);
-                s_wide = wide;
+                s_todo[i] = todo;
+                s_wide[i] = wide;
+                if (todo | wide) s_marks = 1;  // whoever writes it, the same value
             }
         }
         __syncthreads();
-        if (wave < nw) {
-            unsigned long long m = s_wide;
-            for (int turn = 0; m; turn = turn + 1 < nw ? turn + 1 : 0) {
-                const int j = __builtin_ctzll(m);
-                m &= m - 1;
-                if (turn != wave) continue;
-                const unsigned long long c = wave_one(a, t, s0 + j, G, G + a.maxn + 1);
-                const unsigned long long q = c * c;
-                if (lane == 0) add_sums(sums, CostSums{c, q & 0xFFFFFFFFull, q >> 32});
+        const bool marks = s_marks != 0;
+        if (marks && wave == 0) {
+            for (int i = 0; i < cnt; ++i) {
+                const unsigned long long todo = s_todo[i];
+                unsigned long long wide = s_wide[i];
+                if ((todo | wide) == 0) continue;
+                int t;
+                long long sb;
+                item(i, t, sb);
+                int past = (int)__popcll(wide);
+                if (todo) {
+                    const bool mine = (todo >> lane) & 1;
+                    const long long scen = min(sb * 64 + lane, (long long)a.S - 1);
+                    LaneState<16, 256> st;
+                    st.ovf = 1;
+                    st.past = false;
+                    st.err = false;
+                    st.gres = 0;
+                    if (a.lane_bytes != 0) {  // the demands lie within a buffer descriptor's reach
+                        const LaneTour tr = lane_tour(a, t);
+                        const uint32_t lane_off = (uint32_t)scen * 2u;
+                        uint16_t qA[16], qB[16], qC[16];
+                        lane_load_block<16>(rsrc, tr.rowoff, lane_off, 0, qA);
+                        lane_load_block<16>(rsrc, tr.rowoff, lane_off, 1, qB);
+                        lane_load_block<16>(rsrc, tr.rowoff, lane_off, 2, qC);
+                        lane_run<16, 256>(lds.L, tr, a.Q, rsrc, lane_off, qA, qB, qC, false, st, false,
+                                          mine);
+                    }
+                    past += (int)__popcll(__ballot(mine && (st.past || st.ovf)));
+                    wide |= __ballot(mine && st.ovf);
+                    uint32_t c = 0;
+                    if (mine && st.ovf == 0) {
+                        if (st.err) {
+                            atomicOr(&a.stats[t].err_demand, 1);
+                        } else {
+                            c = (uint32_t)st.gres;
+                            a.cost[(long long)t * a.ldc + scen] = st.gres;
+                        }
+                    }
+                    const CostSums v = wave_costs(c);
+                    if (lane == 63) add_sums(sums(t, sb), v);
+                }
+                if (lane == 0) {
+                    if (a.recount && past) atomicAdd(&a.stats[t].ovf_count, past);
+                    s_wide[i] = wide;
+                }
             }
         }
-        __syncthreads();  // the arrays and s_wide are free for the next item
+        if (marks) __syncthreads();
+        if (marks && wave < nw) {
+            int turn = 0;
+            for (int i = 0; i < cnt; ++i) {
+                int t;
+                long long sb;
+                item(i, t, sb);
+                for (unsigned long long m = s_wide[i]; m; m &= m - 1) {
+                    const int j = __builtin_ctzll(m);
+                    const bool mine = turn == wave;
+                    turn = turn + 1 < nw ? turn + 1 : 0;
+                    if (!mine) continue;
+                    const unsigned long long c = wave_one(a, t, sb * 64 + j, G, G + a.maxn + 1);
+                    const unsigned long long q = c * c;
+                    if (lane == 0) add_sums(sums(t, sb), CostSums{c, q & 0xFFFFFFFFull, q >> 32});
+                }
+            }
+        }
+        // every wavefront's additions are in memory before the chunk's items count as done (the
+        // fence writes a whole L2 back: none where there was nothing to add)
+        if (marks) {
+            __threadfence();
+            __syncthreads();
+        }
+        for (int t = t0 + wave; (t - t0) * nsb < sb0 + cnt; t += kTailWaves) {
+            const long long lo = max(0ll, sb0 - (t - t0) * nsb);
+            const long long hi = min(nsb, sb0 + cnt - (t - t0) * nsb);
+            const uint32_t mine = (uint32_t)(hi - lo);
+            uint32_t before = 0;
+            if (lane == 0) before = atomicAdd(&a.stats[t].done, mine);
+            if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) + mine != (uint32_t)nsb) continue;
+            __threadfence();
+            report_tour(a, t);
+        }
     }
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0) s_before = atomicAdd(&a.ctl->done, 1u);
-    __syncthreads();
-    if (s_before != gridDim.x - 1) return;
-    __threadfence();
-    for (long long t = wave; t < T; t += kTailWaves) report_tour(a, (int)t);
 }
 
 // ------------------------------------------------------------------------- small evaluations
