@@ -1150,14 +1150,22 @@ split_status split_autotune(split_ctx *ctx, const int32_t *tours, const int64_t 
         return SPLIT_OK;
     };
 
-    split_tuning win = saved;
+    // The library's own choice (block length by window, one launch for short tours) is one of the
+    // candidates. Where an explicit one comes within kTie of it, the explicit one is taken: that much
+    // is noise, and it spares later calls the look at the windows.
+    constexpr double kTie = 1.04;
+    const split_tuning own = {SPLIT_FORM_AUTO, 0, 0, 0, 0};
+    double own_ms = 0.0;
+    st = measure(own, S, &own_ms);
+    if (st != SPLIT_OK) return finish(st);
+    split_tuning win = own;
     double win_ms = 1e300;
     const Plan lane_probe = make_plan(ctx, split_tuning{SPLIT_FORM_LANE, 0, 0, 0, 0}, S, ld, Q,
                                       T, bi.maxn, bi.max_id, bi.minn == bi.maxn, ctx->inst.max_arc);
     if (lane_probe.form == SPLIT_FORM_LANE) {
         // the block length first (it follows the window lengths, so the demand law), then the
-        // grid and the order with that block length. 8-state blocks hand windows longer than
-        // about 24 positions to the wave kernel, which costs far more than any block saves: a
+        // grid and the order with that block length. 8-state blocks leave windows longer than
+        // about 24 positions to the tail kernel, which costs far more than any block saves: a
         // probe on the first scenarios drops them when they leave more scenarios there.
         const int64_t s_fb = S < 4096 ? S : 4096;
         int64_t fb16 = 0, fb8 = 0;
@@ -1166,13 +1174,13 @@ split_status split_autotune(split_ctx *ctx, const int32_t *tours, const int64_t 
         st = fallbacks(split_tuning{SPLIT_FORM_LANE, 0, 0, 0, 8}, s_fb, &fb8);
         if (st != SPLIT_OK) return finish(st);
         int32_t block = 16;
-        for (int32_t lb : {16, 8}) {
+        for (int32_t lb : {16, 8, 0}) {
             if (lb == 8 && fb8 > fb16) continue;
             const split_tuning c = {SPLIT_FORM_LANE, 0, 0, 0, lb};
             double ms = 0.0;
             st = measure(c, S, &ms);
             if (st != SPLIT_OK) return finish(st);
-            if (ms < win_ms) {
+            if (lb != 0 ? ms < win_ms : kTie * ms < win_ms) {
                 win_ms = ms;
                 win = c;
                 block = lb;
@@ -1210,6 +1218,20 @@ split_status split_autotune(split_ctx *ctx, const int32_t *tours, const int64_t 
                 win_ms = ms;
                 win = c;
             }
+        }
+    }
+    if (win_ms > own_ms) {
+        // once more, side by side, before the library's own choice is taken
+        double ms = 0.0;
+        st = measure(win, S, &ms);
+        if (st != SPLIT_OK) return finish(st);
+        win_ms = ms < win_ms ? ms : win_ms;
+        st = measure(own, S, &ms);
+        if (st != SPLIT_OK) return finish(st);
+        own_ms = ms < own_ms ? ms : own_ms;
+        if (win_ms > kTie * own_ms) {
+            win = own;
+            win_ms = own_ms;
         }
     }
     // leave the context's latest evaluation the full one under the chosen tuning

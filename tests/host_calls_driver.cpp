@@ -155,7 +155,10 @@ hipError_t launch_lane(const EvalArgs &a, hipStream_t)
 {
     return launched(a.lane_block == 0 ? "lane0" : a.lane_block == 8 ? "lane8" : "lane16");
 }
-hipError_t launch_pair(const EvalArgs &, hipStream_t) { return launched("pair"); }
+hipError_t launch_pair(const EvalArgs &a, hipStream_t)
+{
+    return launched(a.lane_block == 0 ? "pair0" : "pair16");
+}
 hipError_t launch_wave_all(const EvalArgs &, hipStream_t) { return launched("wave"); }
 hipError_t launch_small(const SmallArgs &a, hipStream_t)
 {
@@ -356,6 +359,46 @@ void scenarios_after_a_failed_allocation()
     }
 }
 
+// One tour 1..n over S scenarios of 5 units each.
+split_tuning autotuned(int n, int64_t S, int Q, double *ms)
+{
+    Ctx c(n);
+    std::vector<int32_t> tour, cost((size_t)S);
+    for (int k = 1; k <= n; ++k) tour.push_back(k);
+    const int64_t ptr[2] = {0, n};
+    std::vector<int16_t> dem((size_t)n * S, 5);
+    split_tuning best = {}, now = {};
+    CHECK(split_autotune(c.c, tour.data(), ptr, 1, dem.data(), S, S, Q, cost.data(), S, 2, nullptr,
+                         &best, ms) == SPLIT_OK);
+    CHECK(split_tuning_get(c.c, &now) == SPLIT_OK);
+    CHECK(memcmp(&best, &now, sizeof now) == 0);
+    return best;
+}
+
+// The autotuner times the library's own choice too and installs nothing slower.
+void autotune_times_the_own_choice()
+{
+    double ms = 0.0;
+    // a short tour: one launch against three
+    cost_us = {{"prep", 5}, {"tail", 5}, {"small", 8}, {"wave", 12},
+               {"lane0", 20}, {"lane8", 20}, {"lane16", 20}};
+    split_tuning t = autotuned(20, 1000, 100, &ms);
+    CHECK(t.form == SPLIT_FORM_AUTO && t.lane_block == 0 && t.lane_per_cu == 0 && t.wave_grid == 0);
+    CHECK(ms > 0.0079 && ms < 0.0081);
+    // long windows: blocks of 16 run the tour before the tail kernel does it again
+    cost_us = {{"prep", 5}, {"tail", 100}, {"pair0", 5}, {"pair16", 70}, {"lane0", 5},
+               {"lane8", 105}, {"lane16", 105}, {"wave", 9000}};
+    t = autotuned(700, 20000, 1200, &ms);
+    CHECK(t.form != SPLIT_FORM_WAVE && t.lane_block == 0);
+    CHECK(ms < 0.1101);
+    // a difference within the noise: an explicit choice
+    cost_us = {{"prep", 5}, {"tail", 5}, {"lane0", 40}, {"lane8", 40.5}, {"lane16", 60},
+               {"wave", 9000}};
+    t = autotuned(200, 65536, 60, &ms);
+    CHECK(t.form == SPLIT_FORM_LANE && t.lane_block == 8);
+    cost_us.clear();
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
@@ -363,6 +406,7 @@ struct Scenario {
 const Scenario kScenarios[] = {
     {"flag-of-a-failed-pass", flag_of_a_failed_pass},
     {"scenarios-after-a-failed-allocation", scenarios_after_a_failed_allocation},
+    {"autotune-times-the-own-choice", autotune_times_the_own_choice},
 };
 
 }  // namespace

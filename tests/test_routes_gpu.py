@@ -103,3 +103,20 @@ def test_scenarios_finished_one_by_one_fill_the_chip(sg, n, grid, mean, Q):
     assert torch.equal(cost, want) and st.n_fallback == S
     assert ms <= 5 * wave
     ctx.close()
+
+
+@pytest.mark.parametrize("n,S,law,Q", [(20, 1000, "uniform", 100), (700, 20_000, "poisson", 1200)])
+def test_autotuned_calls_are_no_slower_than_the_default(sg, n, S, law, Q):
+    # a short tour (one launch by default) and windows of 60 (no blocks of 16 by default)
+    ctx = sg.SplitContext(0)
+    ctx.set_coords(gen.coords(64, n))
+    dem = (poisson(n, S, 20.0) if law == "poisson"
+           else torch.randint(1, 21, (n, S), dtype=torch.int16, device="cuda"))
+    tour = gen.tour(64, n, n)
+    cost = torch.empty(S, dtype=torch.int32, device="cuda")
+    default = least_ms(lambda: ctx.eval(tour, dem, Q, cost=cost), inner=50)
+    tu, _, _ = ctx.autotune([tour], dem, Q, reps=20)
+    tuned = least_ms(lambda: ctx.eval(tour, dem, Q, cost=cost), inner=50)
+    print(f"[routes] n={n} S={S}: default {default:.4f} ms, {tu} {tuned:.4f} ms", flush=True)
+    assert tuned <= 1.15 * default
+    ctx.close()
