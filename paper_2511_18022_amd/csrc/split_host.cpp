@@ -186,8 +186,9 @@ struct split_graph {
     hipStream_t cap_stream = nullptr;
     char *h_stage[kGraphSlots] = {};
     TourResult *h_stats[kGraphSlots] = {};
-    hipGraph_t graph[kGraphSlots] = {};
-    hipGraphExec_t exec[kGraphSlots] = {};
+    // per host slot; [1] with the pair kernel, for replays of long tours (where plan.pair)
+    hipGraph_t graph[kGraphSlots][2] = {};
+    hipGraphExec_t exec[kGraphSlots][2] = {};
     hipEvent_t done[kGraphSlots] = {};
     bool used[kGraphSlots] = {};
     int next = 0;
@@ -1300,8 +1301,10 @@ void split_graph_destroy(split_graph *gr)
         for (int k = 0; k < kGraphSlots; ++k)
             if (gr->used[k]) (void)hipEventSynchronize(gr->done[k]);
         for (int k = 0; k < kGraphSlots; ++k) {
-            if (gr->exec[k]) (void)hipGraphExecDestroy(gr->exec[k]);
-            if (gr->graph[k]) (void)hipGraphDestroy(gr->graph[k]);
+            for (int pair = 0; pair < 2; ++pair) {
+                if (gr->exec[k][pair]) (void)hipGraphExecDestroy(gr->exec[k][pair]);
+                if (gr->graph[k][pair]) (void)hipGraphDestroy(gr->graph[k][pair]);
+            }
             if (gr->done[k]) (void)hipEventDestroy(gr->done[k]);
             if (gr->h_stage[k]) (void)hipHostFree(gr->h_stage[k]);
             if (gr->h_stats[k]) (void)hipHostFree(gr->h_stats[k]);
@@ -1397,22 +1400,29 @@ split_status split_graph_create(split_ctx *ctx, int32_t max_T, int64_t max_total
         if (hipEventCreateWithFlags(&gr->done[k], hipEventDisableTiming) != hipSuccess)
             return bail(fail(ctx, SPLIT_E_HIP, "split_graph_create: hipEventCreate failed"));
     }
-    // one graph per host slot: the kernels read the slot's header and report to its results
-    for (int k = 0; k < kGraphSlots; ++k) {
+    // One graph per host slot: the kernels read the slot's header and report to its results. Where
+    // the instance's tours may run in the pair kernel, one with it and one without: which is faster
+    // follows the tours of a replay (S = 10,000, graph of one tour over 1000 customers: 8 customers
+    // 62 us with, 47 without; 100 customers 64 and 56; 400 customers 81 and 92 with blocks of 16 before the pair kernel).
+    for (int v = 0; v < kGraphSlots * 2; ++v) {
+        const int k = v / 2, pair = v % 2;
+        if (pair && !gr->plan.pair) continue;
+        Plan plan = gr->plan;
+        plan.pair = pair != 0;
         if (hipStreamBeginCapture(gr->cap_stream, hipStreamCaptureModeThreadLocal) != hipSuccess)
             return bail(fail(ctx, SPLIT_E_HIP, "split_graph_create: hipStreamBeginCapture failed"));
         capturing = true;
         st = enqueue_kernels(ctx, gr->inst, gr->buf, gr->layout, gr->h_stage[k], gr->h_stats[k],
-                             gr->plan, demand, S, ld, Q, cost, ldc, gr->cap_stream, false);
+                             plan, demand, S, ld, Q, cost, ldc, gr->cap_stream, false);
         if (st != SPLIT_OK) return bail(st);
         hipGraph_t graph = nullptr;
         const hipError_t e = hipStreamEndCapture(gr->cap_stream, &graph);
         capturing = false;
-        gr->graph[k] = graph;
+        gr->graph[k][pair] = graph;
         if (e != hipSuccess || !graph)
             return bail(hip_fail(ctx, e, "split_graph_create: hipStreamEndCapture"));
-        if (hipGraphInstantiate(&gr->exec[k], graph, nullptr, nullptr, 0) != hipSuccess) {
-            gr->exec[k] = nullptr;
+        if (hipGraphInstantiate(&gr->exec[k][pair], graph, nullptr, nullptr, 0) != hipSuccess) {
+            gr->exec[k][pair] = nullptr;
             return bail(fail(ctx, SPLIT_E_HIP, "split_graph_create: hipGraphInstantiate failed"));
         }
     }
@@ -1441,7 +1451,8 @@ split_status split_graph_launch(split_graph *gr, const int32_t *tours, const int
     if (gr->used[k]) HIP_TRY(ctx, hipEventSynchronize(gr->done[k]));
     stage_write(gr->h_stage[k], gr->layout, tours, tour_ptr, T, gr->order);
     hipStream_t stream = (hipStream_t)hip_stream;
-    HIP_TRY(ctx, hipGraphLaunch(gr->exec[k], stream));
+    const int pair = gr->plan.pair && bi.maxn >= kPairMinN ? 1 : 0;
+    HIP_TRY(ctx, hipGraphLaunch(gr->exec[k][pair], stream));
     HIP_TRY(ctx, hipEventRecord(gr->done[k], stream));
     gr->used[k] = true;
     gr->last = k;

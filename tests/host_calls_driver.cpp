@@ -399,6 +399,45 @@ void autotune_times_the_own_choice()
     cost_us.clear();
 }
 
+// A replay takes the two-wavefront kernel where its own tours are long enough for it, not where the
+// instance is.
+void graph_replays_choose_by_their_tours()
+{
+    const int N = 400;
+    const int64_t S = 640;
+    for (int32_t block : {0, 16, 8}) {
+        Ctx c(N);
+        const split_tuning tu = {SPLIT_FORM_AUTO, 0, 0, 0, block};
+        CHECK(split_tuning_set(c.c, &tu) == SPLIT_OK);
+        std::vector<int16_t> dem((size_t)N * S, 5);
+        std::vector<int32_t> cost((size_t)4 * S), tours;
+        split_graph *g = nullptr;
+        CHECK(split_graph_create(c.c, 4, 4 * N, dem.data(), S, S, 100, cost.data(), S, &g) == SPLIT_OK);
+        const std::string lane = "lane" + std::to_string(block), pair = "pair" + std::to_string(block);
+        auto replay = [&](std::vector<int> lens, bool two) {
+            std::vector<int64_t> ptr = {0};
+            tours.clear();
+            for (int n : lens) {
+                for (int k = 1; k <= n; ++k) tours.push_back(k);
+                ptr.push_back((int64_t)tours.size());
+            }
+            trace.clear();
+            CHECK(split_graph_launch(g, tours.data(), ptr.data(), (int32_t)lens.size(), nullptr) == SPLIT_OK);
+            CHECK(split_graph_stats(g, nullptr, nullptr) == SPLIT_OK);
+            two = two && block != 8;  // 8-state blocks are never halved
+            CHECK(count(pair.c_str()) == (two ? 1 : 0) && count(lane.c_str()) == (two ? 0 : 1));
+            CHECK(count("prep") == 1 && count("tail") == 1);
+        };
+        for (int rep = 0; rep < 3; ++rep) {  // both host slots
+            replay({8}, false);
+            replay({400}, true);
+            replay({100, 300, 319}, false);
+            replay({12, 320}, true);
+        }
+        split_graph_destroy(g);
+    }
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
@@ -407,6 +446,7 @@ const Scenario kScenarios[] = {
     {"flag-of-a-failed-pass", flag_of_a_failed_pass},
     {"scenarios-after-a-failed-allocation", scenarios_after_a_failed_allocation},
     {"autotune-times-the-own-choice", autotune_times_the_own_choice},
+    {"graph-replays-choose-by-their-tours", graph_replays_choose_by_their_tours},
 };
 
 }  // namespace
