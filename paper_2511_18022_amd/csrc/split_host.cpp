@@ -42,7 +42,6 @@ constexpr int32_t kLaneStaticPerCu = kMaxLanePerCu;  // fixed-stride grid: all r
 constexpr int64_t kLaneStaticMaxRounds = 16;         // and at most this many items each
 constexpr int32_t kTailPerCu = 2;       // the tail kernel's LDS allows 2 workgroups per CU
 constexpr int32_t kPairPerCu = 4;       // as many of the pair kernel's: two wavefronts a SIMD
-constexpr int32_t kPairMinN = 320;
 constexpr int32_t kPairMaxQ = 2047;     // a demand of Q itself stays within the 16-bit bound
 constexpr int64_t kClassMaxArc = 2047;  // 16 states times 2 max_arc: below 2^16
 
@@ -514,6 +513,15 @@ SumSlots sum_slots(int form, int32_t T_grid, int64_t S)
     return s;
 }
 
+// Shortest tour that two wavefronts an item pay for. The join takes what half of a tour of fewer than
+// about 300 positions saves; past two items a compute unit the halves share their SIMDs, and it takes
+// a little more. Whole calls, the pair kernel against the lane kernel, 512 items: 66.3 us against 70.7
+// at 320 customers, 71.8 against 78.7 at 400; 768 items: 69.2 and 73.2 at 320, 72.9 and 74.0 at 340;
+// 1024 items: 72.8 and 75.4 at 320, 74.3 and 74.1 at 340, 78.4 and 76.1 at 360, 73.3 and 80.4 at 380,
+// 86.5 and 93.2 at 500. (Kernels alone, 64 items: 31 us against 25 at 128 positions, 39 and 37 at 256,
+// 48 and 62 at 512, 71 and 108 at 1000.)
+int32_t pair_min_n(const split_ctx *ctx, int64_t items) { return items <= 2ll * ctx->cus ? 320 : 380; }
+
 // Launch configuration from the tuning. T_grid bounds T; maxn and max_id bound the tours;
 // `uniform`: every tour of the launch has the same length (so has every work item).
 Plan make_plan(const split_ctx *ctx, const split_tuning &tu, int64_t S, int64_t ld, int32_t Q,
@@ -549,11 +557,9 @@ Plan make_plan(const split_ctx *ctx, const split_tuning &tu, int64_t S, int64_t 
     p.lane_block = by_class ? 0 : tu.lane_block == 8 ? 8 : 16;
     p.tail_grid = ctx->cus * kTailPerCu;
     // Two wavefronts per item where they all run at once, at most two on a SIMD: more items than
-    // that keep the chip busy with one each. The join takes what half of a tour of fewer than about
-    // 300 positions saves (64 items: 31 us against 25 at 128 positions, 39 against 37 at 256, 48
-    // against 62 at 512, 71 against 108 at 1000).
-    p.pair = p.form == SPLIT_FORM_LANE && lib_choice && p.lane_block != 8 && maxn >= kPairMinN &&
-             max_arc <= kClassMaxArc && Q <= kPairMaxQ && items <= (int64_t)ctx->cus * kPairPerCu;
+    // that keep the chip busy with one each.
+    p.pair = p.form == SPLIT_FORM_LANE && lib_choice && p.lane_block != 8 &&
+             maxn >= pair_min_n(ctx, items) && max_arc <= kClassMaxArc && Q <= kPairMaxQ && items <= (int64_t)ctx->cus * kPairPerCu;
     p.wave_grid = tu.wave_grid > 0 ? tu.wave_grid : 65536;
     p.maxn = maxn;
     return p;
@@ -701,8 +707,9 @@ split_status eval_batch(split_ctx *ctx, const char *who, const int32_t *tours,
     const Plan p = make_plan(ctx, ctx->tuning, S, ld, Q, T, bi.maxn, bi.max_id,
                              bi.minn == bi.maxn, ctx->inst.max_arc);
     // A short tour over few scenarios, all choices left to the library: one launch instead of three,
-    // which take longer than the work (20 customers, S = 1000: 27.7 us a call against 40.5; the bounds
-    // keep the scan of 32 predecessors and the 128 parts to add up small). Short arcs keep every
+    // which take longer than the work (1 to 32 customers, S = 256 to 32,768: 23 to 30 us a call against
+    // 32 to 47, 1.4 to 1.6 times at every corner; the bounds keep the scan of 32 predecessors and the
+    // 128 parts to add up small). Short arcs keep every
     // suffix offset within 16 bits, so only the demand bound can count towards n_fallback.
     const split_tuning &tu = ctx->tuning;
     if (T == 1 && bi.maxn <= kSmallN && S <= kSmallS && ctx->inst.max_arc <= kClassMaxArc &&
@@ -1451,7 +1458,7 @@ split_status split_graph_launch(split_graph *gr, const int32_t *tours, const int
     if (gr->used[k]) HIP_TRY(ctx, hipEventSynchronize(gr->done[k]));
     stage_write(gr->h_stage[k], gr->layout, tours, tour_ptr, T, gr->order);
     hipStream_t stream = (hipStream_t)hip_stream;
-    const int pair = gr->plan.pair && bi.maxn >= kPairMinN ? 1 : 0;
+    const int pair = gr->plan.pair && bi.maxn >= pair_min_n(ctx, (gr->S + 63) / 64 * gr->max_T) ? 1 : 0;
     HIP_TRY(ctx, hipGraphLaunch(gr->exec[k][pair], stream));
     HIP_TRY(ctx, hipEventRecord(gr->done[k], stream));
     gr->used[k] = true;

@@ -438,6 +438,24 @@ void graph_replays_choose_by_their_tours()
     }
 }
 
+// Two wavefronts an item: where the tours are long enough for the number of items.
+void two_wavefronts_by_length_and_items()
+{
+    const struct { int n; int64_t items; bool two; } cases[] = {
+        {319, 512, false}, {320, 1, true}, {320, 512, true}, {320, 513, false}, {379, 1024, false},
+        {380, 513, true}, {380, 1024, true}, {380, 1025, false}, {1000, 1024, true}};
+    for (const auto &x : cases) {
+        Ctx c(x.n);
+        const int64_t S = 64 * x.items;
+        std::vector<int32_t> tour, cost((size_t)S);
+        for (int k = 1; k <= x.n; ++k) tour.push_back(k);
+        std::vector<int16_t> dem((size_t)x.n * S, 5);
+        trace.clear();
+        CHECK(split_eval(c.c, tour.data(), x.n, dem.data(), S, S, 100, cost.data(), nullptr, nullptr) == SPLIT_OK);
+        CHECK(count("pair0") == (x.two ? 1 : 0) && count("lane0") == (x.two ? 0 : 1));
+    }
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
@@ -447,6 +465,7 @@ const Scenario kScenarios[] = {
     {"scenarios-after-a-failed-allocation", scenarios_after_a_failed_allocation},
     {"autotune-times-the-own-choice", autotune_times_the_own_choice},
     {"graph-replays-choose-by-their-tours", graph_replays_choose_by_their_tours},
+    {"two-wavefronts-by-length-and-items", two_wavefronts_by_length_and_items},
 };
 
 }  // namespace
