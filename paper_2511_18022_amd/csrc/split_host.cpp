@@ -514,13 +514,13 @@ SumSlots sum_slots(int form, int32_t T_grid, int64_t S)
 }
 
 // Shortest tour that two wavefronts an item pay for. The join takes what half of a tour of fewer than
-// about 300 positions saves; past two items a compute unit the halves share their SIMDs, and it takes
+// about 300 positions saves; past three items a compute unit the halves share their SIMDs, and it takes
 // a little more. Whole calls, the pair kernel against the lane kernel, 512 items: 66.3 us against 70.7
 // at 320 customers, 71.8 against 78.7 at 400; 768 items: 69.2 and 73.2 at 320, 72.9 and 74.0 at 340;
 // 1024 items: 72.8 and 75.4 at 320, 74.3 and 74.1 at 340, 78.4 and 76.1 at 360, 73.3 and 80.4 at 380,
 // 86.5 and 93.2 at 500. (Kernels alone, 64 items: 31 us against 25 at 128 positions, 39 and 37 at 256,
 // 48 and 62 at 512, 71 and 108 at 1000.)
-int32_t pair_min_n(const split_ctx *ctx, int64_t items) { return items <= 2ll * ctx->cus ? 320 : 380; }
+int32_t pair_min_n(const split_ctx *ctx, int64_t items) { return items <= 3ll * ctx->cus ? 320 : 380; }
 
 // Launch configuration from the tuning. T_grid bounds T; maxn and max_id bound the tours;
 // `uniform`: every tour of the launch has the same length (so has every work item).

@@ -442,8 +442,8 @@ void graph_replays_choose_by_their_tours()
 void two_wavefronts_by_length_and_items()
 {
     const struct { int n; int64_t items; bool two; } cases[] = {
-        {319, 512, false}, {320, 1, true}, {320, 512, true}, {320, 513, false}, {379, 1024, false},
-        {380, 513, true}, {380, 1024, true}, {380, 1025, false}, {1000, 1024, true}};
+        {319, 768, false}, {320, 1, true}, {320, 768, true}, {320, 769, false}, {379, 1024, false},
+        {380, 769, true}, {380, 1024, true}, {380, 1025, false}, {1000, 1024, true}};
     for (const auto &x : cases) {
         Ctx c(x.n);
         const int64_t S = 64 * x.items;
