@@ -293,10 +293,11 @@ split_status ensure_buffers(split_ctx *ctx, EvalBuffers &b, int32_t T, int64_t t
         b.cap_T = nt;
     }
     if (g_sums) {
+        const int64_t nb = room(sum_bytes, 65536);
         b.cap_sums = 0;
-        if (!grow(&b.d_sums, (size_t)sum_bytes))
+        if (!grow(&b.d_sums, (size_t)nb))
             return fail(ctx, SPLIT_E_NOMEM, "allocation of the cost sums failed");
-        b.cap_sums = sum_bytes;
+        b.cap_sums = nb;
     }
     if (g_ctl && hipMalloc(&b.d_ctl, sizeof(BatchCtl)) != hipSuccess)
         return fail(ctx, SPLIT_E_NOMEM, "allocation of the batch counters failed");
@@ -508,7 +509,11 @@ SumSlots sum_slots(int form, int32_t T_grid, int64_t S)
                         (nsb <= kMaxSlots || nsb * T_grid <= ((int64_t)1 << 22))
                     ? 1
                     : 0;
-    s.slots = s.by_item ? nsb : kMaxSlots;
+    // several tours that add: a power of two that their additions per tour can fill, at most
+    const int64_t adds = form == SPLIT_FORM_WAVE ? S : nsb;
+    int64_t few = 1;
+    while (few < adds && few < kMaxSlots) few *= 2;
+    s.slots = s.by_item ? nsb : T_grid > 1 ? few : kMaxSlots;
     s.stride = s.by_item || T_grid > 1 ? (int32_t)sizeof(CostSums) : kSlotStride;
     return s;
 }

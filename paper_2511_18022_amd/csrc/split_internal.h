@@ -53,10 +53,11 @@ struct __attribute__((aligned(32))) CostSums {
 //  by item   one entry per work item, stored by it. For several tours: a workgroup that ends on
 //            atomic additions holds its place until they are done, which made 256 tours over 65,536
 //            scenarios 1.7% slower (8,710 us against 8,560).
-//  added     kMaxSlots entries, zeroed by the prep kernel and added to by the scenario's block (or
-//            the scenario), each on a memory channel of its own: additions to one line, or to lines
-//            of one channel, follow each other at about 11 ns. For one tour, whose workgroups go
-//            on to their next item meanwhile, and for the other forms.
+//  added     a power of two of entries, kMaxSlots for one tour and as many as its additions can fill
+//            for several; zeroed by the prep kernel and added to by the scenario's block (or the
+//            scenario), each on a memory channel of its own: additions to one line, or to lines of
+//            one channel, follow each other at about 11 ns. For one tour, whose workgroups go on to
+//            their next item meanwhile, and for the other forms.
 struct SumSlots {
     char *base;
     int64_t slots;

@@ -83,7 +83,7 @@ __global__ __launch_bounds__(1024) void split_prep_kernel(PrepArgs a)
     const int32_t *tour = a.src_tours + p0;
     const int n = (int)(p1 - p0);
     const int64_t ab = p0 + (int64_t)t * (1 + kRowPad);
-    if (!a.sums.by_item && tid < kMaxSlots) *sums_at(a.sums, t, tid) = CostSums{0, 0, 0};
+    if (!a.sums.by_item && tid < a.sums.slots) *sums_at(a.sums, t, tid) = CostSums{0, 0, 0};
     int64_t *rowoff = a.tour.rowoff + ab;
     uint32_t *rowoff32 = a.tour.rowoff32 + ab;
     int32_t *w = a.tour.w + ab;
@@ -190,7 +190,7 @@ __device__ __forceinline__ void item_costs(const SumSlots &s, int t, long long s
         if (s.by_item)
             *sums_at(s, t, sb) = v;
         else
-            add_sums(sums_at(s, t, sb & (kMaxSlots - 1)), v);
+            add_sums(sums_at(s, t, sb & (s.slots - 1)), v);
     }
 }
 
@@ -1383,7 +1383,7 @@ __global__ __launch_bounds__(64) void split_wave_kernel(EvalArgs a)
         const uint32_t c = wave_one(a, t, scen, G, PP);
         if (threadIdx.x == 0) {
             const unsigned long long q = (unsigned long long)c * c;
-            add_sums(sums_at(a.sums, t, scen & (kMaxSlots - 1)),
+            add_sums(sums_at(a.sums, t, scen & (a.sums.slots - 1)),
                      CostSums{c, q & 0xFFFFFFFFull, q >> 32});
         }
     }
@@ -1498,7 +1498,7 @@ void split_tail_kernel(EvalArgs a)
             sb = past - dt * nsb;
         };
         auto sums = [&](int t, long long sb) {
-            return sums_at(a.sums, t, a.sums.by_item ? sb : sb & (kMaxSlots - 1));
+            return sums_at(a.sums, t, a.sums.by_item ? sb : sb & (a.sums.slots - 1));
         };
         for (int i = wave; i < cnt; i += kTailWaves) {
             int t;

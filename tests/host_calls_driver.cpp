@@ -28,6 +28,7 @@ std::map<std::string, double> cost_us;   // simulated duration of a launch
 std::map<std::string, int> fail_launch;  // launches of this name that fail from now on
 int fail_malloc = 0;                     // the fail_malloc-th device allocation from now fails
 int mallocs = 0, syncs = 0;
+size_t malloc_bytes = 0;
 double clock_us = 0.0;
 std::vector<std::string> *capture = nullptr;
 
@@ -87,6 +88,7 @@ const char *hipGetErrorString(hipError_t) { return "a failure that the test aske
 hipError_t hipMalloc(void **p, size_t n)
 {
     ++mallocs;
+    malloc_bytes += n;
     if (fail_malloc > 0 && --fail_malloc == 0) {
         *p = nullptr;
         return hipErrorOutOfMemory;
@@ -456,6 +458,34 @@ void two_wavefronts_by_length_and_items()
     }
 }
 
+// The cost sums of a batch follow its scenarios, and grow with room to spare.
+void sums_of_batches()
+{
+    const int N = 20, T = 4000;
+    Ctx one(N), c(N);
+    std::vector<int32_t> tours, cost((size_t)8 * 20000);
+    std::vector<int64_t> ptr = {0};
+    for (int t = 0; t < T; ++t) {
+        for (int k = 1; k <= 5; ++k) tours.push_back(k);
+        ptr.push_back((int64_t)tours.size());
+    }
+    std::vector<int16_t> dem((size_t)N * 20000, 5);
+    auto batch = [&](const Ctx &on, int32_t n_tours, int64_t S) {
+        return split_eval_batch(on.c, tours.data(), ptr.data(), n_tours, dem.data(), S, 20000, 100,
+                                cost.data(), S, nullptr, nullptr, nullptr);
+    };
+    // per tour 16 bytes a position with its padding (and a quarter to spare), flags, and for one
+    // scenario one entry of sums
+    malloc_bytes = 0;
+    CHECK(batch(one, T, 1) == SPLIT_OK);
+    CHECK(malloc_bytes <= (size_t)T * ((16 * (6 + kRowPad) + 64) * 5 / 4 + 80));
+    // a batch over ever more scenarios: the device is synchronized and buffers replaced now and then
+    CHECK(batch(c, 8, 5000) == SPLIT_OK);
+    syncs = mallocs = 0;
+    for (int64_t S = 5000; S <= 20000; S += 64) CHECK(batch(c, 8, S) == SPLIT_OK);
+    CHECK(syncs <= 8 && mallocs <= 8);  // four times as much, a quarter to spare each time
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
@@ -466,6 +496,7 @@ const Scenario kScenarios[] = {
     {"autotune-times-the-own-choice", autotune_times_the_own_choice},
     {"graph-replays-choose-by-their-tours", graph_replays_choose_by_their_tours},
     {"two-wavefronts-by-length-and-items", two_wavefronts_by_length_and_items},
+    {"sums-of-batches", sums_of_batches},
 };
 
 }  // namespace
