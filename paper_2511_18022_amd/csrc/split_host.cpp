@@ -599,6 +599,7 @@ split_status enqueue_kernels(split_ctx *ctx, const Instance &in, const EvalBuffe
     pa.sums = sum_slots(p.form, L.capT, S);
     pa.sums.base = b.d_sums;
     pa.pair = p.pair ? 1 : 0;
+    pa.threads = L.capT > 2 * ctx->cus && p.maxn <= 256 ? 256 : 1024;
     pa.N = in.N;
     pa.kind = in.kind;
     pa.xy = in.d_xy;

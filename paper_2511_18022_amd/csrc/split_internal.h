@@ -130,6 +130,7 @@ struct PrepArgs {
     const int32_t *src_tours;
     SumSlots sums;
     int32_t pair;              // 1: also the arrays of the mirrored half
+    int32_t threads;           // of a workgroup: a multiple of 64, 64 (kMaxSlots) to 1024
     int32_t N;
     int32_t kind;          // 0: coordinates, 1: distance matrix
     const int32_t *xy;     // device [(N+1)*2]

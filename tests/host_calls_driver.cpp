@@ -29,6 +29,7 @@ std::map<std::string, int> fail_launch;  // launches of this name that fail from
 int fail_malloc = 0;                     // the fail_malloc-th device allocation from now fails
 int mallocs = 0, syncs = 0;
 size_t malloc_bytes = 0;
+int prep_threads = 0;
 double clock_us = 0.0;
 std::vector<std::string> *capture = nullptr;
 
@@ -152,7 +153,11 @@ hipError_t hipGraphExecDestroy(hipGraphExec_t e) { delete reinterpret_cast<ihipG
 
 namespace splitgpu {
 
-hipError_t launch_prep(const PrepArgs &, hipStream_t) { return launched("prep"); }
+hipError_t launch_prep(const PrepArgs &a, hipStream_t)
+{
+    prep_threads = a.threads;
+    return launched("prep");
+}
 hipError_t launch_lane(const EvalArgs &a, hipStream_t)
 {
     return launched(a.lane_block == 0 ? "lane0" : a.lane_block == 8 ? "lane8" : "lane16");
@@ -486,6 +491,26 @@ void sums_of_batches()
     CHECK(syncs <= 8 && mallocs <= 8);  // four times as much, a quarter to spare each time
 }
 
+// Workgroups of the prep kernel: small ones where more short tours come than it has places.
+void prep_workgroups()
+{
+    Ctx c(300);
+    auto threads = [&](int T, int n) {
+        std::vector<int32_t> tours, cost((size_t)T);
+        std::vector<int64_t> ptr = {0};
+        for (int t = 0; t < T; ++t) {
+            for (int k = 1; k <= n; ++k) tours.push_back(k);
+            ptr.push_back((int64_t)tours.size());
+        }
+        std::vector<int16_t> dem(300, 5);
+        CHECK(split_eval_batch(c.c, tours.data(), ptr.data(), T, dem.data(), 1, 1, 100, cost.data(), 1,
+                               nullptr, nullptr, nullptr) == SPLIT_OK);
+        return prep_threads;
+    };
+    CHECK(threads(512, 100) == 1024 && threads(513, 100) == 256);
+    CHECK(threads(513, 256) == 256 && threads(513, 257) == 1024 && threads(2, 10) == 1024);
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
@@ -497,6 +522,7 @@ const Scenario kScenarios[] = {
     {"graph-replays-choose-by-their-tours", graph_replays_choose_by_their_tours},
     {"two-wavefronts-by-length-and-items", two_wavefronts_by_length_and_items},
     {"sums-of-batches", sums_of_batches},
+    {"prep-workgroups", prep_workgroups},
 };
 
 }  // namespace

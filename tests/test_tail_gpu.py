@@ -93,6 +93,21 @@ def test_long_tours_leave_room_for_fewer_wavefronts(sg):
     ctx.close()
 
 
+@pytest.mark.parametrize("S", [3, 200])
+def test_many_short_tours_over_the_edges_of_small_workgroups(sg, S):
+    # more tours than the prep kernel's large workgroups have places: 256 threads a tour
+    N, T = 256, 600
+    g = np.random.default_rng(S)
+    xy = g.integers(0, 1000, size=(N + 1, 2)).astype(np.int32)
+    ctx = sg.SplitContext(0)
+    ctx.set_coords(xy)
+    dem = g.integers(0, 20, size=(N, S), dtype=np.int16)
+    lens = [1, 2, 63, 64, 65, 127, 128, 129, 191, 192, 193, 255, 256] * 47
+    tours = [g.permutation(np.arange(1, N + 1))[:n].astype(np.int32) for n in lens[:T]]
+    assert sum(check(ctx, sg, tours, oracle.dist_matrix(xy), dem, 100)) == 0
+    ctx.close()
+
+
 def test_a_few_marks_cost_little(sg):
     # four scenarios of every tour go one by one: a call of a few ms, not one of tens
     T, N, S = 256, 600, 16_384
