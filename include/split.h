@@ -281,10 +281,13 @@ split_status split_graph_stats(split_graph *graph, split_stats *stats, int32_t *
 void split_graph_destroy(split_graph *graph);
 
 /*
- * Kernel timing for benchmarks: when enabled, split_eval records HIP events around its
- * dominant kernel on the caller's stream. split_timing_get waits for the last call and
- * returns the accumulated dominant-kernel milliseconds and the number of timed launches
- * since the last reset, with the name of the kernel timed.
+ * Kernel timing for benchmarks: when enabled, split_eval records HIP events around its DP kernel
+ * and, in the lane form, its tail kernel on the caller's stream, and times the one of the two that
+ * took longer: the tail kernel where it does the DP of long windows. split_timing_get waits for
+ * the last call and returns the accumulated milliseconds and the number of timed calls since the
+ * last reset, with the name of the kernel timed in the latest one. A short tour that is evaluated
+ * in one launch is timed as a whole, under the name of the form (split_lane_kernel or
+ * split_wave_kernel) that SPLIT_FORM_AUTO's rule gives it.
  */
 split_status split_timing_enable(split_ctx *ctx, int enable);
 split_status split_timing_get(split_ctx *ctx, double *ms_total, int64_t *launches,

@@ -113,6 +113,14 @@ struct Plan {
     uint32_t lane_bytes = 0;
 };
 
+// A timed call: its DP kernel from start to dp, and (lane form: the tail kernel may do the DP) its
+// tail kernel from dp to end.
+struct TimedCall {
+    hipEvent_t start = nullptr, dp = nullptr, end = nullptr;
+    const char *name = "";
+    bool tail = false;
+};
+
 // The instance as the kernels see it (a graph keeps its own copy).
 struct Instance {
     int32_t N = 0;
@@ -158,8 +166,8 @@ struct split_ctx {
 
     // timing of the dominant kernel
     bool timing = false;
-    std::vector<std::pair<hipEvent_t, hipEvent_t>> tpairs;
-    size_t tpairs_used = 0;
+    std::vector<TimedCall> timed;
+    size_t timed_used = 0;
     double ms_acc = 0.0;
     int64_t launches = 0;
     std::vector<float> ms_samples;  // per timed launch since the last reset
@@ -345,36 +353,56 @@ split_status ensure_host(split_ctx *ctx, int64_t stage_bytes, int32_t T)
 
 split_status collect_timing(split_ctx *ctx)
 {
-    for (size_t k = 0; k < ctx->tpairs_used; ++k) {
-        HIP_TRY(ctx, hipEventSynchronize(ctx->tpairs[k].second));
-        float ms = 0.f;
-        HIP_TRY(ctx, hipEventElapsedTime(&ms, ctx->tpairs[k].first, ctx->tpairs[k].second));
+    for (size_t k = 0; k < ctx->timed_used; ++k) {
+        const TimedCall &c = ctx->timed[k];
+        HIP_TRY(ctx, hipEventSynchronize(c.tail ? c.end : c.dp));
+        float ms = 0.f, tail_ms = 0.f;
+        HIP_TRY(ctx, hipEventElapsedTime(&ms, c.start, c.dp));
+        if (c.tail) HIP_TRY(ctx, hipEventElapsedTime(&tail_ms, c.dp, c.end));
+        ctx->tname = c.name;
+        if (tail_ms > ms) {
+            ms = tail_ms;
+            ctx->tname = tail_kernel_name();
+        }
         ctx->ms_acc += ms;
         ctx->launches += 1;
         ctx->ms_samples.push_back(ms);
     }
-    ctx->tpairs_used = 0;
+    ctx->timed_used = 0;
     return SPLIT_OK;
 }
 
-split_status timing_begin(split_ctx *ctx, hipStream_t stream, hipEvent_t *stop_out)
+// The events of a call whose DP kernel is `name`, the first one recorded; NULL when nothing is timed.
+split_status timing_begin(split_ctx *ctx, hipStream_t stream, const char *name, TimedCall **out)
 {
-    *stop_out = nullptr;
+    *out = nullptr;
     if (!ctx->timing) return SPLIT_OK;
-    if (ctx->tpairs_used == (size_t)kMaxTimingPairs) {
+    if (ctx->timed_used == (size_t)kMaxTimingPairs) {
         split_status st = collect_timing(ctx);
         if (st != SPLIT_OK) return st;
     }
-    if (ctx->tpairs_used == ctx->tpairs.size()) {
-        hipEvent_t a, b;
-        HIP_TRY(ctx, hipEventCreate(&a));
-        HIP_TRY(ctx, hipEventCreate(&b));
-        ctx->tpairs.emplace_back(a, b);
+    if (ctx->timed_used == ctx->timed.size()) {
+        TimedCall c;
+        if (hipEventCreate(&c.start) != hipSuccess || hipEventCreate(&c.dp) != hipSuccess ||
+            hipEventCreate(&c.end) != hipSuccess) {
+            for (hipEvent_t e : {c.start, c.dp, c.end})
+                if (e) (void)hipEventDestroy(e);
+            return fail(ctx, SPLIT_E_HIP, "timing: hipEventCreate failed");
+        }
+        ctx->timed.push_back(c);
     }
-    auto &pr = ctx->tpairs[ctx->tpairs_used++];
-    HIP_TRY(ctx, hipEventRecord(pr.first, stream));
-    *stop_out = pr.second;
+    TimedCall &c = ctx->timed[ctx->timed_used];
+    HIP_TRY(ctx, hipEventRecord(c.start, stream));
+    c.name = name;
+    c.tail = false;
+    *out = &c;
     return SPLIT_OK;
+}
+
+// Counts a call whose kernels were all launched and whose events were all recorded.
+void timing_end(split_ctx *ctx, const TimedCall *c)
+{
+    if (c) ++ctx->timed_used;
 }
 
 void fill_stats(const TourResult &d, int64_t S, split_stats *out)
@@ -631,26 +659,31 @@ split_status enqueue_kernels(split_ctx *ctx, const Instance &in, const EvalBuffe
     ea.wave_grid = p.wave_grid;
     ea.maxn = p.maxn;
 
-    hipEvent_t stop = nullptr;
+    const char *name = p.form == SPLIT_FORM_WAVE   ? wave_kernel_name()
+                       : p.form == SPLIT_FORM_MASK ? mask_kernel_name()
+                       : p.pair                    ? pair_kernel_name()
+                                                   : lane_kernel_name();
+    ctx->tname = name;
+    TimedCall *tc = nullptr;
     if (timed) {
-        split_status st = timing_begin(ctx, stream, &stop);
+        split_status st = timing_begin(ctx, stream, name, &tc);
         if (st != SPLIT_OK) return st;
     }
     if (p.form == SPLIT_FORM_WAVE) {
-        ctx->tname = wave_kernel_name();
         HIP_TRY(ctx, launch_wave_all(ea, stream));
-        if (stop) HIP_TRY(ctx, hipEventRecord(stop, stream));
     } else if (p.form == SPLIT_FORM_MASK) {
-        ctx->tname = mask_kernel_name();
         HIP_TRY(ctx, launch_mask(ea, b.d_mask, S, stream));
         HIP_TRY(ctx, launch_masked_dp(ea, b.d_mask, S, stream));
-        if (stop) HIP_TRY(ctx, hipEventRecord(stop, stream));
     } else {
-        ctx->tname = lane_kernel_name();
         HIP_TRY(ctx, p.pair ? launch_pair(ea, stream) : launch_lane(ea, stream));
-        if (stop) HIP_TRY(ctx, hipEventRecord(stop, stream));
     }
+    if (tc) HIP_TRY(ctx, hipEventRecord(tc->dp, stream));
     HIP_TRY(ctx, launch_tail(ea, stream));
+    if (tc && p.form == SPLIT_FORM_LANE) {
+        HIP_TRY(ctx, hipEventRecord(tc->end, stream));
+        tc->tail = true;
+    }
+    timing_end(ctx, tc);
     return SPLIT_OK;
 }
 
@@ -678,12 +711,14 @@ split_status eval_small(split_ctx *ctx, const int32_t *tour, int32_t n, const Pl
     for (int32_t k = 0; k < kSmallN; ++k) a.tour[k] = tour[k < n ? k : n - 1];
     const int slot = ctx->stage;
     ctx->stage = (ctx->stage + 1) % kStages;
-    hipEvent_t stop = nullptr;
-    st = timing_begin(ctx, stream, &stop);
-    if (st != SPLIT_OK) return st;
+    // timed under the name of the form that the rule for several launches takes
     ctx->tname = p.form == SPLIT_FORM_LANE ? lane_kernel_name() : wave_kernel_name();
+    TimedCall *tc = nullptr;
+    st = timing_begin(ctx, stream, ctx->tname, &tc);
+    if (st != SPLIT_OK) return st;
     HIP_TRY(ctx, launch_small(a, stream));
-    if (stop) HIP_TRY(ctx, hipEventRecord(stop, stream));
+    if (tc) HIP_TRY(ctx, hipEventRecord(tc->dp, stream));
+    timing_end(ctx, tc);
     HIP_TRY(ctx, hipEventRecord(ctx->stage_ev[slot], stream));
     ctx->stage_ev_used[slot] = true;
     ctx->last_ev = ctx->stage_ev[slot];
@@ -861,10 +896,8 @@ void split_ctx_destroy(split_ctx *ctx)
             if (ctx->stage_ev[k]) (void)hipEventDestroy(ctx->stage_ev[k]);
         }
         if (ctx->h_stats) (void)hipHostFree(ctx->h_stats);
-        for (auto &pr : ctx->tpairs) {
-            (void)hipEventDestroy(pr.first);
-            (void)hipEventDestroy(pr.second);
-        }
+        for (const TimedCall &c : ctx->timed)
+            for (hipEvent_t e : {c.start, c.dp, c.end}) (void)hipEventDestroy(e);
     }
     delete ctx;
 }

@@ -192,6 +192,8 @@ hipError_t launch_masked_dp(const EvalArgs &a, const int16_t *mask, long long ma
                             hipStream_t stream);
 const char *mask_kernel_name();
 const char *lane_kernel_name();
+const char *pair_kernel_name();
+const char *tail_kernel_name();
 const char *wave_kernel_name();
 
 // Device scratch of the allocation-free evaluation: kScratchBytes per GPU, 256-byte aligned.

@@ -1900,6 +1900,8 @@ hipError_t launch_masked_dp(const EvalArgs &a, const int16_t *mask, long long ma
 const char *mask_kernel_name() { return "split_mask_kernel+split_masked_dp_kernel"; }
 
 const char *lane_kernel_name() { return "split_lane_kernel"; }
+const char *pair_kernel_name() { return "split_pair_kernel"; }
+const char *tail_kernel_name() { return "split_tail_kernel"; }
 const char *wave_kernel_name() { return "split_wave_kernel"; }
 
 }  // namespace splitgpu

@@ -179,6 +179,8 @@ hipError_t launch_masked_dp(const EvalArgs &, const int16_t *, long long, hipStr
     return launched("masked_dp");
 }
 const char *lane_kernel_name() { return "split_lane_kernel"; }
+const char *pair_kernel_name() { return "split_pair_kernel"; }
+const char *tail_kernel_name() { return "split_tail_kernel"; }
 const char *wave_kernel_name() { return "split_wave_kernel"; }
 const char *mask_kernel_name() { return "split_mask_kernel+split_masked_dp_kernel"; }
 hipError_t scratch_address(int, void **p)
@@ -511,6 +513,45 @@ void prep_workgroups()
     CHECK(threads(513, 256) == 256 && threads(513, 257) == 1024 && threads(2, 10) == 1024);
 }
 
+// The timed interval is that of the kernel that took longest, and has its name.
+void timing_names_the_dominant_kernel()
+{
+    const struct { int n; int64_t S; double lane, pair, tail; const char *name; double us; } cases[] = {
+        {100, 10000, 50, 1, 5, "split_lane_kernel", 50},
+        {700, 10000, 1, 60, 5, "split_pair_kernel", 60},
+        {700, 10000, 1, 6, 140, "split_tail_kernel", 140},   // windows past the lane kernel's
+        {100, 100000, 30, 1, 400, "split_tail_kernel", 400}};
+    for (const auto &x : cases) {
+        cost_us = {{"prep", 7}, {"lane0", x.lane}, {"pair0", x.pair}, {"tail", x.tail}, {"wave", 90}};
+        Ctx c(x.n);
+        std::vector<int32_t> tour, cost((size_t)x.S);
+        for (int k = 1; k <= x.n; ++k) tour.push_back(k);
+        std::vector<int16_t> dem((size_t)x.n * x.S, 5);
+        CHECK(split_timing_enable(c.c, 1) == SPLIT_OK);
+        double ms = 0.0;
+        int64_t launches = 0, samples = 0;
+        const char *name = nullptr;
+        auto eval = [&] {
+            CHECK(split_eval(c.c, tour.data(), x.n, dem.data(), x.S, x.S, 100, cost.data(), nullptr,
+                             nullptr) == SPLIT_OK);
+        };
+        for (int k = 0; k < 3; ++k) eval();
+        CHECK(split_timing_get(c.c, &ms, &launches, &name) == SPLIT_OK);
+        CHECK(launches == 3 && ms > 2.999e-3 * x.us && ms < 3.001e-3 * x.us);
+        CHECK(strcmp(name, x.name) == 0);
+        float one[3];
+        CHECK(split_timing_samples(c.c, one, 3, &samples) == SPLIT_OK && samples == 3);
+        CHECK(one[2] > 0.999e-3 * x.us && one[2] < 1.001e-3 * x.us);
+        // the wave form's tail only reports
+        CHECK(split_set_form(c.c, SPLIT_FORM_WAVE) == SPLIT_OK);
+        CHECK(split_timing_reset(c.c) == SPLIT_OK);
+        eval();
+        CHECK(split_timing_get(c.c, &ms, &launches, &name) == SPLIT_OK);
+        CHECK(strcmp(name, "split_wave_kernel") == 0 && launches == 1 && ms > 0.0899 && ms < 0.0901);
+    }
+    cost_us.clear();
+}
+
 struct Scenario {
     const char *name;
     void (*run)();
@@ -523,6 +564,7 @@ const Scenario kScenarios[] = {
     {"two-wavefronts-by-length-and-items", two_wavefronts_by_length_and_items},
     {"sums-of-batches", sums_of_batches},
     {"prep-workgroups", prep_workgroups},
+    {"timing-names-the-dominant-kernel", timing_names_the_dominant_kernel},
 };
 
 }  // namespace

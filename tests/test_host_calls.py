@@ -24,6 +24,7 @@ def driver(tmp_path_factory):
     "flag-of-a-failed-pass", "scenarios-after-a-failed-allocation",
     "autotune-times-the-own-choice", "graph-replays-choose-by-their-tours",
     "two-wavefronts-by-length-and-items", "sums-of-batches", "prep-workgroups",
+    "timing-names-the-dominant-kernel",
 ])
 def test_host_calls(driver, scenario):
     # nothing preloaded comes before the sanitizer's runtime, which the driver links first
