@@ -673,8 +673,9 @@ def main():
                     help="lane form with these launch choices instead of autotuning")
     ap.add_argument("--lane-block", type=int, default=0, choices=[0, 8, 16],
                     help="lane form: states per block of the scenario-per-lane kernel (0: the "
-                         "library default, 16; 8 suits windows shorter than about 24); batch "
-                         "workloads take it with --tuning, else the autotuner chooses")
+                         "library's choice by the windows of every work item; 8 suits windows "
+                         "shorter than about 24); batch workloads take it with --tuning, else the "
+                         "autotuner chooses")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-alu-count", action="store_true",
                     help="skip counting the window work that sizes the ALU roofline")
@@ -815,7 +816,7 @@ def main():
 
     config = {"workload": w.name, "S": w.S, "Q": w.Q, "seed": w.seed, "demand": COPULA_DESC,
               "coords": "integer uniform 1000x1000, rounded Euclidean int32 costs",
-              "kernel": kname, "form": args.form, "lane_block": ctx.tuning().lane_block or 16,
+              "kernel": kname, "form": args.form, "lane_block": ctx.tuning().lane_block,
               "fallback_scenarios": n_fallback,
               "launch": launch, "eager_ms_per_step": ms_eager,
               "h2d_GBps": dem.numel() * 2 / h2d_s / 1e9}

@@ -21,8 +21,8 @@
  *    scenario-per-lane kernel compares load differences in 16 bits, exact while
  *    8 * max(q) + Q < 2^15; evaluations with Q > 16383 run in the wavefront-per-scenario form
  *    (exact for any Q) whatever form is chosen, and single scenarios outside the bound are
- *    handed to it. SPLIT_MAX_N is the wave kernel's LDS budget: it holds a scenario's prefix
- *    loads and DP values (8 bytes per position) in LDS.
+ *    finished that way too, by the tail kernel. SPLIT_MAX_N is the LDS budget of that way: it
+ *    holds a scenario's prefix loads and DP values (8 bytes per position) in LDS.
  */
 #ifndef SPLIT_H
 #define SPLIT_H
@@ -50,7 +50,9 @@ typedef enum {
 typedef enum {
     SPLIT_FORM_AUTO = 0, /* wavefront-per-scenario for short tours over few scenarios (n <= 32
                             at S <= 256, n <= 24 at S <= 1024, n <= 16 at S <= 4096),
-                            scenario-per-lane otherwise */
+                            scenario-per-lane otherwise; one tour of up to 32 customers over up
+                            to 32768 scenarios, arcs up to 2047 and no other launch choice made:
+                            one launch for the whole evaluation */
     SPLIT_FORM_LANE = 1, /* one scenario per lane; sliding-window minimum in LDS (Q <= 16383;
                             a larger Q runs in the wave form) */
     SPLIT_FORM_WAVE = 2, /* one scenario per wavefront; lanes over predecessors p */
@@ -68,8 +70,9 @@ typedef enum {
  *  mean = (double)sum / S
  *  var  = (((double)(S*sumsq - sum^2)) / S) / (S - 1)   sample variance, 0 when S == 1;
  *         the 128-bit numerator is exact and rounded to double once.
- *  n_fallback = scenarios whose capacity window outgrew the fast kernel's history and were
- *         re-evaluated by the general kernel (diagnostic only; results are exact either way).
+ *  n_fallback = scenarios that the lane kernel's blocks cannot hold (a capacity window past its
+ *         history, or a value past 16 bits) and that the tail kernel evaluated (diagnostic only;
+ *         results are exact either way).
  */
 typedef struct {
     int64_t sum;

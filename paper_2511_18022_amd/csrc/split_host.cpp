@@ -584,8 +584,8 @@ Plan make_plan(const split_ctx *ctx, const split_tuning &tu, int64_t S, int64_t 
     p.lane_static = fixed;
     p.lane_uniform = uniform;
     // Left to the library, the block length follows the windows of each item's first positions,
-    // where arcs this short keep every suffix offset of either length within 16 bits (at most 2 max_arc a state):
-    // n_fallback then does not depend on the length chosen.
+    // where arcs this short keep every suffix offset of either length within 16 bits (at most
+    // 2 max_arc a state): n_fallback then does not depend on the length chosen.
     const bool by_class = tu.lane_block == 0 && max_arc <= kClassMaxArc;
     p.lane_block = by_class ? 0 : tu.lane_block == 8 ? 8 : 16;
     p.tail_grid = ctx->cus * kTailPerCu;
@@ -750,8 +750,8 @@ split_status eval_batch(split_ctx *ctx, const char *who, const int32_t *tours,
     // A short tour over few scenarios, all choices left to the library: one launch instead of three,
     // which take longer than the work (1 to 32 customers, S = 256 to 32,768: 23 to 30 us a call against
     // 32 to 47, 1.4 to 1.6 times at every corner; the bounds keep the scan of 32 predecessors and the
-    // 128 parts to add up small). Short arcs keep every
-    // suffix offset within 16 bits, so only the demand bound can count towards n_fallback.
+    // 128 parts to add up small). Short arcs keep every suffix offset within 16 bits, so only the
+    // demand bound can count towards n_fallback.
     const split_tuning &tu = ctx->tuning;
     if (T == 1 && bi.maxn <= kSmallN && S <= kSmallS && ctx->inst.max_arc <= kClassMaxArc &&
         tu.form == SPLIT_FORM_AUTO && tu.lane_per_cu == 0 && tu.lane_block == 0 && tu.wave_grid == 0)
@@ -1449,7 +1449,8 @@ split_status split_graph_create(split_ctx *ctx, int32_t max_T, int64_t max_total
     // One graph per host slot: the kernels read the slot's header and report to its results. Where
     // the instance's tours may run in the pair kernel, one with it and one without: which is faster
     // follows the tours of a replay (S = 10,000, graph of one tour over 1000 customers: 8 customers
-    // 62 us with, 47 without; 100 customers 64 and 56; 400 customers 81 and 92 with blocks of 16 before the pair kernel).
+    // 62 us with it, 47 without; 100 customers 64 and 56; eight tours of 8 to 300 over 5,000
+    // scenarios 111 and 87).
     for (int v = 0; v < kGraphSlots * 2; ++v) {
         const int k = v / 2, pair = v % 2;
         if (pair && !gr->plan.pair) continue;

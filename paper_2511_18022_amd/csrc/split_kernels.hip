@@ -988,8 +988,7 @@ __device__ __forceinline__ bool windows_long(const uint16_t (&qA)[16], const uin
 // 10^5, and redoing their items made a call of 849 scenarios 121 us instead of 93.
 // The class only chooses a kernel: what outgrows its history all the same is redone by the long one.
 // Measured, whole calls: 200 customers, windows of 13, S = 10^5: 83 us (90 in blocks of 16);
-// 701 customers, windows of 60, S = 20,011: 181 us (14,760 with blocks of 16 first and the rest one
-// scenario per wavefront).
+// 1000 customers, windows of 60, S = 10,000: 180 us (261 with blocks of 16 first).
 enum { kWindowsMid, kWindowsShort, kWindowsLong };
 __device__ __forceinline__ int window_class(const uint16_t (&qA)[16], const uint16_t (&qB)[16],
                                             const uint16_t (&qC)[16], int n, int Q,
