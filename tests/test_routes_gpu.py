@@ -120,3 +120,33 @@ def test_autotuned_calls_are_no_slower_than_the_default(sg, n, S, law, Q):
     print(f"[routes] n={n} S={S}: default {default:.4f} ms, {tu} {tuned:.4f} ms", flush=True)
     assert tuned <= 1.15 * default
     ctx.close()
+
+
+@pytest.mark.parametrize("lens,S", [([8], 10_000), ([8, 12, 100, 100, 200, 200, 250, 300], 5000)])
+def test_replays_of_short_tours_take_one_wavefront_an_item(sg, lens, S):
+    # a graph over 1000 customers with few work items: halves for long tours, not for these
+    N = 1000
+    g = np.random.default_rng(9)
+    ctx = sg.SplitContext(0)
+    ctx.set_coords(gen.coords(65, N))
+    dem = torch.randint(10, 31, (N, S), dtype=torch.int16, device="cuda")
+    tours = [g.permutation(np.arange(1, N + 1))[:n].astype(np.int32) for n in lens]
+    times = {}
+    for name, tuning in (("own", sg.SplitTuning()), ("lane", sg.SplitTuning(lane_per_cu=8))):
+        ctx.set_tuning(tuning)
+        graph = ctx.graph(len(lens), len(lens) * N, dem, 500)
+
+        def call():
+            graph.launch(tours)
+            graph.stats()
+
+        times[name] = least_ms(call, reps=9, inner=50)
+        times[name, "cost"] = graph.cost.cpu().numpy()
+        times[name, "fallback"] = [s.n_fallback for s in graph.stats()[0]]
+        graph.close()
+    print(f"[routes] replay of {lens}: {times['own']:.4f} ms, lane kernel {times['lane']:.4f} ms",
+          flush=True)
+    assert np.array_equal(times["own", "cost"], times["lane", "cost"])
+    assert times["own", "fallback"] == times["lane", "fallback"]
+    assert times["own"] <= 1.12 * times["lane"]
+    ctx.close()
