@@ -655,6 +655,9 @@ split_status enqueue_kernels(split_ctx *ctx, const Instance &in, const EvalBuffe
     ea.lane_uniform = p.lane_uniform ? 1 : 0;
     ea.lane_block = p.lane_block;
     ea.recount = p.form == SPLIT_FORM_LANE && p.lane_block != 8 ? 1 : 0;
+    // blocks of 16 in one wavefront hold every window of a tour of fewer than 64 customers (blocks of 8
+    // do not, and the pair kernel marks more than it has to)
+    ea.history_min_n = p.form == SPLIT_FORM_LANE && p.lane_block == 16 && !p.pair ? 64 : 0;
     ea.tail_grid = p.tail_grid;
     ea.wave_grid = p.wave_grid;
     ea.maxn = p.maxn;

@@ -31,10 +31,8 @@ split_status ctx_fail(split_ctx *ctx, split_status st, const char *fmt, ...);
 // "Infinity" for DP values. Host checks guarantee |DP value| + |weight| < 2^30.
 constexpr int32_t kInf = 0x3fffffff;
 
-// Cost marks of a scenario that a DP kernel leaves to the tail kernel (costs are >= 0): a window past
-// the history, and values past the 16 bits of blocks of 16 states.
+// Cost mark of a scenario that a DP kernel leaves to the tail kernel (costs are >= 0).
 constexpr int32_t kCostOvf = INT32_MIN;
-constexpr int32_t kCostWide = INT32_MIN + 1;
 
 // Device-side flags of one tour (zeroed by the prep kernel of each call).
 struct DevStats {
@@ -159,6 +157,7 @@ struct EvalArgs {
     int32_t lane_uniform;    // lane kernel: 1 = every tour of the launch has the same length
     int32_t lane_block;      // lane kernel block length: 16 or 8 states, 0 by the windows
     int32_t recount;         // 1: the tail kernel counts the scenarios past the lane kernel's history
+    int32_t history_min_n;   // tail kernel: no mark of a shorter tour is for its windows
     int32_t tail_grid;       // tail kernel workgroups (at most)
     int32_t wave_grid;       // wave kernel workgroups of a full evaluation (form wave)
     int32_t maxn;            // bound on the tour lengths (sizes the wave kernel's LDS)

@@ -847,10 +847,17 @@ __device__ __forceinline__ LaneTour lane_tour(const EvalArgs &a, int t)
     return r;
 }
 
+// Counts are exact only while 8 * max(q) + Q < 2^15 (qor >= max(q), in either half); bit 15 (a negative
+// int16 demand) also lands here, and the general kernel reports it.
+__device__ __forceinline__ bool past_bound(uint32_t qor, int Q)
+{
+    return 8u * ((qor | (qor >> 16)) & 0xFFFFu) + (uint32_t)Q > 32767u;
+}
+
 // States 0..n of a tour for the scenarios at byte offset lane_off (one per lane) of its demand
-// rows; qA, qB and qC hold the demands of blocks 0, 1 and 2. H = 256: ends where every lane that is
-// wanted has outgrown the history (one scenario with windows of 500 among 2^20: 1.70 ms a call
-// without, 1.67 with).
+// rows; qA, qB and qC hold the demands of blocks 0, 1 and 2. H = 256: ends where no lane that is
+// wanted can be finished any more (one scenario with windows of 500 among 2^20: 1.70 ms a call
+// without, 1.64 with).
 template <int LB, int H, bool HALF = false>
 __device__ __forceinline__ void lane_run(LaneLds<H> &L, const LaneTour &tr, int Q,
                                          __amdgpu_buffer_rsrc_t rsrc, uint32_t lane_off,
@@ -895,7 +902,7 @@ __device__ __forceinline__ void lane_run(LaneLds<H> &L, const LaneTour &tr, int 
     // kSteps steps per iteration keep these roles constant (H = 64: and the LDS rows of a step)
     for (int c = 0; c <= nb; c += C::kSteps) {
         if (by_progress) item_priority(c, nb);
-        if (H > 64 && !__any(wanted && st.ovf == 0)) break;
+        if (H > 64 && !__any(wanted && st.ovf == 0 && !past_bound(st.qor, Q))) break;
         const int R = H == 64 ? 0 : c & (C::kRing - 1);
         lane_step<LB, H, HALF>(L, lane, R, c, n, fill, QQ, rsrc, wrsrc, rowoff, lane_off, w, qB, qD, sA, sB, wA, wB, st);
         lane_step<LB, H, HALF>(L, lane, R + 1, c + 1, n, fill, QQ, rsrc, wrsrc, rowoff, lane_off, w, qC, qA, sB, sA, wB, wA, st);
@@ -908,14 +915,12 @@ __device__ __forceinline__ void lane_run(LaneLds<H> &L, const LaneTour &tr, int 
             lane_step<LB, H, HALF>(L, lane, 7, c + 7, n, fill, QQ, rsrc, wrsrc, rowoff, lane_off, w, qA, qC, sB, sA, wB, wA, st);
         }
     }
-    // counts exact only while 8 * max(q) + Q < 2^15 (qor >= max(q)); bit 15 (a negative
-    // int16 demand) also lands here, and the general kernel reports it
-    st.ovf |= 8u * ((st.qor | (st.qor >> 16)) & 0xFFFFu) + (uint32_t)Q > 32767u;
+    st.ovf |= past_bound(st.qor, Q);
 }
 
 // The end of a work item: the costs of the scenarios that are done; the others are marked for the
-// tail kernel, which also counts them under `recount`. ovf: negative where a window outgrew the
-// history, positive where only demands or suffix offsets past 16 bits stand against blocks of 16.
+// tail kernel, which also counts them under `recount`. (A second mark, for scenarios that no history
+// helps, cost 0.7% of a batch in the code around the lane kernel's loop.)
 __device__ __forceinline__ void lane_finish(const EvalArgs &a, int t, long long scen, int ovf,
                                             bool err, int gres, bool recount)
 {
@@ -923,7 +928,7 @@ __device__ __forceinline__ void lane_finish(const EvalArgs &a, int t, long long 
     const bool active = scen < a.S;
     const bool left = active && ovf != 0;
     if (active && (left || !err))
-        a.cost[(long long)t * a.ldc + scen] = !left ? gres : ovf > 0 ? kCostWide : kCostOvf;
+        a.cost[(long long)t * a.ldc + scen] = left ? kCostOvf : gres;
     item_costs(a.sums, t, scen >> 6, active && !left && !err ? (uint32_t)gres : 0u);
     const unsigned long long m = __ballot(left);
     if (m != 0 && threadIdx.x == 0) {
@@ -1045,8 +1050,7 @@ __device__ __forceinline__ void lane_item(LaneLds<64> &L, const EvalArgs &a, int
         lane_load_block<8>(rsrc, tr.rowoff, lane_off, 2, qC);
         LaneState<8, 64> st;
         lane_run<8, 64>(L, tr, a.Q, rsrc, lane_off, qA, qB, qC, prio, st);
-        // offsets past 16 bits over 8 states may still fit over 16: only the demands' bit counts
-        lane_finish(a, t, scen, st.ovf == 1 || st.ovf == 0 ? st.ovf : INT_MIN, st.err, st.gres, false);
+        lane_finish(a, t, scen, st.ovf, st.err, st.gres, false);
     } else {
         uint16_t qA[16], qB[16], qC[16];
         lane_load_block<16>(rsrc, tr.rowoff, lane_off, 0, qA);
@@ -1054,7 +1058,7 @@ __device__ __forceinline__ void lane_item(LaneLds<64> &L, const EvalArgs &a, int
         lane_load_block<16>(rsrc, tr.rowoff, lane_off, 2, qC);
         int cls = kWindowsMid;
         if constexpr (LB == 0) cls = window_class(qA, qB, qC, tr.n, a.Q, scen < a.S);
-        int ovf = INT_MIN, gres = 0;
+        int ovf = 1, gres = 0;
         bool err = false;
         if (__builtin_expect(cls == kWindowsMid, 1)) {
             LaneState<16, 64> st;
@@ -1199,7 +1203,7 @@ __device__ __forceinline__ int pair_item(LaneLds<64> (&L)[2], const EvalArgs &a,
     const uint32_t flags = L[1].pp[0][lane];
     const int best = pair_join<LB>(L[0], L[1], tr, a.Q, rsrc, lane_off, half.n, st);
     ovf = st.ovf | (int)(flags & 1u) |
-          (8u * ((st.qor | (st.qor >> 16)) & 0xFFFFu) + (uint32_t)a.Q > 32767u ? 1 : 0);
+          (past_bound(st.qor, a.Q) ? 1 : 0);
     err = st.err || (flags & 2u);
     return total + best;
 }
@@ -1271,7 +1275,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void s
             cost = pair_item<8>(L, a, tr, half, total, back, lane_off, rsrc, rA, rB, rC, ovf, err);
         }
     }
-    if (!back) lane_finish(a, t, scen, ovf != 0 ? INT_MIN : 0, err, cost, true);
+    if (!back) lane_finish(a, t, scen, ovf, err, cost, true);
 }
 
 // ------------------------------------------------------------------------- wave kernel
@@ -1420,20 +1424,19 @@ __device__ __forceinline__ void report_tour(const EvalArgs &a, int t)
                               load(&a.stats[t].ovf_count)};
 }
 
-// The scenarios that the DP kernels marked. Those past the lane kernel's history (kCostOvf) go 64 at
-// a time through its blocks of 16 over a history of 256 positions (windows of up to 239), by the
-// first wavefront. Those that outgrow this history too, and those whose suffix offsets or demands
-// pass 16 bits (kCostWide: blocks of 16 cannot hold them, whatever the history), are then finished
-// one by one, a scenario by each of the four wavefronts, in the same LDS. With a.recount the kernel
-// counts the scenarios past the lane kernel's history (n_fallback): an item is left here whole.
+// The scenarios that the DP kernels marked, 64 at a time through the lane kernel's blocks of 16 over a
+// history of 256 positions (windows of up to 239), by the first wavefront. Those that outgrow this
+// history too, or whose suffix offsets or demands pass 16 bits, are then finished one by one, a
+// scenario by each of the four wavefronts, in the same LDS. With a.recount the kernel counts the
+// scenarios past the lane kernel's history (n_fallback): an item is left here whole.
 //
 // Bound by the latency of one wavefront's serial chain: 80 KB of LDS leave two workgroups a compute
 // unit. For the blocks that is still one state of 64 scenarios per step, where one scenario per
 // wavefront leaves most lanes idle: 701 customers, windows of about 60, S = 20,011 took 14.76 ms as
 // a call; with this kernel 0.15 ms. One by one, four wavefronts a workgroup take as many scenarios
 // at once as a kernel of their own with 8 bytes of LDS a position did: 200 customers, coordinates up
-// to 10^5, S = 2^17: 4.2 ms a call (19.0 with one wavefront, 4.5 in the separate kernel); 1000
-// customers, windows of 300, S = 2^17: 33.1 (149.5 and 35.1). wave_one has to be inlined: as a call
+// to 10^5, S = 2^17: 4.3 ms a call (19.0 with one wavefront, 4.5 in the separate kernel); 1000
+// customers, windows of 300, S = 2^17: 32.8 (149.5 and 35.1). wave_one has to be inlined: as a call
 // it reads LDS through generic pointers, and keeps the blocks' registers in scratch memory (1000
 // customers, windows of 60, S = 2^20: 6.1 ms a call against 4.3).
 // Counts go to memory once per item: one atomic per scenario took 240 us of this launch there.
@@ -1460,7 +1463,7 @@ void split_tail_kernel(EvalArgs a)
         LaneLds<256> L;
         int32_t words[kTailWords];
     } lds;
-    // the scenarios of a chunk's items that are left, for the history and one by one
+    // the scenarios of a chunk's items that are left, at first and after the history
     __shared__ unsigned long long s_todo[kTailChunk], s_wide[kTailChunk];
     __shared__ uint32_t s_chunk, s_marks;
     static_assert(sizeof lds == 4 * kTailWords && kTailWords >= 2 * (SPLIT_MAX_N + 1),
@@ -1510,11 +1513,11 @@ void split_tail_kernel(EvalArgs a)
             item(i, t, sb);
             const long long scen = sb * 64 + lane;
             const int32_t mark = scen < a.S ? a.cost[(long long)t * a.ldc + scen] : 0;
-            const unsigned long long todo = __ballot(mark == kCostOvf), wide = __ballot(mark == kCostWide);
+            const unsigned long long todo = __ballot(mark == kCostOvf);
             if (lane == 0) {
                 s_todo[i] = todo;
-                s_wide[i] = wide;
-                if (todo | wide) s_marks = 1;  // whoever writes it, the same value
+                s_wide[i] = 0;
+                if (todo) s_marks = 1;  // whoever writes it, the same value
             }
         }
         __syncthreads();
@@ -1522,44 +1525,41 @@ void split_tail_kernel(EvalArgs a)
         if (marks && wave == 0) {
             for (int i = 0; i < cnt; ++i) {
                 const unsigned long long todo = s_todo[i];
-                unsigned long long wide = s_wide[i];
-                if ((todo | wide) == 0) continue;
+                if (todo == 0) continue;
                 int t;
                 long long sb;
                 item(i, t, sb);
-                int past = (int)__popcll(wide);
-                if (todo) {
-                    const bool mine = (todo >> lane) & 1;
-                    const long long scen = min(sb * 64 + lane, (long long)a.S - 1);
-                    LaneState<16, 256> st;
-                    st.ovf = 1;
-                    st.past = false;
-                    st.err = false;
-                    st.gres = 0;
-                    if (a.lane_bytes != 0) {  // the demands lie within a buffer descriptor's reach
-                        const LaneTour tr = lane_tour(a, t);
-                        const uint32_t lane_off = (uint32_t)scen * 2u;
-                        uint16_t qA[16], qB[16], qC[16];
-                        lane_load_block<16>(rsrc, tr.rowoff, lane_off, 0, qA);
-                        lane_load_block<16>(rsrc, tr.rowoff, lane_off, 1, qB);
-                        lane_load_block<16>(rsrc, tr.rowoff, lane_off, 2, qC);
-                        lane_run<16, 256>(lds.L, tr, a.Q, rsrc, lane_off, qA, qB, qC, false, st, false,
-                                          mine);
-                    }
-                    past += (int)__popcll(__ballot(mine && (st.past || st.ovf)));
-                    wide |= __ballot(mine && st.ovf);
-                    uint32_t c = 0;
-                    if (mine && st.ovf == 0) {
-                        if (st.err) {
-                            atomicOr(&a.stats[t].err_demand, 1);
-                        } else {
-                            c = (uint32_t)st.gres;
-                            a.cost[(long long)t * a.ldc + scen] = st.gres;
-                        }
-                    }
-                    const CostSums v = wave_costs(c);
-                    if (lane == 63) add_sums(sums(t, sb), v);
+                const bool mine = (todo >> lane) & 1;
+                const long long scen = min(sb * 64 + lane, (long long)a.S - 1);
+                LaneState<16, 256> st;
+                st.ovf = 1;
+                st.past = false;
+                st.err = false;
+                st.gres = 0;
+                // the demands lie within a buffer descriptor's reach, and a longer history can help (20
+                // customers, coordinates up to 10^5, S = 2^20: 1.04 ms a call, 1.35 with the blocks first)
+                const LaneTour tr = lane_tour(a, t);
+                if (a.lane_bytes != 0 && tr.n >= a.history_min_n) {
+                    const uint32_t lane_off = (uint32_t)scen * 2u;
+                    uint16_t qA[16], qB[16], qC[16];
+                    lane_load_block<16>(rsrc, tr.rowoff, lane_off, 0, qA);
+                    lane_load_block<16>(rsrc, tr.rowoff, lane_off, 1, qB);
+                    lane_load_block<16>(rsrc, tr.rowoff, lane_off, 2, qC);
+                    lane_run<16, 256>(lds.L, tr, a.Q, rsrc, lane_off, qA, qB, qC, false, st, false, mine);
                 }
+                const int past = (int)__popcll(__ballot(mine && (st.past || st.ovf)));
+                const unsigned long long wide = __ballot(mine && st.ovf);
+                uint32_t c = 0;
+                if (mine && st.ovf == 0) {
+                    if (st.err) {
+                        atomicOr(&a.stats[t].err_demand, 1);
+                    } else {
+                        c = (uint32_t)st.gres;
+                        a.cost[(long long)t * a.ldc + scen] = st.gres;
+                    }
+                }
+                const CostSums v = wave_costs(c);
+                if (lane == 63) add_sums(sums(t, sb), v);
                 if (lane == 0) {
                     if (a.recount && past) atomicAdd(&a.stats[t].ovf_count, past);
                     s_wide[i] = wide;
