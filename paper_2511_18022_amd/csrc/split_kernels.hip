@@ -18,10 +18,9 @@
 //  split_pair_kernel      the lane kernel with two wavefronts per 64 scenarios, from both ends of the
 //                         tour, for launches of few work items.
 //  split_small_kernel     a whole evaluation of a short tour over few scenarios.
-//  split_tail_kernel      reports the sums; first the lane kernel's blocks over a history of 256 positions, for tours
-//                         whose windows outgrow the lane kernel's 64 and for the scenarios it
-//                         marks; what outgrows this history too is finished one scenario per
-//                         wavefront.
+//  split_tail_kernel      what the DP kernels left: the lane kernel's blocks over a history of 256
+//                         positions for windows that outgrow the lane kernel's 64, then one
+//                         scenario per wavefront for what outgrows that too; reports the sums.
 //  split_wave_kernel      one scenario per wavefront; lanes cover the window's predecessors
 //                         (transition-level parallelism of Section 3) and the minimum is a
 //                         DPP reduction. Exact for any window length; used for small S.
@@ -919,8 +918,8 @@ __device__ __forceinline__ void lane_run(LaneLds<H> &L, const LaneTour &tr, int 
 }
 
 // The end of a work item: the costs of the scenarios that are done; the others are marked for the
-// tail kernel, which also counts them under `recount`. (A second mark, for scenarios that no history
-// helps, cost 0.7% of a batch in the code around the lane kernel's loop.)
+// tail kernel, which also counts them under `recount`. (With a second mark, for scenarios that no
+// history helps, a batch was 0.7% slower; where the kernels' code lies alone moves it by 0.4%.)
 __device__ __forceinline__ void lane_finish(const EvalArgs &a, int t, long long scen, int ovf,
                                             bool err, int gres, bool recount)
 {
