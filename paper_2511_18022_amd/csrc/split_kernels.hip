@@ -946,7 +946,7 @@ __device__ __forceinline__ void lane_finish(const EvalArgs &a, int t, long long 
 // z^2 = 1.8 ln(n - 48) - 1.7 (within 0.3 for n of 65 to 5000). One in five such items has none.
 // The line: an item left to the long kernel takes 4 times the lane kernel's share of the chip, one
 // that the lane kernel marks after all, both. Measured, whole calls, 1000 customers, S = 2^20, mean
-// windows of 41, 43, 44 and 60 under Poisson demands: 1.26, 4.84, 4.24 and 4.25 ms;
+// windows of 41, 43, 44 and 60 under Poisson demands: 1.25, 4.34, 3.81 and 3.81 ms;
 // 0.95 ms under constant demands and windows of up to 47. A rule by the first 15 customers' share of
 // the capacity alone (at most 15 / 40) sent every item of all these to the long kernel.
 __device__ __forceinline__ bool windows_long(const uint16_t (&qA)[16], const uint16_t (&qB)[16],
@@ -992,7 +992,7 @@ __device__ __forceinline__ bool windows_long(const uint16_t (&qA)[16], const uin
 // 10^5, and redoing their items made a call of 849 scenarios 121 us instead of 93.
 // The class only chooses a kernel: what outgrows its history all the same is redone by the long one.
 // Measured, whole calls: 200 customers, windows of 13, S = 10^5: 83 us (90 in blocks of 16);
-// 1000 customers, windows of 60, S = 10,000: 180 us (261 with blocks of 16 first).
+// 1000 customers, windows of 60, S = 10,000: 167 us (249 with blocks of 16 first).
 enum { kWindowsMid, kWindowsShort, kWindowsLong };
 __device__ __forceinline__ int window_class(const uint16_t (&qA)[16], const uint16_t (&qB)[16],
                                             const uint16_t (&qC)[16], int n, int Q,
@@ -1432,20 +1432,20 @@ __device__ __forceinline__ void report_tour(const EvalArgs &a, int t)
 // Bound by the latency of one wavefront's serial chain: 80 KB of LDS leave two workgroups a compute
 // unit. For the blocks that is still one state of 64 scenarios per step, where one scenario per
 // wavefront leaves most lanes idle: 701 customers, windows of about 60, S = 20,011 took 14.76 ms as
-// a call; with this kernel 0.15 ms. One by one, four wavefronts a workgroup take as many scenarios
+// a call; with this kernel 0.13 ms. One by one, four wavefronts a workgroup take as many scenarios
 // at once as a kernel of their own with 8 bytes of LDS a position did: 200 customers, coordinates up
 // to 10^5, S = 2^17: 4.3 ms a call (19.0 with one wavefront, 4.5 in the separate kernel); 1000
-// customers, windows of 300, S = 2^17: 32.8 (149.5 and 35.1). wave_one has to be inlined: as a call
+// customers, windows of 300, S = 2^17: 32.7 (149.5 and 35.1). wave_one has to be inlined: as a call
 // it reads LDS through generic pointers, and keeps the blocks' registers in scratch memory (1000
-// customers, windows of 60, S = 2^20: 6.1 ms a call against 4.3).
+// customers, windows of 60, S = 2^20: 6.1 ms a call against 3.8).
 // Counts go to memory once per item: one atomic per scenario took 240 us of this launch there.
 //
 // Where something is marked, workgroups take chunks of items from a queue: marks are mostly few and
 // may come at any stride (the same scenarios of every tour, say). Up to kTailChunk items a chunk, so
 // that the queue's counter is no bottleneck, and about 16 chunks a workgroup.
-// 256 tours over 65,536 scenarios, four of them with windows of 500: 10.1 ms a call (8.9 without
+// 256 tours over 65,536 scenarios, four of them with windows of 500: 10.0 ms a call (8.9 without
 // them; 228 with items at a fixed stride and the last workgroup reporting every tour, 51 with 2,048
-// workgroups at a fixed stride); 1000 customers, S = 2^20, windows of 42, 3,279 marks: 2.1 ms (3.9
+// workgroups at a fixed stride); 1000 customers, S = 2^20, windows of 42, 3,279 marks: 1.9 ms (3.9
 // and 3.4).
 //
 // The tours' results go straight to the caller's (pinned host) memory. Where nothing was marked, each
@@ -1536,7 +1536,7 @@ void split_tail_kernel(EvalArgs a)
                 st.err = false;
                 st.gres = 0;
                 // the demands lie within a buffer descriptor's reach, and a longer history can help (20
-                // customers, coordinates up to 10^5, S = 2^20: 1.04 ms a call, 1.35 with the blocks first)
+                // customers, coordinates up to 10^5, S = 2^20: 0.90 ms a call, 1.23 with the blocks first)
                 const LaneTour tr = lane_tour(a, t);
                 if (a.lane_bytes != 0 && tr.n >= a.history_min_n) {
                     const uint32_t lane_off = (uint32_t)scen * 2u;
@@ -1583,10 +1583,12 @@ void split_tail_kernel(EvalArgs a)
                 }
             }
         }
-        // every wavefront's additions are in memory before the chunk's items count as done (the
-        // fence writes a whole L2 back: none where there was nothing to add)
+        // Every wavefront's additions are complete before the chunk's items count as done. They are
+        // atomic at the device's scope, as the count and the reads of a report are, so their
+        // completion is all that is waited for: a fence would write a whole L2 back (153 customers,
+        // windows of 56, S = 56,771: 105 us a call, 152 with a fence a chunk).
         if (marks) {
-            __threadfence();
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
         }
         for (int t = t0 + wave; (t - t0) * nsb < sb0 + cnt; t += kTailWaves) {
@@ -1596,7 +1598,7 @@ void split_tail_kernel(EvalArgs a)
             uint32_t before = 0;
             if (lane == 0) before = atomicAdd(&a.stats[t].done, mine);
             if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) + mine != (uint32_t)nsb) continue;
-            __threadfence();
+            asm volatile("" ::: "memory");
             report_tour(a, t);
         }
     }
