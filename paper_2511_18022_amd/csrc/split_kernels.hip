@@ -30,6 +30,7 @@
 #include <limits.h>
 
 #include <mutex>
+#include <type_traits>
 
 namespace splitgpu {
 
@@ -918,8 +919,7 @@ __device__ __forceinline__ void lane_run(LaneLds<H> &L, const LaneTour &tr, int 
 }
 
 // The end of a work item: the costs of the scenarios that are done; the others are marked for the
-// tail kernel, which also counts them under `recount`. (With a second mark, for scenarios that no
-// history helps, a batch was 0.7% slower; where the kernels' code lies alone moves it by 0.4%.)
+// tail kernel, which also counts them under `recount`.
 __device__ __forceinline__ void lane_finish(const EvalArgs &a, int t, long long scen, int ovf,
                                             bool err, int gres, bool recount)
 {
@@ -935,6 +935,24 @@ __device__ __forceinline__ void lane_finish(const EvalArgs &a, int t, long long 
         if (!recount) atomicAdd(&a.stats[t].ovf_count, (int)__popcll(m));
     }
     if (active && !left && err) atomicOr(&a.stats[t].err_demand, 1);
+}
+
+// Sum over the 64 lanes of a wavefront, for all of them. (With shuffles windows_long cost the lane kernel
+// 30 spilled scalars an item: 2% of a call over short tours.)
+__device__ __forceinline__ float wave_fsum(float v)
+{
+    auto add = [&v](auto ctrl, auto rows) {
+        v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value,
+                                                        decltype(rows)::value, 0xf, false));
+    };
+    using std::integral_constant;
+    add(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});  // row_shr:1
+    add(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});  // row_shr:2
+    add(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});  // row_shr:4
+    add(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});  // row_shr:8
+    add(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});  // row_bcast:15
+    add(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});  // row_bcast:31
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
 // Whether windows are so long that an item of 64 scenarios almost surely has one of more than 47
@@ -964,13 +982,8 @@ __device__ __forceinline__ bool windows_long(const uint16_t (&qA)[16], const uin
     add(qA);  // position 0 has no demand
     add(qB);
     add(qC);
-    float s1 = load, s2 = load * load;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        s1 += __shfl_xor(s1, off, 64);
-        s2 += __shfl_xor(s2, off, 64);
-        sq += __shfl_xor(sq, off, 64);
-    }
+    const float s1 = wave_fsum(load), s2 = wave_fsum(load * load);
+    sq = wave_fsum(sq);
     const float m = s1 / 64.f;  // mean load of 47 customers
     if (!(m > 0.f)) return true;
     const float cv2 = fmaxf(47.f * sq / (64.f * m * m) - 1.f, 47.f * (s2 / (64.f * m * m) - 1.f));
@@ -1087,8 +1100,11 @@ __device__ __forceinline__ void lane_item(LaneLds<64> &L, const EvalArgs &a, int
 // runs item b, then either items b + gridDim.x, b + 2 gridDim.x, ... (lane_static) or items
 // gridDim.x, gridDim.x + 1, ... taken from a queue until none is left (a grid of at least
 // T * nsb workgroups runs one item each). A queue index is fetched while the current item runs.
+// At the start of a 64 KB page: where its code lies after the kernels before it in this file moves a
+// launch by up to 0.5% (in turn, three runs each: 256 tours, S = 65,536: 8,451 us so, 8,479 without;
+// 1000 customers, S = 2^20: 930.5 and 934.1).
 template <int LB>
-__global__ __launch_bounds__(64) void split_lane_kernel(EvalArgs a)
+__global__ __launch_bounds__(64) __attribute__((aligned(65536))) void split_lane_kernel(EvalArgs a)
 {
     __shared__ LaneLds<64> L;
     const int lane = threadIdx.x;
